@@ -15,12 +15,13 @@
 //   3. a column-wise exclusive scan of that table, taken in key-major order,
 //      gives every (chunk, key) pair its first output slot, and the key
 //      starts (cell_start);
-//   4. per chunk the beads are placed in tag order: the lanes of a wavefront
-//      that share a key take consecutive slots, and the wavefronts of a
-//      workgroup take turns.
+//   4. per chunk the beads are placed in tag order: each wavefront takes a
+//      contiguous part of the chunk with its own row of running slots, and its
+//      lanes that share a key take consecutive slots. The permutation and its
+//      inverse are written together.
 // No step needs a global atomic, and the result does not depend on the input
-// order. Finally the bead arrays are gathered into the output buffers and the
-// bond table is permuted and renumbered through the inverse permutation.
+// order. Finally one pass gathers the bead arrays and the renumbered bond table
+// into the output buffers.
 #include <algorithm>
 
 #include "hpf_common.hpp"
@@ -35,14 +36,11 @@ struct SortK {
 };
 
 constexpr int kSortThreads = 256;
-constexpr int kScanPer = 16;
-constexpr int kScanTile = kSortThreads * kScanPer;   // entries per scan block
-constexpr int kScanTopThreads = 1024;
-constexpr int kScanTopPer = 8;
-constexpr int kMaxScanTiles = kScanTopThreads * kScanTopPer;
-constexpr int kChunkThreads = 256;                    // histogram / placement workgroups
-constexpr int kPlaceRegs = 16;                        // 256-tag blocks a thread holds at once
-constexpr int64_t kMinChunk = (int64_t)kChunkThreads * kPlaceRegs;   // 4096 tags (one placement round)
+constexpr int kScanThreads = 1024;
+constexpr int kChunkThreads = 256;                    // histogram workgroups
+constexpr uint32_t kRangeKeys = 2048;                 // keys above which a chunk's key range is looked up
+constexpr int kPlaceRows = 16;                        // 64-tag rows a placing wavefront loads at once
+constexpr int64_t kMinChunk = 4096;
 constexpr int64_t kSmallChunk = kChunkThreads * 4;                    // 1024 tags
 constexpr int64_t kChunksWanted = 2048;     // chunks that keep the histogram and placement passes busy
 constexpr int kColBlock = 64;                         // chunks per column-scan block
@@ -57,60 +55,38 @@ __global__ __launch_bounds__(kSortThreads) void k_fill_u32(uint32_t* __restrict_
         p[i] = v;
 }
 
+// idx = -1 (no bead carries the tag yet) and perm = identity (every output slot holds a
+// valid index even if the tags are no permutation), in one pass.
+__global__ __launch_bounds__(kSortThreads) void k_sort_init(int32_t* __restrict__ idx, int32_t* __restrict__ perm,
+                                                            int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * kSortThreads + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kSortThreads) {
+        idx[i] = -1;
+        perm[i] = (int32_t)i;
+    }
+}
+
 // ------------------------------------------------------------ scan (u32) --
 
-// Per-tile exclusive scan in place; tile totals to tile_sums.
-__global__ __launch_bounds__(kSortThreads) void k_scan_tiles(uint32_t* __restrict__ a, int64_t n,
-                                                             uint32_t* __restrict__ tile_sums)
+// In-place exclusive scan of a[0, n) by one workgroup; a[n] receives the total. n is at
+// most kMaxSortKeys, so one workgroup reads at most 36 entries per thread, and a single
+// launch replaces three (tiles, tops, add), each of which cost its ~4 us start.
+__global__ __launch_bounds__(kScanThreads) void k_scan_keys(uint32_t* __restrict__ a, uint32_t n)
 {
-    __shared__ uint32_t sh[kSortThreads / kWave + 1];
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
-    uint32_t v[kScanPer];
-    uint32_t sum = 0;
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
-        v[j] = base + j < n ? a[base + j] : 0u;
-        sum += v[j];
-    }
-    uint32_t total;
-    uint32_t run = block_excl_scan<kSortThreads>(sum, sh, &total);
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
-        if (base + j < n)
-            a[base + j] = run;
-        run += v[j];
+    __shared__ uint32_t sh[kScanThreads / kWave + 1];
+    uint32_t run = 0;
+    for (uint32_t k0 = 0; k0 < n; k0 += kScanThreads) {
+        const uint32_t k = k0 + threadIdx.x;
+        const uint32_t v = k < n ? a[k] : 0u;
+        uint32_t total;
+        const uint32_t r = block_excl_scan<kScanThreads>(v, sh, &total);
+        if (k < n)
+            a[k] = run + r;
+        run += total;
     }
     if (threadIdx.x == 0)
-        tile_sums[blockIdx.x] = total;
-}
-
-__global__ __launch_bounds__(kScanTopThreads) void k_scan_top(uint32_t* __restrict__ t, int n)
-{
-    __shared__ uint32_t sh[kScanTopThreads / kWave + 1];
-    const int base = threadIdx.x * kScanTopPer;
-    uint32_t v[kScanTopPer];
-    uint32_t sum = 0;
-#pragma unroll
-    for (int j = 0; j < kScanTopPer; ++j) {
-        v[j] = base + j < n ? t[base + j] : 0u;
-        sum += v[j];
-    }
-    uint32_t total;
-    uint32_t run = block_excl_scan<kScanTopThreads>(sum, sh, &total);
-#pragma unroll
-    for (int j = 0; j < kScanTopPer; ++j) {
-        if (base + j < n)
-            t[base + j] = run;
-        run += v[j];
-    }
-}
-
-__global__ __launch_bounds__(kSortThreads) void k_scan_add(uint32_t* __restrict__ a, int64_t n,
-                                                           const uint32_t* __restrict__ tile_sums)
-{
-    const int64_t i = (int64_t)blockIdx.x * kSortThreads + threadIdx.x;
-    if (i < n)
-        a[i] += tile_sums[i / kScanTile];
+        a[n] = run;
 }
 
 // ------------------------------------------------------------------ keys --
@@ -150,6 +126,19 @@ __global__ __launch_bounds__(kSortThreads) void k_tag_index(Keyer keyer, const i
 
 // ------------------------------------------------------ 2. chunk histograms --
 
+// Adds one per lane with a key to slot[key]: equal keys of consecutive tags come in runs
+// (chain neighbours), and each run is one LDS add.
+__device__ __forceinline__ void count_runs(uint32_t* slot, uint32_t key)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t before = __shfl_up(key, 1, kWave);
+    const uint64_t heads = __ballot(lane == 0 || before != key);
+    if (((heads >> lane) & 1ull) && key != kNoKey) {
+        const uint64_t after = lane == kWave - 1 ? 0ull : heads >> (lane + 1);
+        atomicAdd(slot + key, after ? (uint32_t)__builtin_ctzll(after) + 1u : (uint32_t)(kWave - lane));
+    }
+}
+
 __global__ __launch_bounds__(kChunkThreads) void k_sort_hist(const int32_t* __restrict__ idx,
                                                              int64_t N, int64_t S, uint32_t nkeys,
                                                              uint32_t* __restrict__ key_t,
@@ -161,7 +150,6 @@ __global__ __launch_bounds__(kChunkThreads) void k_sort_hist(const int32_t* __re
         hist[k] = 0u;
     __syncthreads();
     const int64_t t0 = c * S, t1 = min(N, t0 + S);
-    const int lane = threadIdx.x & (kWave - 1);
     bool missing = false;
     for (int64_t base = t0; base < t1; base += kChunkThreads) {
         const int64_t t = base + threadIdx.x;
@@ -174,10 +162,7 @@ __global__ __launch_bounds__(kChunkThreads) void k_sort_hist(const int32_t* __re
                 key_t[t] = kNoKey;
             }
         }
-        const bool act = key != kNoKey;
-        const uint64_t grp = wave_key_group(key, act);
-        if (act && __builtin_ctzll(grp) == lane)
-            atomicAdd(hist + key, (uint32_t)__builtin_popcountll(grp));
+        count_runs(hist, key);
     }
     if (missing)
         raise_flag(HPF_FLAG_SORT_ORDER);
@@ -189,6 +174,10 @@ __global__ __launch_bounds__(kChunkThreads) void k_sort_hist(const int32_t* __re
 
 // ------------------------------------------------ 3. column-wise scan --
 
+// The loops below read kColUnroll rows at once: one row after the other each waited out a
+// memory latency (64 rows took 17 us whatever the number of keys).
+constexpr int kColUnroll = 16;
+
 // part[cb][k] = sum of table[c][k] over the chunks c of column block cb
 __global__ __launch_bounds__(kSortThreads) void k_col_partial(const uint32_t* __restrict__ table, int64_t nchunks,
                                                               uint32_t nkeys, uint32_t* __restrict__ part)
@@ -198,9 +187,35 @@ __global__ __launch_bounds__(kSortThreads) void k_col_partial(const uint32_t* __
         return;
     const int64_t c0 = (int64_t)blockIdx.y * kColBlock, c1 = min(nchunks, c0 + kColBlock);
     uint32_t s = 0;
-    for (int64_t c = c0; c < c1; ++c)
-        s += table[c * nkeys + k];
+    for (int64_t c = c0; c < c1; c += kColUnroll) {
+        uint32_t v[kColUnroll];
+#pragma unroll
+        for (int j = 0; j < kColUnroll; ++j)
+            v[j] = c + j < c1 ? table[(c + j) * nkeys + k] : 0u;
+#pragma unroll
+        for (int j = 0; j < kColUnroll; ++j)
+            s += v[j];
+    }
     part[(int64_t)blockIdx.y * nkeys + k] = s;
+}
+
+// a[r][k] -> run + the sum of the rows before r, r in [r0, r1); returns the run after r1
+__device__ __forceinline__ uint32_t col_scan(uint32_t* __restrict__ a, int64_t r0, int64_t r1, uint32_t nkeys,
+                                             uint32_t k, uint32_t run)
+{
+    for (int64_t r = r0; r < r1; r += kColUnroll) {
+        uint32_t v[kColUnroll];
+#pragma unroll
+        for (int j = 0; j < kColUnroll; ++j)
+            v[j] = r + j < r1 ? a[(r + j) * nkeys + k] : 0u;
+#pragma unroll
+        for (int j = 0; j < kColUnroll; ++j) {
+            if (r + j < r1)
+                a[(r + j) * nkeys + k] = run;
+            run += v[j];
+        }
+    }
+    return run;
 }
 
 // part[cb][k] -> exclusive prefix over cb; tot[k] = key total
@@ -208,15 +223,8 @@ __global__ __launch_bounds__(kSortThreads) void k_col_prefix(uint32_t* __restric
                                                              uint32_t nkeys, uint32_t* __restrict__ tot)
 {
     const uint32_t k = blockIdx.x * kSortThreads + threadIdx.x;
-    if (k >= nkeys)
-        return;
-    uint32_t run = 0;
-    for (int64_t cb = 0; cb < ncb; ++cb) {
-        const uint32_t v = part[cb * nkeys + k];
-        part[cb * nkeys + k] = run;
-        run += v;
-    }
-    tot[k] = run;
+    if (k < nkeys)
+        tot[k] = col_scan(part, 0, ncb, nkeys, k, 0u);
 }
 
 // table[c][k] -> first output slot of chunk c's beads with key k
@@ -229,37 +237,143 @@ __global__ __launch_bounds__(kSortThreads) void k_col_apply(uint32_t* __restrict
     if (k >= nkeys)
         return;
     const int64_t c0 = (int64_t)blockIdx.y * kColBlock, c1 = min(nchunks, c0 + kColBlock);
-    uint32_t run = start[k] + part[(int64_t)blockIdx.y * nkeys + k];
-    for (int64_t c = c0; c < c1; ++c) {
-        const uint32_t v = table[c * nkeys + k];
-        table[c * nkeys + k] = run;
-        run += v;
+    col_scan(table, c0, c1, nkeys, k, start[k] + part[(int64_t)blockIdx.y * nkeys + k]);
+}
+
+// Step 3 for few chunks (one column block) in one workgroup and one launch: key totals,
+// their scan (start, with the total in start[nkeys]) and the slots. Below 64 chunks (65,000
+// beads) the four launches it replaces are nothing but their start-up times.
+constexpr uint32_t kSmallKeys = 4096;
+
+__global__ __launch_bounds__(kScanThreads) void k_col_small(uint32_t* __restrict__ table, int64_t nchunks,
+                                                            uint32_t nkeys, uint32_t* __restrict__ start)
+{
+    __shared__ uint32_t sh[kScanThreads / kWave + 1];
+    uint32_t base = 0;
+    for (uint32_t k0 = 0; k0 < nkeys; k0 += kScanThreads) {
+        const uint32_t k = k0 + threadIdx.x;
+        uint32_t tot = 0;
+        if (k < nkeys)
+            tot = col_scan(table, 0, nchunks, nkeys, k, 0u);
+        uint32_t total;
+        const uint32_t first = base + block_excl_scan<kScanThreads>(tot, sh, &total);
+        if (k < nkeys) {
+            start[k] = first;
+            for (int64_t c = 0; c < nchunks; ++c)
+                table[c * nkeys + k] += first;
+        }
+        base += total;
     }
+    if (threadIdx.x == 0)
+        start[nkeys] = base;
 }
 
 // ------------------------------------------------------ 4. placement --
 
-__global__ __launch_bounds__(kChunkThreads) void k_sort_place(const uint32_t* __restrict__ key_t,
-                                                              const int32_t* __restrict__ idx, int64_t N, int64_t S,
-                                                              uint32_t nkeys, const uint32_t* __restrict__ table,
-                                                              int32_t* __restrict__ perm)
+// Active lanes that hold this lane's key (0 for an inactive lane): up to `rounds` distinct keys
+// one after the other, then, if lanes are left, one ballot per key bit, whatever the number of
+// keys. The rounds pay where a wavefront holds a few keys: at 20,000 beads a key (10M beads in
+// 16-cell bricks) the placement takes 70 us with six rounds and 105 us without; at 2000
+// (8-cell bricks, a dozen keys a wavefront) 27 with and 21 without, a sweep of replicas 155 and
+// 119; solvent beads hold up to 64 keys.
+constexpr int kMatchRounds = 6;
+constexpr int64_t kMatchBeads = 6000;                 // beads per key from which they are taken
+
+__device__ __forceinline__ uint64_t wave_same_key(uint32_t key, bool active, int rounds, int nbits)
 {
-    extern __shared__ uint32_t next[];
-    const int64_t c = blockIdx.x;
-    const uint32_t* row = table + c * (int64_t)nkeys;
-    for (uint32_t k = threadIdx.x; k < nkeys; k += kChunkThreads)
-        next[k] = row[k];
-    __syncthreads();
-    const int64_t t0 = c * S, t1 = min(N, t0 + S);
+    uint64_t left = __ballot(active), mine = 0;
+    for (int j = 0; j < rounds && left; ++j) {
+        const uint32_t k = __builtin_amdgcn_readlane(key, __builtin_ctzll(left));
+        const uint64_t m = __ballot(active && key == k);
+        if (key == k)
+            mine = m;
+        left &= ~m;
+    }
+    if (left) {
+        uint64_t m = left;
+        for (int b = 0; b < nbits; ++b) {
+            const bool set = (key >> b) & 1u;
+            const uint64_t v = __ballot(set);
+            m &= set ? v : ~v;
+        }
+        if ((left >> (threadIdx.x & (kWave - 1))) & 1ull)
+            mine = m;
+    }
+    return active ? mine : 0ull;
+}
+
+// A workgroup of `rows` wavefronts places one chunk; wavefront w owns the w-th part of the
+// chunk and row w of the LDS slots. The rows are first counted, then turned into each
+// wavefront's first slots (chunk slot + the earlier wavefronts' counts); from there on a
+// wavefront needs no barrier. With many keys only the chunk's own key range is cleared and
+// summed (the replicas of a batch follow each other in tag order, so a chunk sees few).
+// Bound by its scattered 4-byte stores; the inverse is therefore left to a pass in storage
+// order, where it is nearly in sequence (written here it took 35 us more at 10M beads).
+// Before, the wavefronts of a workgroup took turns on one row, a barrier per turn, and
+// grouped their lanes one distinct key at a time: 3M beads, mostly solvent, took 169 us.
+__global__ __launch_bounds__(4 * kWave) void k_sort_place(const uint32_t* __restrict__ key_t,
+                                                          const int32_t* __restrict__ idx, int64_t N, int64_t S,
+                                                          uint32_t nkeys, int rounds, int nbits,
+                                                          const uint32_t* __restrict__ table,
+                                                          int32_t* __restrict__ perm)
+{
+    extern __shared__ uint32_t slots[];
+    __shared__ uint32_t range[2];
+    const int rows = (int)(blockDim.x / kWave);
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    for (int64_t g0 = t0; g0 < t1; g0 += kMinChunk) {
-        uint32_t key[kPlaceRegs];
-        int32_t src[kPlaceRegs];
-        // 256-tag blocks of this round that hold tags (fewer than kPlaceRegs for a short chunk)
-        const int nblk = (int)min((int64_t)kPlaceRegs, (t1 - g0 + kChunkThreads - 1) / kChunkThreads);
+    const int64_t c = blockIdx.x;
+    const int64_t part = S / rows;
+    const int64_t t0 = min(N, c * S + wave * part), t1 = min(N, t0 + part);
+    uint32_t ka = 0, kb = nkeys;
+    if (nkeys > kRangeKeys) {
+        if (threadIdx.x == 0) {
+            range[0] = nkeys;
+            range[1] = 0u;
+        }
+        __syncthreads();
+        int lo = 0x7fffffff, hi = -1;
+        for (int64_t t = t0 + lane; t < t1; t += kWave) {
+            const uint32_t key = key_t[t];
+            if (key != kNoKey) {
+                lo = min(lo, (int)key);
+                hi = max(hi, (int)key);
+            }
+        }
+        lo = wave_min(lo);
+        hi = wave_max(hi);
+        if (lane == 0 && hi >= 0) {
+            atomicMin(&range[0], (uint32_t)lo);
+            atomicMax(&range[1], (uint32_t)hi + 1u);
+        }
+        __syncthreads();
+        ka = range[0];                                // ka >= kb: no tag of the chunk has a key
+        kb = range[1];
+    }
+    uint32_t* mine = slots + wave * nkeys;
+    for (uint32_t k = ka + threadIdx.x; k < kb; k += blockDim.x)
+        for (int w = 0; w < rows; ++w)
+            slots[w * nkeys + k] = 0u;
+    __syncthreads();
+    for (int64_t t = t0 + lane; t < t0 + part && t - lane < t1; t += kWave)
+        count_runs(mine, t < t1 ? key_t[t] : kNoKey);
+    __syncthreads();
+    const uint32_t* first = table + c * (int64_t)nkeys;
+    for (uint32_t k = ka + threadIdx.x; k < kb; k += blockDim.x) {
+        uint32_t run = first[k];
+        for (int w = 0; w < rows; ++w) {
+            const uint32_t v = slots[w * nkeys + k];
+            slots[w * nkeys + k] = run;
+            run += v;
+        }
+    }
+    __syncthreads();
+    volatile uint32_t* next = mine;            // lanes of one wavefront follow each other in order
+    for (int64_t g0 = t0; g0 < t1; g0 += kPlaceRows * kWave) {
+        uint32_t key[kPlaceRows];
+        int32_t src[kPlaceRows];
 #pragma unroll
-        for (int b = 0; b < kPlaceRegs; ++b) {
-            const int64_t t = g0 + (int64_t)b * kChunkThreads + threadIdx.x;
+        for (int b = 0; b < kPlaceRows; ++b) {
+            const int64_t t = g0 + b * kWave + lane;
             key[b] = kNoKey;
             src[b] = 0;
             if (t < t1) {
@@ -268,24 +382,16 @@ __global__ __launch_bounds__(kChunkThreads) void k_sort_place(const uint32_t* __
             }
         }
 #pragma unroll
-        for (int b = 0; b < kPlaceRegs; ++b) {
-            if (b >= nblk)                           // uniform: the block holds no tags
-                continue;
-            for (int w = 0; w < kChunkThreads / kWave; ++w) {
-                if (wave == w) {
-                    const bool act = key[b] != kNoKey;
-                    const uint64_t grp = wave_key_group(key[b], act);
-                    const int leader = act ? __builtin_ctzll(grp) : lane;
-                    uint32_t base = 0;
-                    if (act && leader == lane) {
-                        base = next[key[b]];
-                        next[key[b]] = base + (uint32_t)__builtin_popcountll(grp);
-                    }
-                    base = __shfl(base, leader, kWave);
-                    if (act)
-                        perm[base + (uint32_t)__builtin_popcountll(grp & ((1ull << lane) - 1))] = src[b];
-                }
-                __syncthreads();
+        for (int b = 0; b < kPlaceRows; ++b) {
+            if (g0 + b * kWave >= t1)                // uniform: the row holds no tags
+                break;
+            const bool act = key[b] != kNoKey;
+            const uint64_t grp = wave_same_key(key[b], act, rounds, nbits);
+            if (act) {
+                const uint32_t base = next[key[b]];
+                if (__builtin_ctzll(grp) == lane)
+                    next[key[b]] = base + (uint32_t)__builtin_popcountll(grp);
+                perm[base + (uint32_t)__builtin_popcountll(grp & ((1ull << lane) - 1))] = src[b];
             }
         }
     }
@@ -300,16 +406,39 @@ __global__ __launch_bounds__(kSortThreads) void k_iota(int32_t* __restrict__ p, 
 
 // ------------------------------------------------ gather and bond table --
 
-__global__ __launch_bounds__(kSortThreads) void k_sort_permute(const int32_t* __restrict__ perm, int64_t N,
+// New storage index of partner j (-1: none, or outside [-1, N), which is flagged). A bead
+// that a broken permutation left out has no inverse entry; its partners get -1.
+__device__ __forceinline__ int32_t renumbered(int32_t j, const int32_t* __restrict__ inv, int64_t N, bool& bad)
+{
+    if (j >= 0 && j < N) {
+        const int32_t nj = inv[j];
+        return nj >= 0 && nj < N ? nj : -1;
+    }
+    bad |= j != -1;
+    return -1;
+}
+
+__global__ __launch_bounds__(kSortThreads) void k_sort_inverse(const int32_t* __restrict__ perm, int64_t N,
+                                                               int32_t* __restrict__ inv)
+{
+    const int64_t p = xcd_block(blockIdx.x, gridDim.x) * kSortThreads + threadIdx.x;
+    if (p < N)
+        inv[perm[p]] = (int32_t)p;
+}
+
+// Bead rows and bond rows in the new order, in one pass (HBM-bound).
+__global__ __launch_bounds__(kSortThreads) void k_sort_permute(const int32_t* __restrict__ perm,
+                                                               const int32_t* __restrict__ inv, int64_t N,
                                                                const float3* __restrict__ R_in,
                                                                const float3* __restrict__ V_in,
                                                                const uint8_t* __restrict__ T_in,
                                                                const int32_t* __restrict__ tag_in,
+                                                               const int32_t* __restrict__ bonds_in, int D,
                                                                float3* __restrict__ R_out,
                                                                float3* __restrict__ V_out,
                                                                uint8_t* __restrict__ T_out,
                                                                int32_t* __restrict__ tag_out,
-                                                               int32_t* __restrict__ inv)
+                                                               int32_t* __restrict__ bonds_out)
 {
     const int64_t p = xcd_block(blockIdx.x, gridDim.x) * kSortThreads + threadIdx.x;
     if (p >= N)
@@ -321,28 +450,9 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_permute(const int32_t* __
     T_out[p] = T_in[o];
     if (tag_in)
         tag_out[p] = tag_in[o];
-    inv[o] = (int32_t)p;
-}
-
-__global__ __launch_bounds__(kSortThreads) void k_sort_bonds(const int32_t* __restrict__ perm,
-                                                             const int32_t* __restrict__ inv, int64_t N,
-                                                             const int32_t* __restrict__ bonds_in, int D,
-                                                             int32_t* __restrict__ bonds_out)
-{
-    const int64_t p = xcd_block(blockIdx.x, gridDim.x) * kSortThreads + threadIdx.x;
-    if (p >= N)
-        return;
-    const int32_t o = perm[p];
     bool bad = false;
-    for (int b = 0; b < D; ++b) {
-        const int32_t j = bonds_in[(int64_t)b * N + o];
-        int32_t nj = -1;
-        if (j >= 0 && j < N)
-            nj = inv[j];
-        else if (j >= N || j < -1)
-            bad = true;
-        bonds_out[(int64_t)b * N + p] = nj;
-    }
+    for (int b = 0; b < D; ++b)
+        bonds_out[(int64_t)b * N + p] = renumbered(bonds_in[(int64_t)b * N + o], inv, N, bad);
     if (bad)
         raise_flag(HPF_FLAG_BAD_BOND);
 }
@@ -361,15 +471,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_angles(const int32_t* __r
     bool bad = false;
     for (int r = 0; r < 3 * A; ++r) {
         const int32_t j = ang_in[(int64_t)r * N + o];
-        int32_t nj = j;
-        if (r % 3 != 2) {
-            nj = -1;
-            if (j >= 0 && j < N)
-                nj = inv[j];
-            else if (j >= N || j < -1)
-                bad = true;
-        }
-        ang_out[(int64_t)r * N + p] = nj;
+        ang_out[(int64_t)r * N + p] = r % 3 == 2 ? j : renumbered(j, inv, N, bad);
     }
     if (bad)
         raise_flag(HPF_FLAG_BAD_BOND);
@@ -542,7 +644,8 @@ __global__ __launch_bounds__(kPlaceThreads) void k_resort_place(const int32_t* _
                                                                 const uint32_t* __restrict__ moff,
                                                                 const uint32_t* __restrict__ start,
                                                                 unsigned long long* __restrict__ movers,
-                                                                int32_t* __restrict__ perm)
+                                                                int32_t* __restrict__ perm,
+                                                                int32_t* __restrict__ inv)
 {
     __shared__ unsigned long long smv[kMoverCap];
     const uint32_t k = blockIdx.x;
@@ -575,6 +678,7 @@ __global__ __launch_bounds__(kPlaceThreads) void k_resort_place(const int32_t* _
                 hi = mid;
         }
         perm[base + q + lo] = (int32_t)(uint32_t)e;
+        inv[(uint32_t)e] = (int32_t)(base + q + lo);
     }
     // stayers: rank among stayers + movers with a smaller tag
     for (int64_t q = threadIdx.x; q < ns; q += kPlaceThreads) {
@@ -589,6 +693,7 @@ __global__ __launch_bounds__(kPlaceThreads) void k_resort_place(const int32_t* _
                 hi = mid;
         }
         perm[base + q + lo] = i;
+        inv[i] = (int32_t)(base + q + lo);
     }
 }
 
@@ -600,9 +705,10 @@ static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 struct SortPlan {
     int64_t N = 0;
     uint32_t nkeys = 0;
-    int64_t S = 0, nchunks = 0, ncb = 0, nscan = 0, ntiles = 0;
-    size_t off_key = 0, off_perm = 0, off_idx = 0, off_table = 0, off_part = 0, off_tiles = 0, off_start = 0;
-    // re-sort from a previous order: compacted stayers, movers, per-key counts and offsets
+    int64_t S = 0, nchunks = 0, ncb = 0;
+    size_t off_key = 0, off_perm = 0, off_inv = 0, off_table = 0, off_part = 0, off_start = 0;
+    // re-sort from a previous order: compacted stayers (the full sort keeps its tag index
+    // there), movers, per-key counts and offsets
     size_t off_stay = 0, off_movers = 0, off_cstay = 0, off_cmove = 0, off_fill = 0, off_moff = 0;
     size_t bytes = 0;
 };
@@ -624,19 +730,14 @@ bool sort_plan(int64_t N, int64_t nkeys, SortPlan* p)
     p->S = S;
     p->nchunks = std::max<int64_t>(1, (N + S - 1) / S);
     p->ncb = (p->nchunks + kColBlock - 1) / kColBlock;
-    p->nscan = nkeys + 1;
-    p->ntiles = (p->nscan + kScanTile - 1) / kScanTile;
-    if (p->ntiles > kMaxScanTiles)
-        return false;
     const size_t N1 = (size_t)(N > 0 ? N : 1);
     size_t o = 0;
     p->off_key = o; o += align_up(sizeof(uint32_t) * N1);
     p->off_perm = o; o += align_up(sizeof(int32_t) * N1);
-    p->off_idx = o; o += align_up(sizeof(int32_t) * N1);          // tag index, then inverse permutation
+    p->off_inv = o; o += align_up(sizeof(int32_t) * N1);
     p->off_table = o; o += align_up(sizeof(uint32_t) * (size_t)p->nchunks * (size_t)nkeys);
     p->off_part = o; o += align_up(sizeof(uint32_t) * (size_t)p->ncb * (size_t)nkeys);
-    p->off_tiles = o; o += align_up(sizeof(uint32_t) * (size_t)(p->ntiles + 1));
-    p->off_start = o; o += align_up(sizeof(uint32_t) * (size_t)(p->nscan + 1));
+    p->off_start = o; o += align_up(sizeof(uint32_t) * (size_t)(nkeys + 2));
     p->off_stay = o; o += align_up(sizeof(int32_t) * N1);
     p->off_movers = o; o += align_up(sizeof(uint64_t) * N1);
     p->off_cstay = o; o += align_up(sizeof(uint32_t) * (size_t)nkeys);
@@ -672,6 +773,29 @@ bool sort_layout(int64_t N, const int32_t M[3], int B, SortK* sk_out, SortPlan* 
 
 static unsigned grid_for(int64_t n) { return (unsigned)((n + kSortThreads - 1) / kSortThreads); }
 
+static void launch_permute(int64_t N, const int32_t* perm, const int32_t* inv, const float* R_in, const float* V_in,
+                           const uint8_t* T_in, const int32_t* tag_in, const int32_t* bonds_in, int D, float* R_out,
+                           float* V_out, uint8_t* T_out, int32_t* tag_out, int32_t* bonds_out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_sort_permute, dim3(grid_for(N)), dim3(kSortThreads), 0, s, perm, inv, N,
+                       reinterpret_cast<const float3*>(R_in), reinterpret_cast<const float3*>(V_in), T_in, tag_in,
+                       bonds_in, bonds_in ? D : 0, reinterpret_cast<float3*>(R_out), reinterpret_cast<float3*>(V_out),
+                       T_out, tag_out, bonds_out);
+}
+
+// Wavefronts of a placement workgroup: as many slot rows of nkeys u32 as give the most
+// wavefronts per CU in its 160 KiB of LDS (4 up to 10,240 keys, then 2 or 1; a row of the
+// largest key count is 144 KiB).
+static int place_rows(uint32_t nkeys)
+{
+    const size_t lds = 160 * 1024, row = sizeof(uint32_t) * (size_t)nkeys;
+    int best = 1;
+    for (int rows = 2; rows <= 4; rows *= 2)
+        if (rows * (lds / (row * rows)) >= best * (lds / (row * best)))
+            best = rows;
+    return best;
+}
+
 // The four steps and the gather for any key function; `start` receives the
 // key starts (nkeys + 1 entries, the last = number of placed beads).
 template <class Keyer>
@@ -682,49 +806,47 @@ hpf_status_t run_sort(const SortPlan& pl, Keyer keyer, int64_t N, const float* R
 {
     uint32_t* key_t = reinterpret_cast<uint32_t*>(work + pl.off_key);
     int32_t* perm = reinterpret_cast<int32_t*>(work + pl.off_perm);
-    int32_t* idx = reinterpret_cast<int32_t*>(work + pl.off_idx);
+    int32_t* idx = reinterpret_cast<int32_t*>(work + pl.off_stay);
+    int32_t* inv = reinterpret_cast<int32_t*>(work + pl.off_inv);
     uint32_t* table = reinterpret_cast<uint32_t*>(work + pl.off_table);
     uint32_t* part = reinterpret_cast<uint32_t*>(work + pl.off_part);
-    uint32_t* tiles = reinterpret_cast<uint32_t*>(work + pl.off_tiles);
     const uint32_t nk = pl.nkeys;
+    if (N == 0) {
+        hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)std::min<int64_t>(grid_for(nk + 1), 4096)), dim3(kSortThreads),
+                           0, s, start, (int64_t)nk + 1, 0u);
+        return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
+    }
     const size_t smem = sizeof(uint32_t) * nk;
-    if (smem > 65536 &&
-        (hipFuncSetAttribute(reinterpret_cast<const void*>(k_sort_hist),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess ||
+    const int rows = place_rows(nk);
+    const size_t smem_place = smem * rows;
+    if ((smem > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(k_sort_hist),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) ||
+        (smem_place > 65536 &&
          hipFuncSetAttribute(reinterpret_cast<const void*>(k_sort_place), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)smem) != hipSuccess))
+                             (int)smem_place) != hipSuccess))
         return HPF_EINVAL;
-    const unsigned gfill = (unsigned)std::min<int64_t>(grid_for(pl.nscan), 4096);
-    hipLaunchKernelGGL(k_fill_u32, dim3(gfill), dim3(kSortThreads), 0, s, start, pl.nscan, 0u);
-    if (N > 0) {
-        hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)std::min<int64_t>(grid_for(N), 4096)), dim3(kSortThreads), 0, s,
-                           reinterpret_cast<uint32_t*>(idx), N, 0xffffffffu);
-        hipLaunchKernelGGL(k_iota, dim3(grid_for(N)), dim3(kSortThreads), 0, s, perm, N);
-        hipLaunchKernelGGL(k_tag_index<Keyer>, dim3(grid_for(N)), dim3(kSortThreads), 0, s, keyer, tag_in, N, idx,
-                           key_t);
-        hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)pl.nchunks), dim3(kChunkThreads), smem, s, idx,
-                           N, pl.S, nk, key_t, table);
-        const dim3 gcol((nk + kSortThreads - 1) / kSortThreads, (unsigned)pl.ncb);
+    hipLaunchKernelGGL(k_sort_init, dim3((unsigned)std::min<int64_t>(grid_for(N), 8192)), dim3(kSortThreads), 0, s,
+                       idx, perm, N);
+    hipLaunchKernelGGL(k_tag_index<Keyer>, dim3(grid_for(N)), dim3(kSortThreads), 0, s, keyer, tag_in, N, idx, key_t);
+    hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)pl.nchunks), dim3(kChunkThreads), smem, s, idx, N, pl.S, nk, key_t,
+                       table);
+    if (pl.ncb == 1 && nk <= kSmallKeys) {
+        hipLaunchKernelGGL(k_col_small, dim3(1), dim3(kScanThreads), 0, s, table, pl.nchunks, nk, start);
+    } else {
+        const unsigned gk = (nk + kSortThreads - 1) / kSortThreads;
+        const dim3 gcol(gk, (unsigned)pl.ncb);
         hipLaunchKernelGGL(k_col_partial, gcol, dim3(kSortThreads), 0, s, table, pl.nchunks, nk, part);
-        hipLaunchKernelGGL(k_col_prefix, dim3((nk + kSortThreads - 1) / kSortThreads), dim3(kSortThreads), 0, s,
-                           part, pl.ncb, nk, start);
-    }
-    hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)pl.ntiles), dim3(kSortThreads), 0, s, start, pl.nscan, tiles);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanTopThreads), 0, s, tiles, (int)pl.ntiles);
-    hipLaunchKernelGGL(k_scan_add, dim3(grid_for(pl.nscan)), dim3(kSortThreads), 0, s, start, pl.nscan, tiles);
-    if (N > 0) {
-        const dim3 gcol((nk + kSortThreads - 1) / kSortThreads, (unsigned)pl.ncb);
+        hipLaunchKernelGGL(k_col_prefix, dim3(gk), dim3(kSortThreads), 0, s, part, pl.ncb, nk, start);
+        hipLaunchKernelGGL(k_scan_keys, dim3(1), dim3(kScanThreads), 0, s, start, nk);
         hipLaunchKernelGGL(k_col_apply, gcol, dim3(kSortThreads), 0, s, table, part, start, pl.nchunks, nk);
-        hipLaunchKernelGGL(k_sort_place, dim3((unsigned)pl.nchunks), dim3(kChunkThreads), smem, s, key_t, idx, N,
-                           pl.S, nk, table, perm);
-        hipLaunchKernelGGL(k_sort_permute, dim3(grid_for(N)), dim3(kSortThreads), 0, s, perm, N,
-                           reinterpret_cast<const float3*>(R_in), reinterpret_cast<const float3*>(V_in), T_in,
-                           tag_in, reinterpret_cast<float3*>(R_out), reinterpret_cast<float3*>(V_out), T_out,
-                           tag_out, idx);
-        if (D > 0 && bonds_in)
-            hipLaunchKernelGGL(k_sort_bonds, dim3(grid_for(N)), dim3(kSortThreads), 0, s, perm, idx, N, bonds_in,
-                               D, bonds_out);
     }
+    int nbits = 1;
+    while ((1u << nbits) < nk)
+        ++nbits;
+    hipLaunchKernelGGL(k_sort_place, dim3((unsigned)pl.nchunks), dim3(kWave * rows), smem_place, s, key_t, idx, N,
+                       pl.S, nk, N / nk >= kMatchBeads ? kMatchRounds : 0, nbits, table, perm);
+    hipLaunchKernelGGL(k_sort_inverse, dim3(grid_for(N)), dim3(kSortThreads), 0, s, perm, N, inv);
+    launch_permute(N, perm, inv, R_in, V_in, T_in, tag_in, bonds_in, D, R_out, V_out, T_out, tag_out, bonds_out, s);
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }
 
@@ -749,7 +871,7 @@ hpf_status_t launch_resort(const SortK& sk, const SortPlan& pl, int64_t N, const
     const uint32_t nk = pl.nkeys;
     auto* keyp = reinterpret_cast<uint32_t*>(work + pl.off_key);
     auto* perm = reinterpret_cast<int32_t*>(work + pl.off_perm);
-    auto* inv = reinterpret_cast<int32_t*>(work + pl.off_idx);
+    auto* inv = reinterpret_cast<int32_t*>(work + pl.off_inv);
     auto* stay = reinterpret_cast<int32_t*>(work + pl.off_stay);
     auto* movers = reinterpret_cast<unsigned long long*>(work + pl.off_movers);
     auto* cstay = reinterpret_cast<uint32_t*>(work + pl.off_cstay);
@@ -771,14 +893,9 @@ hpf_status_t launch_resort(const SortK& sk, const SortPlan& pl, int64_t N, const
         hipLaunchKernelGGL(k_resort_movers, dim3(nk), dim3(kResortThreads), 0, s, tag_in, cs_old, N, keyp, moff, fill,
                            movers);
         hipLaunchKernelGGL(k_resort_place, dim3(nk), dim3(kPlaceThreads), 0, s, tag_in, cs_old, N, stay, cstay, cmove,
-                           moff, cs_new, movers, perm);
-        hipLaunchKernelGGL(k_sort_permute, dim3(grid_for(N)), dim3(kSortThreads), 0, s, perm, N,
-                           reinterpret_cast<const float3*>(R_in), reinterpret_cast<const float3*>(V_in), T_in,
-                           tag_in, reinterpret_cast<float3*>(R_out), reinterpret_cast<float3*>(V_out), T_out,
-                           tag_out, inv);
-        if (D > 0 && bonds_in)
-            hipLaunchKernelGGL(k_sort_bonds, dim3(grid_for(N)), dim3(kSortThreads), 0, s, perm, inv, N, bonds_in,
-                               D, bonds_out);
+                           moff, cs_new, movers, perm, inv);
+        launch_permute(N, perm, inv, R_in, V_in, T_in, tag_in, bonds_in, D, R_out, V_out, T_out, tag_out, bonds_out,
+                       s);
     }
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }
@@ -789,7 +906,7 @@ hpf_status_t launch_sort_angles(const SortPlan& pl, int64_t N, const int32_t* an
     if (N == 0 || A == 0)
         return HPF_OK;
     const int32_t* perm = reinterpret_cast<const int32_t*>(work + pl.off_perm);
-    const int32_t* inv = reinterpret_cast<const int32_t*>(work + pl.off_idx);
+    const int32_t* inv = reinterpret_cast<const int32_t*>(work + pl.off_inv);
     hipLaunchKernelGGL(k_sort_angles, dim3(grid_for(N)), dim3(kSortThreads), 0, s, perm, inv, N, ang_in, A, ang_out);
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }

@@ -351,6 +351,39 @@ hpf_status_t verlet_step(float* R, float* Vel, const float* F, const float* inv_
                          int64_t N, float dt, const float* box, int32_t half,
                          double* kin_part, void* stream);
 
+/* ---------------------------------------------------------------------------
+ * hpf_force_kick -- all forces at the current positions and the second half kick in
+ * one pass, bit for bit the results of this call sequence:
+ *     hpf_force_gather(R, ..., G = field, F)            when staggered = 0, or
+ *     hpf_force_gather_staggered(R, ..., V = field, F)  when staggered = 1;
+ *     bond_forces(R, ..., F, e_part);
+ *     angle_forces(R, ..., F, ea_part)                  when A > 0;
+ *     verlet_step(half = 2, kin_part)
+ * Arguments as in those calls: field is the gradient float[K][M^3][3] or the potential
+ * float[K][M^3]; ntypes, angle_k, theta0 and form are read only when A > 0; F is
+ * OVERWRITTEN with the total force; the three partial-sum buffers are nullable.
+ * Sets HPF_FLAG_BAD_BEAD / HPF_FLAG_BAD_BOND / HPF_FLAG_NONFINITE like the separate calls.
+ * ------------------------------------------------------------------------- */
+hpf_status_t hpf_force_kick(const float* R, const uint8_t* T, int64_t N, const hpf_mesh_t* mesh, int32_t K,
+                            const float* field, int32_t staggered, const int32_t* bonds, int32_t D,
+                            float k, float r0, const int32_t* angles, int32_t A, int32_t ntypes,
+                            const float* angle_k, const float* theta0, const int32_t* form,
+                            const float* box, float* F, float* Vel, const float* inv_mass, float dt,
+                            double* e_part, double* ea_part, double* kin_part, void* stream);
+
+/* ---------------------------------------------------------------------------
+ * hpf_verlet_scatter -- verlet_step(half = 1) of cell-sorted beads and the deposit of the
+ * new positions in one pass: R and Vel are updated in place, bit for bit as by
+ * verlet_step, and `work` and `counts` receive the deposit exactly as
+ * hpf_advance_scatter leaves it (same layout and limits: counts must hold zeros on
+ * entry, and hpf_density_finish_cells or hpf_field_potential_cells completes it).
+ * cell_start, B, halo, work as in hpf_advance_scatter; inv_mass nullable.
+ * ------------------------------------------------------------------------- */
+hpf_status_t hpf_verlet_scatter(float* R, float* Vel, const float* F, const uint8_t* T, const float* inv_mass,
+                                int64_t N, float dt, const float* box, const hpf_mesh_t* mesh, int32_t K,
+                                const uint32_t* cell_start, int32_t B, int32_t halo, uint64_t* counts,
+                                void* work, size_t work_bytes, void* stream);
+
 /* hpf_andersen -- the Andersen collisions of time level *thermostat->step on
  * every bead (see hpf_thermostat_t), to be applied after verlet_step(half = 2).
  * Vel float[N][3] device, updated; inv_mass nullable float[N] (NULL = unit

@@ -343,6 +343,23 @@ hpf_status_t bond_forces(const float* R, int64_t N, const int32_t* bonds, int32_
     return launch_bond_forces(R, N, bonds, D, k, r0, b, F, e_part, as_stream(stream));
 }
 
+// Kernel form of the angle parameters; false for invalid ones.
+static bool angle_k(int32_t ntypes, const float* k, const float* theta0, const int32_t* form, AngleK* out)
+{
+    AngleK ak{};
+    ak.ntypes = ntypes;
+    for (int t = 0; t < ntypes; ++t) {
+        if (!std::isfinite(k[t]) || !std::isfinite(theta0[t]) || (form[t] != 0 && form[t] != 1))
+            return false;
+        ak.k[t] = k[t];
+        ak.theta0[t] = theta0[t];
+        ak.cos0[t] = (float)std::cos((double)theta0[t]);
+        ak.form[t] = form[t];
+    }
+    *out = ak;
+    return true;
+}
+
 hpf_status_t angle_forces(const float* R, int64_t N, const int32_t* angles, int32_t A, int32_t ntypes,
                           const float* k, const float* theta0, const int32_t* form, const float* box, float* F,
                           double* e_part, void* stream)
@@ -352,16 +369,9 @@ hpf_status_t angle_forces(const float* R, int64_t N, const int32_t* angles, int3
         return HPF_EINVAL;
     if (N > 0 && (!R || !F || (A > 0 && !angles)))
         return HPF_EINVAL;
-    AngleK ak{};
-    ak.ntypes = ntypes;
-    for (int t = 0; t < ntypes; ++t) {
-        if (!std::isfinite(k[t]) || !std::isfinite(theta0[t]) || (form[t] != 0 && form[t] != 1))
-            return HPF_EINVAL;
-        ak.k[t] = k[t];
-        ak.theta0[t] = theta0[t];
-        ak.cos0[t] = (float)std::cos((double)theta0[t]);
-        ak.form[t] = form[t];
-    }
+    AngleK ak;
+    if (!angle_k(ntypes, k, theta0, form, &ak))
+        return HPF_EINVAL;
     BoxK b;
     for (int d = 0; d < 3; ++d) {
         b.L[d] = box[d];
@@ -445,6 +455,55 @@ hpf_status_t hpf_advance_scatter(const float* R, float* R_next, float* Vel, cons
                                   reinterpret_cast<unsigned long long*>(w + sb),
                                   reinterpret_cast<unsigned long long*>(counts), F_out, e_part, kin_part, th,
                                   as_stream(stream));
+}
+
+hpf_status_t hpf_force_kick(const float* R, const uint8_t* T, int64_t N, const hpf_mesh_t* mesh, int32_t K,
+                            const float* field, int32_t staggered, const int32_t* bonds, int32_t D, float k, float r0,
+                            const int32_t* angles, int32_t A, int32_t ntypes, const float* angle_k_, const float* theta0,
+                            const int32_t* form, const float* box, float* F, float* Vel, const float* inv_mass,
+                            float dt, double* e_part, double* ea_part, double* kin_part, void* stream)
+{
+    if (!advance_args_ok(N, mesh, K, D, k, r0, box, dt) || A < 0 || A > HPF_MAX_ANGLES || staggered < 0 ||
+        staggered > 1)
+        return HPF_EINVAL;
+    AngleK ak{};
+    if (A > 0 && (ntypes < 1 || ntypes > HPF_MAX_ANGLE_TYPES || !angle_k_ || !theta0 || !form ||
+                  !angle_k(ntypes, angle_k_, theta0, form, &ak)))
+        return HPF_EINVAL;
+    if (N > 0 && (!R || !T || !field || !F || !Vel || (D > 0 && !bonds) || (A > 0 && !angles)))
+        return HPF_EINVAL;
+    BoxK b;
+    for (int d = 0; d < 3; ++d) {
+        b.L[d] = box[d];
+        b.halfL[d] = 0.5f * box[d];
+    }
+    return launch_force_kick(R, T, N, mesh_k(mesh), K, field, staggered != 0, bonds, D, k, r0, angles, A, ak, b, F,
+                             Vel, inv_mass, dt, e_part, ea_part, kin_part, as_stream(stream));
+}
+
+hpf_status_t hpf_verlet_scatter(float* R, float* Vel, const float* F, const uint8_t* T, const float* inv_mass,
+                                int64_t N, float dt, const float* box, const hpf_mesh_t* mesh, int32_t K,
+                                const uint32_t* cell_start, int32_t B, int32_t halo, uint64_t* counts, void* work,
+                                size_t work_bytes, void* stream)
+{
+    TileK tk;
+    size_t sb = 0, tb = 0;
+    if (!box_ok(box) || !(dt > 0.0f) || !std::isfinite(dt) || !counts || !cell_start ||
+        !scatter_cells_setup(N, mesh, K, B, halo, &tk, &sb, &tb))
+        return HPF_EINVAL;
+    if (N > 0 && (!R || !Vel || !F || !T))
+        return HPF_EINVAL;
+    if (!work || work_bytes < tb)
+        return HPF_ESPACE;
+    BoxK b;
+    for (int d = 0; d < 3; ++d) {
+        b.L[d] = box[d];
+        b.halfL[d] = 0.5f * box[d];
+    }
+    char* w = static_cast<char*>(work);
+    return launch_verlet_scatter(R, Vel, F, T, inv_mass, N, dt, b, tk, K, cell_start,
+                                 reinterpret_cast<unsigned long long*>(w + sb),
+                                 reinterpret_cast<unsigned long long*>(counts), as_stream(stream));
 }
 
 hpf_status_t hpf_andersen(float* Vel, const float* inv_mass, int64_t N, const hpf_thermostat_t* thermostat,

@@ -210,6 +210,32 @@ __device__ __forceinline__ bool field_force_staggered(const float3& r, int t, co
     return true;
 }
 
+// Adds one harmonic bond of bead i (position xi, partner at xj) to f, and its energy
+// k (r - r0)^2 (FP32) to ei.
+template <bool kR0Zero>
+__device__ __forceinline__ void bond_add(const float3& xi, const float3& xj, float k, float r0, const BoxK& box,
+                                         float3& f, float& ei)
+{
+    const float two_k = 2.0f * k;
+    const float dx = min_image(xj.x, xi.x, box.L[0], box.halfL[0]);
+    const float dy = min_image(xj.y, xi.y, box.L[1], box.halfL[1]);
+    const float dz = min_image(xj.z, xi.z, box.L[2], box.halfL[2]);
+    const float r2 = dx * dx + dy * dy + dz * dz;
+    float coef;
+    if (kR0Zero) {
+        coef = two_k;
+        ei += k * r2;
+    } else {
+        const float r = sqrtf(r2);
+        const float dr = r - r0;
+        coef = r > 0.0f ? two_k * dr / r : 0.0f;
+        ei += k * dr * dr;
+    }
+    f.x += coef * dx;
+    f.y += coef * dy;
+    f.z += coef * dz;
+}
+
 // Sum of the harmonic bond forces on bead i over its table row, and its
 // bond energy k (r - r0)^2 summed over its bonds (FP32).
 template <bool kR0Zero>
@@ -217,7 +243,6 @@ __device__ __forceinline__ float3 bond_sum(int64_t i, const float3& xi, const fl
                                            int64_t N, const int32_t* __restrict__ bonds, int D, float k,
                                            float r0, const BoxK& box, float& ei, bool& bad)
 {
-    const float two_k = 2.0f * k;
     float3 f = make_float3(0.0f, 0.0f, 0.0f);
     ei = 0.0f;
     for (int b = 0; b < D; ++b) {
@@ -228,24 +253,7 @@ __device__ __forceinline__ float3 bond_sum(int64_t i, const float3& xi, const fl
             bad = true;
             continue;
         }
-        const float3 xj = R[j];
-        const float dx = min_image(xj.x, xi.x, box.L[0], box.halfL[0]);
-        const float dy = min_image(xj.y, xi.y, box.L[1], box.halfL[1]);
-        const float dz = min_image(xj.z, xi.z, box.L[2], box.halfL[2]);
-        const float r2 = dx * dx + dy * dy + dz * dz;
-        float coef;
-        if (kR0Zero) {
-            coef = two_k;
-            ei += k * r2;
-        } else {
-            const float r = sqrtf(r2);
-            const float dr = r - r0;
-            coef = r > 0.0f ? two_k * dr / r : 0.0f;
-            ei += k * dr * dr;
-        }
-        f.x += coef * dx;
-        f.y += coef * dy;
-        f.z += coef * dz;
+        bond_add<kR0Zero>(xi, R[j], k, r0, box, f, ei);
     }
     return f;
 }
@@ -348,70 +356,91 @@ struct AngleK {
     int form[8];
 };
 
-// Force on bead i from its angle-table rows (each angle is evaluated by each of
-// its three members, as the bonds are from both ends) and its share of their
-// energy (one third each). theta is the angle at the middle bead between the
+// One angle-table entry of bead i: the other two members p and q, and the code.
+struct AngleRow {
+    int32_t p, q, code;
+};
+
+__device__ __forceinline__ AngleRow angle_row(const int32_t* __restrict__ angles, int r, int64_t N, int64_t i)
+{
+    AngleRow a{-1, 0, 0};
+    a.p = angles[(3 * (int64_t)r + 0) * N + i];
+    if (a.p >= 0) {                      // beads in no angle read one row of three
+        a.q = angles[(3 * (int64_t)r + 1) * N + i];
+        a.code = angles[(3 * (int64_t)r + 2) * N + i];
+    }
+    return a;
+}
+
+__device__ __forceinline__ bool angle_valid(const AngleRow& a, int64_t N, const AngleK& ak)
+{
+    return a.p >= 0 && a.p < N && a.q >= 0 && a.q < N && (a.code >> 1) < ak.ntypes;
+}
+
+// Adds the force of one valid entry on bead i (position xi) to f and its share of the energy
+// (one third: each angle is evaluated by each of its three members, as the bonds are from
+// both ends) to ei. theta is the angle at the middle bead between the
 // minimum-image arms a = x_end1 - x_mid and b = x_end2 - x_mid;
 // theta = atan2(|a x b|, a.b); dcos/dx_end1 = (b^ - c a^) / |a|,
 // dcos/dx_end2 = (a^ - c b^) / |b|, dcos/dx_mid = -(their sum). For the harmonic
 // form dU/dcos = -2k (theta - theta0) / sin(theta), sin(theta) floored at 1e-3.
-__device__ __forceinline__ float3 angle_sum(int64_t i, const float3& xi, const float3* __restrict__ R, int64_t N,
-                                            const int32_t* __restrict__ angles, int A, const AngleK& ak,
-                                            const BoxK& box, double& ei, bool& bad)
+__device__ __forceinline__ void angle_add(int32_t code, const float3& xi, const float3& xp, const float3& xq,
+                                          const AngleK& ak, const BoxK& box, float3& f, double& ei, bool energy)
 {
-    float3 f = make_float3(0.0f, 0.0f, 0.0f);
-    for (int r = 0; r < A; ++r) {
-        const int32_t p = angles[(3 * (int64_t)r + 0) * N + i];
-        const int32_t q = angles[(3 * (int64_t)r + 1) * N + i];
-        const int32_t code = angles[(3 * (int64_t)r + 2) * N + i];
-        if (p < 0)
-            continue;
-        const int role = code & 1, type = code >> 1;
-        if (p >= N || q < 0 || q >= N || type >= ak.ntypes) {
-            bad = true;
-            continue;
-        }
-        const float3 xp = R[p], xq = R[q];
-        // the middle bead and the two ends
-        const float3 xm = role ? xi : xp;
-        const float3 x1 = role ? xp : xi;
-        float a[3], b[3];
-        a[0] = min_image(x1.x, xm.x, box.L[0], box.halfL[0]);
-        a[1] = min_image(x1.y, xm.y, box.L[1], box.halfL[1]);
-        a[2] = min_image(x1.z, xm.z, box.L[2], box.halfL[2]);
-        b[0] = min_image(xq.x, xm.x, box.L[0], box.halfL[0]);
-        b[1] = min_image(xq.y, xm.y, box.L[1], box.halfL[1]);
-        b[2] = min_image(xq.z, xm.z, box.L[2], box.halfL[2]);
-        const float na = sqrtf(a[0] * a[0] + a[1] * a[1] + a[2] * a[2]);
-        const float nb = sqrtf(b[0] * b[0] + b[1] * b[1] + b[2] * b[2]);
-        const float dot = a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
-        const float cx = a[1] * b[2] - a[2] * b[1], cy = a[2] * b[0] - a[0] * b[2], cz = a[0] * b[1] - a[1] * b[0];
-        const float cr = sqrtf(cx * cx + cy * cy + cz * cz);
-        const float c = dot / (na * nb);
-        float U, dUdc;
-        if (ak.form[type] == 0) {
-            const float th = atan2f(cr, dot) - ak.theta0[type];
-            const float st = fmaxf(cr / (na * nb), 1e-3f);
-            U = ak.k[type] * th * th;
-            dUdc = -2.0f * ak.k[type] * th / st;
-        } else {
-            const float dc = c - ak.cos0[type];
-            U = ak.k[type] * dc * dc;
-            dUdc = 2.0f * ak.k[type] * dc;
-        }
-        float g[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const float g1 = (b[d] / nb - c * a[d] / na) / na;
-            const float g2 = (a[d] / na - c * b[d] / nb) / nb;
-            g[d] = role ? -(g1 + g2) : g1;
-        }
-        f.x -= dUdc * g[0];
-        f.y -= dUdc * g[1];
-        f.z -= dUdc * g[2];
-        ei += (double)U / 3.0;
+    const int role = code & 1, type = code >> 1;
+    // the middle bead and the two ends
+    const float3 xm = role ? xi : xp;
+    const float3 x1 = role ? xp : xi;
+    float a[3], b[3];
+    a[0] = min_image(x1.x, xm.x, box.L[0], box.halfL[0]);
+    a[1] = min_image(x1.y, xm.y, box.L[1], box.halfL[1]);
+    a[2] = min_image(x1.z, xm.z, box.L[2], box.halfL[2]);
+    b[0] = min_image(xq.x, xm.x, box.L[0], box.halfL[0]);
+    b[1] = min_image(xq.y, xm.y, box.L[1], box.halfL[1]);
+    b[2] = min_image(xq.z, xm.z, box.L[2], box.halfL[2]);
+    const float na = sqrtf(a[0] * a[0] + a[1] * a[1] + a[2] * a[2]);
+    const float nb = sqrtf(b[0] * b[0] + b[1] * b[1] + b[2] * b[2]);
+    const float dot = a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
+    const float cx = a[1] * b[2] - a[2] * b[1], cy = a[2] * b[0] - a[0] * b[2], cz = a[0] * b[1] - a[1] * b[0];
+    const float cr = sqrtf(cx * cx + cy * cy + cz * cz);
+    const float c = dot / (na * nb);
+    float U, dUdc;
+    if (ak.form[type] == 0) {
+        const float th = atan2f(cr, dot) - ak.theta0[type];
+        const float st = fmaxf(cr / (na * nb), 1e-3f);
+        U = ak.k[type] * th * th;
+        dUdc = -2.0f * ak.k[type] * th / st;
+    } else {
+        const float dc = c - ak.cos0[type];
+        U = ak.k[type] * dc * dc;
+        dUdc = 2.0f * ak.k[type] * dc;
     }
-    return f;
+    float g[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const float g1 = (b[d] / nb - c * a[d] / na) / na;
+        const float g2 = (a[d] / na - c * b[d] / nb) / nb;
+        g[d] = role ? -(g1 + g2) : g1;
+    }
+    f.x -= dUdc * g[0];
+    f.y -= dUdc * g[1];
+    f.z -= dUdc * g[2];
+    if (energy)                          // uniform: only where the caller sums it
+        ei += (double)U / 3.0;
+}
+
+// Force on bead i from its angle-table rows [first, A), added to f.
+__device__ __forceinline__ void angle_sum(int64_t i, const float3& xi, const float3* __restrict__ R, int64_t N,
+                                          const int32_t* __restrict__ angles, int first, int A, const AngleK& ak,
+                                          const BoxK& box, float3& f, double& ei, bool& bad, bool energy)
+{
+    for (int r = first; r < A; ++r) {
+        const AngleRow a = angle_row(angles, r, N, i);
+        if (angle_valid(a, N, ak))
+            angle_add(a.code, xi, R[a.p], R[a.q], ak, box, f, ei, energy);
+        else
+            bad |= a.p >= 0;
+    }
 }
 
 // F_i += the angle forces on bead i; optional FP64 energy partials.
@@ -426,7 +455,8 @@ __global__ __launch_bounds__(kPThreads) void k_angle_forces(const float3* __rest
     double e = 0.0;
     bool bad = false;
     FOR_BEADS(w, i) {
-        const float3 fa = angle_sum(i, R[i], R, N, angles, A, ak, box, e, bad);
+        float3 fa = make_float3(0.0f, 0.0f, 0.0f);
+        angle_sum(i, R[i], R, N, angles, 0, A, ak, box, fa, e, bad, e_part != nullptr);
         float3 f = F[i];
         f.x += fa.x;
         f.y += fa.y;
@@ -523,6 +553,224 @@ __global__ __launch_bounds__(kPThreads) void k_verlet_half2(float3* __restrict__
         raise_flag(HPF_FLAG_NONFINITE);
     if (kin_part)
         acc.store(kin_part, w.block, scratch);
+}
+
+// All forces on a bead and its second half kick in one pass: the gather (centred, or the
+// staggered stencil with kStag), the bonds, the angles (kAngles) and verlet_step(half = 2),
+// each with the operations of its own kernel in the same order, so forces, velocities and
+// (same walk, same slots) energy partials are theirs bit for bit. Bound by the latency of its
+// dependent reads (own row and table rows, then corners and partners) and, with angles, by
+// their divisions: the table rows of up to kPreRows bonds and kPreAngles angles are read at
+// once, and an angle's two partners one angle ahead. Held to 128 VGPRs (4 waves per SIMD):
+// with six angle rows ahead it took 147 and 72 us, with three 62. One pass instead of four
+// saves their re-reads of R and F (36 B a bead each) and three launches: on 1.2M beads of
+// lipids in water (five angle slots, three bond rows) they took 24 + 14 + 39 + 8.5 us.
+constexpr int kPreRows = 3;
+constexpr int kPreAngles = 3;
+
+template <bool kStag, bool kR0Zero, bool kAngles>
+__global__ __launch_bounds__(kPThreads, 4) void k_force_kick(const float3* __restrict__ R, const uint8_t* __restrict__ T,
+                                                          int64_t N, MeshK m, int K, const float* __restrict__ field,
+                                                          const int32_t* __restrict__ bonds, int D, float k, float r0,
+                                                          const int32_t* __restrict__ angles, int A, AngleK ak,
+                                                          BoxK box, float3* __restrict__ F, float3* __restrict__ Vel,
+                                                          const float* __restrict__ inv_mass, float hdt,
+                                                          double* __restrict__ e_part, double* __restrict__ ea_part,
+                                                          double* __restrict__ kin_part)
+{
+    __shared__ double scratch[kPThreads / kWave];
+    const BeadWalk w = bead_walk(N);
+    clear_unused_slots(e_part, 1);
+    clear_unused_slots(ea_part, 1);
+    clear_unused_slots(kin_part, 4);
+    KinAcc acc;
+    double e = 0.0, ea = 0.0;
+    bool bad_bead = false, bad_bond = false, nonfinite = false;
+    FOR_BEADS(w, i) {
+        const float3 r = R[i];
+        const int t = T[i];
+        int32_t j[kPreRows];
+#pragma unroll
+        for (int b = 0; b < kPreRows; ++b)
+            j[b] = b < D ? bonds[(int64_t)b * N + i] : -1;
+        AngleRow an[kAngles ? kPreAngles : 1];
+        if (kAngles) {
+#pragma unroll
+            for (int q = 0; q < kPreAngles; ++q)
+                an[q].p = q < A ? angles[3 * (int64_t)q * N + i] : -1;
+#pragma unroll
+            for (int q = 0; q < kPreAngles; ++q) {
+                an[q].q = an[q].code = 0;
+                if (an[q].p >= 0) {
+                    an[q].q = angles[(3 * (int64_t)q + 1) * N + i];
+                    an[q].code = angles[(3 * (int64_t)q + 2) * N + i];
+                }
+            }
+        }
+        float3 v = Vel[i];
+        float3 xj[kPreRows];
+#pragma unroll
+        for (int b = 0; b < kPreRows; ++b)
+            xj[b] = R[j[b] >= 0 && j[b] < N ? (int64_t)j[b] : i];
+        float3 f;
+        if (kStag)
+            bad_bead |= !field_force_staggered(r, t, m, K, field, f);
+        else
+            bad_bead |= !field_force(r, t, m, K, reinterpret_cast<const float3*>(field), f);
+        float3 fb = make_float3(0.0f, 0.0f, 0.0f);
+        float ei = 0.0f;
+#pragma unroll
+        for (int b = 0; b < kPreRows; ++b) {
+            if (j[b] < 0)
+                continue;
+            if (j[b] >= N) {
+                bad_bond = true;
+                continue;
+            }
+            bond_add<kR0Zero>(r, xj[b], k, r0, box, fb, ei);
+        }
+        for (int b = kPreRows; b < D; ++b) {
+            const int32_t jb = bonds[(int64_t)b * N + i];
+            if (jb >= 0 && jb < N)
+                bond_add<kR0Zero>(r, R[jb], k, r0, box, fb, ei);
+            else
+                bad_bond |= jb >= 0;
+        }
+        f.x += fb.x;
+        f.y += fb.y;
+        f.z += fb.z;
+        e += 0.5 * (double)ei;
+        if (kAngles) {
+            float3 fa = make_float3(0.0f, 0.0f, 0.0f);
+            bool ok = angle_valid(an[0], N, ak);
+            float3 xp = R[ok ? (int64_t)an[0].p : i], xq = R[ok ? (int64_t)an[0].q : i];
+#pragma unroll
+            for (int q = 0; q < kPreAngles; ++q) {
+                const bool now = ok;
+                const float3 xpn = xp, xqn = xq;
+                if (q + 1 < kPreAngles) {
+                    ok = angle_valid(an[q + 1], N, ak);
+                    if (ok) {
+                        xp = R[an[q + 1].p];
+                        xq = R[an[q + 1].q];
+                    }
+                }
+                if (now)
+                    angle_add(an[q].code, r, xpn, xqn, ak, box, fa, ea, ea_part != nullptr);
+                else
+                    bad_bond |= an[q].p >= 0;
+            }
+            if (A > kPreAngles)
+                angle_sum(i, r, R, N, angles, kPreAngles, A, ak, box, fa, ea, bad_bond, ea_part != nullptr);
+            f.x += fa.x;
+            f.y += fa.y;
+            f.z += fa.z;
+        }
+        F[i] = f;
+        const float im = inv_mass ? inv_mass[i] : 1.0f;
+        kick(v, f, im, hdt);
+        nonfinite |= !finite3(v);
+        Vel[i] = v;
+        acc.add(v, im);
+    }
+    if (bad_bead)
+        raise_flag(HPF_FLAG_BAD_BEAD);
+    if (bad_bond)
+        raise_flag(HPF_FLAG_BAD_BOND);
+    if (nonfinite)
+        raise_flag(HPF_FLAG_NONFINITE);
+    if (e_part) {
+        const double s = block_sum(e, scratch);
+        if (threadIdx.x == 0)
+            e_part[w.block] = s;
+    }
+    if (ea_part) {
+        const double s = block_sum(ea, scratch);
+        if (threadIdx.x == 0)
+            ea_part[w.block] = s;
+    }
+    if (kin_part)
+        acc.store(kin_part, w.block, scratch);
+}
+
+// The first half step (verlet_step(half = 1), in place) and the deposit of the new positions
+// in one pass over the cell-sorted beads, a brick a workgroup, into the boxes and counts that
+// k_advance_scatter fills. The next bead's rows are read while this one is deposited. It
+// replaces the half step (60 B a bead) and the four launches of the cell scatter, which read
+// the positions again: 1.2M beads, five species, 74^3 points: 11 + 2.7 + 27 + 8 us apart.
+constexpr int kVSThreads = 512;
+
+__global__ __launch_bounds__(kVSThreads) void k_verlet_scatter(float3* __restrict__ R, float3* __restrict__ Vel,
+                                                               const float3* __restrict__ F,
+                                                               const uint8_t* __restrict__ T,
+                                                               const float* __restrict__ inv_mass, int64_t N,
+                                                               float dt, BoxK box, TileK tk, int K,
+                                                               const uint32_t* __restrict__ cell_start,
+                                                               unsigned long long* __restrict__ partials,
+                                                               unsigned long long* __restrict__ counts)
+{
+    extern __shared__ unsigned long long dbox[];
+    const MeshK& m = tk.m;
+    const int B = tk.B, P = tk.P, h = tk.h;
+    const int nbox = K * P * P * P;
+    const int64_t item = xcd_block(blockIdx.x, gridDim.x);
+    const bool tail = item == tk.ntiles;              // the beads the sort could not bin
+    const float hdt = 0.5f * dt;
+    const int bx = (int)(item % tk.nb[0]);
+    const int by = (int)((item / tk.nb[0]) % tk.nb[1]);
+    const int bz = (int)(item / ((int64_t)tk.nb[0] * tk.nb[1]));
+    const int x0 = bx * B, y0 = by * B, z0 = bz * B;
+    const int ox = min(B, m.M[0] - x0), oy = min(B, m.M[1] - y0), oz = min(B, m.M[2] - z0);
+    const int64_t first = min((int64_t)cell_start[item], N);
+    const int64_t last = tail ? N : min((int64_t)cell_start[item + 1], N);
+    bool bad_bead = false, nonfinite = false;
+    int64_t i = first + threadIdx.x;
+    float3 r, v, f;
+    int t = 0;
+    float im = 1.0f;
+    auto fetch = [&](int64_t q) {
+        r = R[q];
+        v = Vel[q];
+        f = F[q];
+        t = T[q];
+        if (inv_mass)
+            im = inv_mass[q];
+    };
+    if (i < last)
+        fetch(i);
+    if (!tail)
+        for (int q = threadIdx.x; q < nbox; q += kVSThreads)
+            dbox[q] = 0ull;
+    __syncthreads();
+    for (; i < last; i += kVSThreads) {
+        float3 rn = r, vn = v;
+        const float3 fn = f;
+        const int tn = t;
+        const float imn = im;
+        if (i + kVSThreads < last)
+            fetch(i + kVSThreads);
+        kick(vn, fn, imn, hdt);
+        drift(rn, vn, dt, box);
+        nonfinite |= !(finite3(rn) && finite3(vn));
+        Vel[i] = vn;
+        R[i] = rn;
+        BeadCell b;
+        int lx, ly, lz;
+        if (!tail && bead_cell(rn, m, b) && tn < K && brick_box_cell(b, m, x0, y0, z0, ox, oy, oz, h, lx, ly, lz))
+            box_deposit(dbox, P, tn, lx, ly, lz, b);
+        else
+            bad_bead |= !deposit_global(rn, tn, K, m, counts);
+    }
+    if (bad_bead)
+        raise_flag(HPF_FLAG_BAD_BEAD);
+    if (nonfinite)
+        raise_flag(HPF_FLAG_NONFINITE);
+    if (tail)
+        return;
+    __syncthreads();
+    unsigned long long* out = partials + item * (int64_t)nbox;
+    for (int q = threadIdx.x; q < nbox; q += kVSThreads)
+        out[q] = dbox[q];
 }
 
 // One bead of the fused pass: field force + bond forces at x_n, second half
@@ -641,7 +889,6 @@ __device__ __forceinline__ float3 bead_finish(int64_t i, const BeadIn& p, const 
         ff = interp8(L.b, L.g);
     bad_bead |= !L.ok;
     // bond forces: the operations of bond_sum
-    const float two_k = 2.0f * k;
     float3 fb = make_float3(0.0f, 0.0f, 0.0f);
     float ei = 0.0f;
 #pragma unroll
@@ -655,24 +902,7 @@ __device__ __forceinline__ float3 bead_finish(int64_t i, const BeadIn& p, const 
             bad_bond = true;
             continue;
         }
-        const float3 xj = L.xj[b];
-        const float dx = min_image(xj.x, r.x, box.L[0], box.halfL[0]);
-        const float dy = min_image(xj.y, r.y, box.L[1], box.halfL[1]);
-        const float dz = min_image(xj.z, r.z, box.L[2], box.halfL[2]);
-        const float r2 = dx * dx + dy * dy + dz * dz;
-        float coef;
-        if (kR0Zero) {
-            coef = two_k;
-            ei += k * r2;
-        } else {
-            const float rr = sqrtf(r2);
-            const float dr = rr - r0;
-            coef = rr > 0.0f ? two_k * dr / rr : 0.0f;
-            ei += k * dr * dr;
-        }
-        fb.x += coef * dx;
-        fb.y += coef * dy;
-        fb.z += coef * dz;
+        bond_add<kR0Zero>(r, L.xj[b], k, r0, box, fb, ei);
     }
     float3 f = make_float3(ff.x, ff.y, ff.z);
     f.x += fb.x;
@@ -987,6 +1217,47 @@ hpf_status_t launch_verlet(float* R, float* Vel, const float* F, const float* in
         hipLaunchKernelGGL(k_verlet_half2, dim3((unsigned)nb), dim3(kPThreads), 0, s, Vp, Fp,
                            inv_mass, N, dt, kin_part);
     }
+    return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
+}
+
+using ForceKickFn = void (*)(const float3*, const uint8_t*, int64_t, MeshK, int, const float*, const int32_t*, int,
+                             float, float, const int32_t*, int, AngleK, BoxK, float3*, float3*, const float*, float,
+                             double*, double*, double*);
+
+hpf_status_t launch_force_kick(const float* R, const uint8_t* T, int64_t N, const MeshK& m, int K, const float* field,
+                               bool staggered, const int32_t* bonds, int D, float k, float r0, const int32_t* angles,
+                               int A, const AngleK& ak, const BoxK& box, float* F, float* Vel, const float* inv_mass,
+                               float dt, double* e_part, double* ea_part, double* kin_part, hipStream_t s)
+{
+    const bool sums = e_part || ea_part || kin_part;
+    if (N == 0 && !sums)
+        return HPF_OK;
+    const int64_t nb = bead_blocks(N, sums ? HPF_NPART : (1 << 20));
+    static const ForceKickFn fns[2][2][2] = {
+        {{k_force_kick<false, false, false>, k_force_kick<false, false, true>},
+         {k_force_kick<false, true, false>, k_force_kick<false, true, true>}},
+        {{k_force_kick<true, false, false>, k_force_kick<true, false, true>},
+         {k_force_kick<true, true, false>, k_force_kick<true, true, true>}}};
+    hipLaunchKernelGGL(fns[staggered][r0 == 0.0f][A > 0], dim3((unsigned)nb), dim3(kPThreads), 0, s,
+                       reinterpret_cast<const float3*>(R), T, N, m, K, field, bonds, D, k, r0, angles, A, ak, box,
+                       reinterpret_cast<float3*>(F), reinterpret_cast<float3*>(Vel), inv_mass, 0.5f * dt, e_part,
+                       ea_part, kin_part);
+    return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
+}
+
+hpf_status_t launch_verlet_scatter(float* R, float* Vel, const float* F, const uint8_t* T, const float* inv_mass,
+                                   int64_t N, float dt, const BoxK& box, const TileK& tk, int K,
+                                   const uint32_t* cell_start, unsigned long long* partials,
+                                   unsigned long long* counts, hipStream_t s)
+{
+    const size_t smem = scatter_cells_smem(K, tk.P);
+    if (smem > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(k_verlet_scatter),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
+        return HPF_EINVAL;
+    hipLaunchKernelGGL(k_verlet_scatter, dim3((unsigned)(tk.ntiles + 1)), dim3(kVSThreads), smem, s,
+                       reinterpret_cast<float3*>(R), reinterpret_cast<float3*>(Vel),
+                       reinterpret_cast<const float3*>(F), T, inv_mass, N, dt, box, tk, K, cell_start, partials,
+                       counts);
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }
 

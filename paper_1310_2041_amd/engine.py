@@ -2,17 +2,21 @@
 C-ABI calls (velocity Verlet around a density-field force evaluation).
 
 Per step, on one HIP stream:
+  hpf_verlet_scatter           kick + drift + wrap, deposit of the new positions
+  hpf_field_potential_cells    counts, FP64 phi and V
+  hpf_field_gradient           centred mesh gradient
+  hpf_force_kick               F = field + bonds + angles, kick, FP64 kinetic-energy partials
+and in a step that sorts (every ``sort_every`` steps) or whose beads are not cell-sorted, in
+place of the first two:
   verlet_step(half=1)          kick + drift + wrap
-  hpf_sort_by_cell             every ``sort_every`` steps (ping-pong buffers)
+  hpf_sort_by_cell             (ping-pong buffers)
   hpf_density_scatter          fixed-point CIC counts
   hpf_field_potential          FP64 phi and V, counts cleared
-  hpf_field_gradient           centred mesh gradient
-  hpf_force_gather             F = field force (overwrite)
-  bond_forces                  F += harmonic bonds
-  verlet_step(half=2)          kick, FP64 kinetic-energy partials
 Energies are reduced in FP64 only on reporting steps.
 """
 from __future__ import annotations
+
+import contextlib
 
 import numpy as np
 import torch
@@ -42,6 +46,14 @@ def auto_brick(M, K: int, halo: int) -> int:
     if nb >= 512 and K * P ** 3 * 8 <= LDS_BYTES and all(int(m) >= P for m in M):
         return B
     return 8
+
+
+def _on(stream):
+    """Context in which torch enqueues on `stream` (None: the current stream)."""
+    if stream is None:
+        return contextlib.nullcontext()
+    return torch.cuda.stream(stream if isinstance(stream, torch.cuda.Stream) else
+                             torch.cuda.ExternalStream(int(stream)))
 
 
 class HpfState:
@@ -89,6 +101,7 @@ class HpfState:
         # field is rebuilt at every force evaluation and gathered with the deposit's weights.
         if composition_list and (self.field_every != 1 or stencil != "centred"):
             raise ValueError("composition_list needs field_every=1 and the centred stencil")
+        self.strays = None             # step()'s counts of the beads outside their boxes
         self.density_pending = False   # partial boxes + counts hold the deposit of the current R
         # when True, the fused passes also store the total force at x_n into F (F_out)
         self.keep_force = False
@@ -235,17 +248,21 @@ class HpfState:
         """Whether force evaluation `evaluation` rebuilds the density field."""
         return evaluation % self.field_every == 0
 
+    def rebuild(self, report=False, stream=None):
+        """Counts, potential and (centred stencil) gradient of the current positions."""
+        self.scatter(stream)
+        hpf.hpf_field_potential(self.counts, self.mesh, self.field, self.V,
+                                self.part[ROW_W] if (report or self.field_every > 1) else None,
+                                stream, present=self.present)
+        if self.stencil == "centred":
+            hpf.hpf_field_gradient(self.V, self.mesh, self.K, self.G, stream, present=self.present)
+
     def field_forces(self, report=False, stream=None, rebuild=True):
         """F = field force (scatter, potential, gradient, gather); without `rebuild`, only the
         gather from the last gradient. W partials are kept whenever the interval exceeds one,
         so that the steps until the next rebuild report the field energy in force."""
         if rebuild:
-            self.scatter(stream)
-            hpf.hpf_field_potential(self.counts, self.mesh, self.field, self.V,
-                                    self.part[ROW_W] if (report or self.field_every > 1) else None,
-                                    stream, present=self.present)
-            if self.stencil == "centred":
-                hpf.hpf_field_gradient(self.V, self.mesh, self.K, self.G, stream, present=self.present)
+            self.rebuild(report, stream)
         if self.stencil == "staggered":
             hpf.hpf_force_gather_staggered(self.R, self.T, self.mesh, self.K, self.V, self.F, stream)
         else:
@@ -268,15 +285,35 @@ class HpfState:
         self.angle_forces(report, stream)
 
     def step(self, report=False, sort=False, stream=None):
+        rebuild = self.rebuilds_field(self.steps_done + 1)
+        if rebuild and not sort and not self.density_pending and self._strays_ready(stream):
+            # the half step deposits the new positions; the boxes and the beads outside them
+            # (in a counts buffer of its own, zero between steps) become V in one pass
+            hpf.hpf_verlet_scatter(self.R, self.Vel, self.F, self.T, self.dt, self.box, self.mesh, self.K,
+                                   self.cell_start, self.B, self.halo, self.strays, self.scatter_work, stream=stream)
+            hpf.hpf_field_potential_cells(self.strays, self.N, self.mesh, self.field, self.B, self.halo,
+                                          self.scatter_work, self.V,
+                                          self.part[ROW_W] if (report or self.field_every > 1) else None, stream,
+                                          present=self.present)
+            if self.stencil == "centred":
+                hpf.hpf_field_gradient(self.V, self.mesh, self.K, self.G, stream, present=self.present)
+        else:
+            hpf.verlet_step(self.R, self.Vel, self.F, self.dt, self.box, 1, stream=stream)
+            if sort:
+                self.sort(stream)
+            if rebuild:
+                self.rebuild(report, stream)
         self.density_pending = False
-        hpf.verlet_step(self.R, self.Vel, self.F, self.dt, self.box, 1, stream=stream)
-        if sort:
-            self.sort(stream)
-        self.forces(report, stream, rebuild=self.rebuilds_field(self.steps_done + 1))
         kin = self.part[ROW_KE:ROW_KE + 4] if report else None
         th = self.thermostat()
-        hpf.verlet_step(None, self.Vel, self.F, self.dt, self.box, 2,
-                        kin_part=kin if th is None else None, stream=stream)
+        stag = self.stencil == "staggered"
+        k, theta0, form = self.angle_params
+        hpf.hpf_force_kick(self.R, self.T, self.mesh, self.K, self.V if stag else self.G,
+                           self.bonds if self.bonds.shape[0] else None, self.k_bond, self.r0, self.box, self.F,
+                           self.Vel, self.dt, stag, self.angles, k, theta0, form,
+                           e_part=self.part[ROW_EB] if report else None,
+                           ea_part=self.part[ROW_EA] if report and self.angles is not None else None,
+                           kin_part=kin if th is None else None, stream=stream)
         if th is not None:
             hpf.hpf_andersen(self.Vel, th, kin_part=kin, stream=stream)
             self._advance_time_level(stream)
@@ -284,13 +321,21 @@ class HpfState:
             hpf.hpf_reduce_partials(self.part, N_ROWS, self.energy, stream)
         self.steps_done += 1
 
+    def _strays_ready(self, stream=None) -> bool:
+        """Whether step() may deposit in its half step: cell-sorted, and the counts buffer of the
+        beads outside their boxes exists (made on the step's stream at the first such step that
+        is not being captured)."""
+        if not (self.sorted and self.cells_ok):
+            return False
+        if self.strays is None:
+            with _on(stream):
+                if not torch.cuda.is_current_stream_capturing():
+                    self.strays = torch.zeros((self.K, self.nm), dtype=torch.int64, device=self.R.device)
+        return self.strays is not None
+
     def _advance_time_level(self, stream=None):
-        if stream is None:
+        with _on(stream):
             self.tstep.add_(1)
-        else:
-            with torch.cuda.stream(stream if isinstance(stream, torch.cuda.Stream) else
-                                   torch.cuda.ExternalStream(int(stream))):
-                self.tstep.add_(1)
 
     def start(self, sort=True, stream=None):
         """Initial sort and force evaluation, with energies of the initial state."""

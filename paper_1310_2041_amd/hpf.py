@@ -127,6 +127,11 @@ _SIGNATURES = {
     "hpf_advance": ([_P, _P, _P, _P, C.c_int64, C.POINTER(Mesh), C.c_int32, _P, _P, C.c_int32,
                      C.c_float, C.c_float, _P, _P, C.c_float, _P, _P, _P, _P, _P], C.c_int32),
     "hpf_andersen": ([_P, _P, C.c_int64, _P, _P, _P], C.c_int32),
+    "hpf_force_kick": ([_P, _P, C.c_int64, C.POINTER(Mesh), C.c_int32, _P, C.c_int32, _P, C.c_int32, C.c_float,
+                        C.c_float, _P, C.c_int32, C.c_int32, _P, _P, _P, _P, _P, _P, _P, C.c_float, _P, _P, _P,
+                        _P], C.c_int32),
+    "hpf_verlet_scatter": ([_P, _P, _P, _P, _P, C.c_int64, C.c_float, _P, C.POINTER(Mesh), C.c_int32, _P,
+                            C.c_int32, C.c_int32, _P, _P, C.c_size_t, _P], C.c_int32),
     "hpf_advance_scatter": ([_P, _P, _P, _P, C.c_int64, C.POINTER(Mesh), C.c_int32, _P, _P, C.c_int32,
                              C.c_float, C.c_float, _P, _P, C.c_float, _P, C.c_int32, C.c_int32, _P, _P,
                              C.c_size_t, _P, _P, _P, _P, _P], C.c_int32),
@@ -339,21 +344,27 @@ def bond_forces(R, bonds, k: float, r0: float, box, F, e_part=None, stream=None)
                                             _stream(stream)))
 
 
+def _angle_types(k, theta0, form):
+    """Number of angle types and their parameters as C arrays."""
+    kk = [float(x) for x in (k if hasattr(k, "__len__") else (k,))]
+    nt = len(kk)
+    th = [float(x) for x in (theta0 if hasattr(theta0, "__len__") else (theta0,) * nt)]
+    fm = [int(x) for x in (form if hasattr(form, "__len__") else (form,) * nt)]
+    return nt, (C.c_float * nt)(*kk), (C.c_float * nt)(*th), (C.c_int32 * nt)(*fm)
+
+
 def angle_forces(R, angles, k, theta0, form, box, F, e_part=None, stream=None):
     """Angle forces (Bonded forces section) added to F; angles is the per-bead table [3A, N]
     (None = no angles); k, theta0 (radians), form: one value per angle type."""
     N = R.shape[0]
     A = angles.shape[0] // 3 if angles is not None else 0
-    kk = [float(x) for x in (k if hasattr(k, "__len__") else (k,))]
-    nt = len(kk)
-    th = [float(x) for x in (theta0 if hasattr(theta0, "__len__") else (theta0,) * nt)]
-    fm = [int(x) for x in (form if hasattr(form, "__len__") else (form,) * nt)]
+    nt, kk, th, fm = _angle_types(k, theta0, form)
     if e_part is not None and e_part.numel() < HPF_NPART:
         raise ValueError("e_part needs HPF_NPART slots")
     _check("angle_forces", lib().angle_forces(
         _dev(R, "R", torch.float32, (N, 3)), N,
         _dev(angles, "angles", torch.int32, (3 * A, N), allow_none=True) if A else None, A, nt,
-        (C.c_float * nt)(*kk), (C.c_float * nt)(*th), (C.c_int32 * nt)(*fm), _box(box),
+        kk, th, fm, _box(box),
         _dev(F, "F", torch.float32, (N, 3)),
         _dev(e_part, "e_part", torch.float64, None, allow_none=True), _stream(stream)))
 
@@ -378,6 +389,43 @@ def verlet_step(R, Vel, F, dt: float, box, half: int, inv_mass=None, kin_part=No
         raise ValueError("kin_part needs 4 * HPF_NPART slots")
     _check("verlet_step", lib().verlet_step(r, v, f, im, N, float(dt), _box(box), int(half), kp,
                                             _stream(stream)))
+
+
+def hpf_force_kick(R, T, mesh: Mesh, K: int, field, bonds, k: float, r0: float, box, F, Vel, dt: float,
+                   staggered: bool = False, angles=None, angle_k=(), theta0=(), form=(), inv_mass=None, e_part=None,
+                   ea_part=None, kin_part=None, stream=None):
+    """All forces and the second half kick; field is the gradient [K, M^3, 3], or the potential [K, M^3]
+    when staggered."""
+    N = R.shape[0]
+    D = bonds.shape[0] if bonds is not None else 0
+    A = angles.shape[0] // 3 if angles is not None else 0
+    nt, kk, th, fm = _angle_types(angle_k, theta0, form) if A else (0, None, None, None)
+    for p, n, name in ((e_part, 1, "e_part"), (ea_part, 1, "ea_part"), (kin_part, 4, "kin_part")):
+        if p is not None and p.numel() < n * HPF_NPART:
+            raise ValueError(f"{name} needs {n} * HPF_NPART slots")
+    shape = (K, _nm(mesh)) if staggered else (K, _nm(mesh), 3)
+    _check("hpf_force_kick", lib().hpf_force_kick(
+        _dev(R, "R", torch.float32, (N, 3)), _dev(T, "T", torch.uint8, (N,)), N, C.byref(mesh), int(K),
+        _dev(field, "field", torch.float32, shape), int(bool(staggered)),
+        _dev(bonds, "bonds", torch.int32, (D, N), allow_none=True) if D else None, D, float(k), float(r0),
+        _dev(angles, "angles", torch.int32, (3 * A, N), allow_none=True) if A else None, A, nt, kk, th, fm, _box(box),
+        _dev(F, "F", torch.float32, (N, 3)), _dev(Vel, "Vel", torch.float32, (N, 3)),
+        _dev(inv_mass, "inv_mass", torch.float32, (N,), allow_none=True), float(dt),
+        _dev(e_part, "e_part", torch.float64, None, allow_none=True),
+        _dev(ea_part, "ea_part", torch.float64, None, allow_none=True),
+        _dev(kin_part, "kin_part", torch.float64, None, allow_none=True), _stream(stream)))
+
+
+def hpf_verlet_scatter(R, Vel, F, T, dt: float, box, mesh: Mesh, K: int, cell_start, B: int, halo: int, counts, work,
+                       inv_mass=None, stream=None):
+    N = R.shape[0]
+    _check("hpf_verlet_scatter", lib().hpf_verlet_scatter(
+        _dev(R, "R", torch.float32, (N, 3)), _dev(Vel, "Vel", torch.float32, (N, 3)),
+        _dev(F, "F", torch.float32, (N, 3)), _dev(T, "T", torch.uint8, (N,)),
+        _dev(inv_mass, "inv_mass", torch.float32, (N,), allow_none=True), N, float(dt), _box(box), C.byref(mesh),
+        int(K), _dev(cell_start, "cell_start", torch.int32, (sort_key_count(mesh, B) + 2,)), int(B), int(halo),
+        _dev(counts, "counts", torch.int64, (K, _nm(mesh))), _dev(work, "work", torch.uint8), work.numel(),
+        _stream(stream)))
 
 
 def hpf_advance(R, R_next, Vel, T, mesh: Mesh, K: int, G, bonds, k: float, r0: float, box,

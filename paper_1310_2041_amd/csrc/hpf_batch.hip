@@ -321,18 +321,18 @@ __global__ __launch_bounds__(kASThreadsBatch) void k_batch_advance_scatter(
         if (kPipe) {
             // software-pipelined as in k_advance_scatter (the table has at most kPreBonds rows)
             int64_t i = first + threadIdx.x;
-            BeadIn cur;
+            BeadIn<kPreBonds> cur;
             if (i < last)
                 bead_fetch<kThermo, kNT>(cur, i, R, Vel, T, bonds, D, Ntot, nullptr, th);
             for (; i < last; i += kASThreadsBatch) {
-                BeadLoads L;
+                BeadLoads<kPreBonds> L;
                 if constexpr (kNT)
                     __builtin_amdgcn_s_setprio(1);
-                bead_issue(L, cur, i, m, K, Gr, R, Ntot);
+                bead_issue<kThermo, kNT>(L, cur, i, m, K, Gr, R, Vel, Ntot, th);
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (kNT)
                     __builtin_amdgcn_s_setprio(0);
-                BeadIn nxt;
+                BeadIn<kPreBonds> nxt;
                 bead_fetch<kThermo, kNT>(nxt, min(i + kASThreadsBatch, last - 1), R, Vel, T, bonds, D, Ntot, nullptr,
                                     th);
                 __builtin_amdgcn_sched_barrier(0);

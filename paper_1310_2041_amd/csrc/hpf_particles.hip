@@ -813,7 +813,8 @@ __device__ __forceinline__ float3 advance_bead(int64_t i, const float3* __restri
     return r;
 }
 
-// Software-pipelined form of advance_bead for bond tables of at most two rows.
+// Software-pipelined form of advance_bead for bond tables of at most three rows (600,000 beads
+// of three-armed stars: the depositing pass 35.7 us in the plain loop, 32.3 piped).
 // A bead's own data (position, velocity, type, bond row, inverse mass) is
 // loaded one loop iteration ahead, and those loads are issued after the
 // current bead's corner and partner loads: vector memory operations retire in
@@ -825,35 +826,43 @@ __device__ __forceinline__ float3 advance_bead(int64_t i, const float3* __restri
 // other waves' arithmetic: the 10M-bead blend's depositing pass went from 257 to 248 us
 // and the 100M-bead step from 4.27 to 4.21 ms; a system inside the Infinity Cache (1M
 // beads) ran 4 us slower with it, and keeps the default priority.
-constexpr int kPreBonds = 2;
+constexpr int kPreBonds = 2;       // rows of a linear chain
+constexpr int kPreBondsWide = 3;   // branched molecules
 
+// Whether a bead's velocity is read one bead ahead too. The wider bond table reads it with the
+// corners instead: held a bead ahead it would not fit the 128 VGPRs of two workgroups per CU.
+template <int kD>
+constexpr bool kHoldV = kD <= kPreBonds;
+
+template <int kD>
 struct BeadIn {
     float3 r, v;
     float im;
     int t;
     int32_t tag;
-    int32_t j[kPreBonds];
+    int32_t j[kD];
 };
 
-template <bool kThermo, bool kNT>
-__device__ __forceinline__ void bead_fetch(BeadIn& p, int64_t i, const float3* __restrict__ R,
+template <bool kThermo, bool kNT, int kD>
+__device__ __forceinline__ void bead_fetch(BeadIn<kD>& p, int64_t i, const float3* __restrict__ R,
                                            const float3* __restrict__ Vel, const uint8_t* __restrict__ T,
                                            const int32_t* __restrict__ bonds, int D, int64_t N,
                                            const float* __restrict__ inv_mass, const ThermoK& th)
 {
     p.r = R[i];                       // also read as bond partners: cached
-    p.v = load_hint<kNT>(Vel + i);
+    if (kHoldV<kD>)
+        p.v = load_hint<kNT>(Vel + i);
     p.t = load_hint<kNT>(T + i);
     p.im = inv_mass ? inv_mass[i] : 1.0f;
-    p.tag = (kThermo && th.thr) ? th.tag[i] : 0;
 #pragma unroll
-    for (int b = 0; b < kPreBonds; ++b)
+    for (int b = 0; b < kD; ++b)
         p.j[b] = b < D ? load_hint<kNT>(bonds + (int64_t)b * N + i) : -1;
 }
 
+template <int kD>
 struct BeadLoads {
     float3 g[8];
-    float3 xj[kPreBonds];
+    float3 xj[kD];
     BeadCell b;
     bool ok;
 };
@@ -861,23 +870,28 @@ struct BeadLoads {
 // Cell of the bead, its 8 corner loads (corners_buffer; a bead that cannot be binned
 // loads the corners of cell 0 and gets no field force) and its partner loads (an index
 // outside [0, N) loads the bead itself; the bond is then skipped or flagged).
-__device__ __forceinline__ void bead_issue(BeadLoads& L, const BeadIn& p, int64_t i, const MeshK& m, int K,
-                                           const float3* __restrict__ G, const float3* __restrict__ R, int64_t N)
+template <bool kThermo, bool kNT, int kD>
+__device__ __forceinline__ void bead_issue(BeadLoads<kD>& L, BeadIn<kD>& p, int64_t i, const MeshK& m, int K,
+                                           const float3* __restrict__ G, const float3* __restrict__ R,
+                                           const float3* __restrict__ Vel, int64_t N, const ThermoK& th)
 {
+    if (!kHoldV<kD>)
+        p.v = load_hint<kNT>(Vel + i);
+    p.tag = (kThermo && th.thr) ? th.tag[i] : 0;
     L.ok = bead_cell(p.r, m, L.b) && p.t < K;
     BeadCell c = L.b;
     if (!L.ok)
         c.c[0] = c.c[1] = c.c[2] = 0;
     corners_buffer(c, L.ok ? p.t : 0, m, G, L.g);
 #pragma unroll
-    for (int b = 0; b < kPreBonds; ++b) {
+    for (int b = 0; b < kD; ++b) {
         const int32_t j = p.j[b];
         L.xj[b] = R[(j >= 0 && j < N) ? (int64_t)j : i];
     }
 }
 
-template <bool kR0Zero, bool kThermo, bool kNT>
-__device__ __forceinline__ float3 bead_finish(int64_t i, const BeadIn& p, const BeadLoads& L,
+template <bool kR0Zero, bool kThermo, bool kNT, int kD>
+__device__ __forceinline__ float3 bead_finish(int64_t i, const BeadIn<kD>& p, const BeadLoads<kD>& L,
                                               float3* __restrict__ R_next, float3* __restrict__ Vel, int64_t N,
                                               int D, float k, float r0, const BoxK& box, float dt, float hdt,
                                               float3* __restrict__ F_out, KinAcc& acc, double& e, bool& bad_bead,
@@ -892,7 +906,7 @@ __device__ __forceinline__ float3 bead_finish(int64_t i, const BeadIn& p, const 
     float3 fb = make_float3(0.0f, 0.0f, 0.0f);
     float ei = 0.0f;
 #pragma unroll
-    for (int b = 0; b < kPreBonds; ++b) {
+    for (int b = 0; b < kD; ++b) {
         if (b >= D)
             break;
         const int32_t j = p.j[b];
@@ -930,7 +944,7 @@ __device__ __forceinline__ float3 bead_finish(int64_t i, const BeadIn& p, const 
 // (4% faster at 10M beads than 256); the general loop keeps kPThreads.
 constexpr int kAdvPipeThreads = 512;
 
-template <bool kR0Zero, bool kPipe, bool kThermo, bool kNT>
+template <bool kR0Zero, bool kPipe, bool kThermo, bool kNT, int kD>
 __global__ __launch_bounds__(kAdvPipeThreads) void k_advance(const float3* __restrict__ R,
                                                        float3* __restrict__ R_next,
                                                        float3* __restrict__ Vel,
@@ -957,18 +971,18 @@ __global__ __launch_bounds__(kAdvPipeThreads) void k_advance(const float3* __res
         // rows): a thread's beads are i, i + stride, ... (one per chunk of its walk), and
         // the next one's own loads stay in flight through this one's arithmetic
         int64_t i = w.first + threadIdx.x;
-        BeadIn cur;
+        BeadIn<kD> cur;
         if (i < w.end)
             bead_fetch<kThermo, kNT>(cur, i, R, Vel, T, bonds, D, N, inv_mass, th);
         for (; i < w.end; i += w.stride) {
-            BeadLoads L;
+            BeadLoads<kD> L;
             if constexpr (kNT)
                 __builtin_amdgcn_s_setprio(1);
-            bead_issue(L, cur, i, m, K, G, R, N);
+            bead_issue<kThermo, kNT>(L, cur, i, m, K, G, R, Vel, N, th);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (kNT)
                 __builtin_amdgcn_s_setprio(0);
-            BeadIn nxt;
+            BeadIn<kD> nxt;
             bead_fetch<kThermo, kNT>(nxt, i + w.stride < w.end ? i + w.stride : i, R, Vel, T, bonds, D, N, inv_mass,
                                 th);
             __builtin_amdgcn_sched_barrier(0);
@@ -1016,13 +1030,17 @@ __global__ __launch_bounds__(kAdvPipeThreads) void k_advance(const float3* __res
 // and on the stored deposit boxes.
 constexpr int kASThreadsDefault = 512;
 constexpr int kASThreadsWide = 768;
+// The thermostat's form needs more than 128 VGPRs, so a CU holds 3 waves per SIMD of it: three
+// workgroups of 256 threads, but only one of 512 (3.3M beads in 2028 bricks: 137 against 189 us;
+// 384 threads, whose second workgroup did not fit either, 219).
+constexpr int kASThreadsThermo = 256;
 
-template <bool kR0Zero, int kASThreads, bool kPipe, bool kThermo, bool kNT>
-// The second bound is waves per SIMD. The production form (512 threads, r0 = 0, no
-// thermostat) keeps two workgroups per CU, 4 waves per SIMD (at most 128 VGPRs, which it
-// fits without spilling); the others take 3 (at most 168), as does a 768-thread workgroup,
-// which runs alone on its CU next to its large deposit box.
-__global__ __launch_bounds__(kASThreads, kASThreads == kASThreadsDefault && kR0Zero && !kThermo ? 4 : 3) void
+template <bool kR0Zero, int kASThreads, bool kPipe, bool kThermo, bool kNT, int kD>
+// The second bound is waves per SIMD. The form without the thermostat (512 threads) keeps two
+// workgroups per CU, 4 waves per SIMD (at most 128 VGPRs, which it fits without spilling);
+// the others take 3 (at most 168), as does a 768-thread workgroup, which runs alone on its CU
+// next to its large deposit box.
+__global__ __launch_bounds__(kASThreads, kASThreads == kASThreadsDefault && !kThermo ? 4 : 3) void
 k_advance_scatter(
     const float3* __restrict__ R,
                                                                 float3* __restrict__ R_next,
@@ -1072,18 +1090,18 @@ k_advance_scatter(
                 // that order) and stay in flight through its arithmetic; a thread's last
                 // bead fetches a valid bead again.
                 int64_t i = first + threadIdx.x;
-                BeadIn cur;
+                BeadIn<kD> cur;
                 if (i < last)
                     bead_fetch<kThermo, kNT>(cur, i, R, Vel, T, bonds, D, N, inv_mass, th);
                 for (; i < last; i += kASThreads) {
-                    BeadLoads L;
+                    BeadLoads<kD> L;
                     if constexpr (kNT)
                         __builtin_amdgcn_s_setprio(1);
-                    bead_issue(L, cur, i, m, K, G, R, N);
+                    bead_issue<kThermo, kNT>(L, cur, i, m, K, G, R, Vel, N, th);
                     __builtin_amdgcn_sched_barrier(0);
                     if constexpr (kNT)
                         __builtin_amdgcn_s_setprio(0);
-                    BeadIn nxt;
+                    BeadIn<kD> nxt;
                     bead_fetch<kThermo, kNT>(nxt, min(i + kASThreads, last - 1), R, Vel, T, bonds, D, N, inv_mass, th);
                     __builtin_amdgcn_sched_barrier(0);
                     const float3 rn = bead_finish<kR0Zero, kThermo, kNT>(i, cur, L, R_next, Vel, N, D, k, r0, box, dt, hdt,
@@ -1265,18 +1283,24 @@ hpf_status_t launch_verlet_scatter(float* R, float* Vel, const float* F, const u
 // prefetches, the gradient mesh and the stored deposit boxes.
 static int64_t streamed_bytes(int64_t N, int D, int K, const MeshK& m, int64_t box_bytes)
 {
-    return N * (49 + 4 * (int64_t)std::min(D, kPreBonds)) + (int64_t)K * m.nm * 12 + box_bytes;
+    return N * (49 + 4 * (int64_t)std::min(D, kPreBondsWide)) + (int64_t)K * m.nm * 12 + box_bytes;
 }
 
 using AdvFn = void (*)(const float3*, float3*, float3*, const uint8_t*, int64_t, MeshK, int, const float3*,
                        const int32_t*, int, float, float, BoxK, const float*, float, float3*, double*, double*,
                        ThermoK);
 
-template <bool kPipe, bool kNT>
+template <bool kPipe, bool kNT, int kD>
 static AdvFn advance_fn(bool thermo, bool r0z)
 {
-    return thermo ? (r0z ? k_advance<true, kPipe, true, kNT> : k_advance<false, kPipe, true, kNT>)
-                  : (r0z ? k_advance<true, kPipe, false, kNT> : k_advance<false, kPipe, false, kNT>);
+    return thermo ? (r0z ? k_advance<true, kPipe, true, kNT, kD> : k_advance<false, kPipe, true, kNT, kD>)
+                  : (r0z ? k_advance<true, kPipe, false, kNT, kD> : k_advance<false, kPipe, false, kNT, kD>);
+}
+
+template <int kD>
+static AdvFn advance_pipe_fn(bool nt, bool thermo, bool r0z)
+{
+    return nt ? advance_fn<true, true, kD>(thermo, r0z) : advance_fn<true, false, kD>(thermo, r0z);
 }
 
 hpf_status_t launch_advance(const float* R, float* R_next, float* Vel, const uint8_t* T, int64_t N,
@@ -1286,9 +1310,9 @@ hpf_status_t launch_advance(const float* R, float* R_next, float* Vel, const uin
 {
     if (N == 0 && !e_part && !kin_part)
         return HPF_OK;
-    // the software-pipelined bead loop serves bond tables of up to kPreBonds rows and
+    // the software-pipelined bead loop serves bond tables of up to kPreBondsWide rows and
     // gradient meshes of up to kBufMeshBytes
-    const bool pipe = D <= kPreBonds && (int64_t)K * m.nm * 12 <= kBufMeshBytes;
+    const bool pipe = D <= kPreBondsWide && (int64_t)K * m.nm * 12 <= kBufMeshBytes;
     const int threads = pipe ? kAdvPipeThreads : kPThreads;
     const int64_t cap = (e_part || kin_part) ? HPF_NPART : (1 << 20);
     const int64_t nb = std::max<int64_t>(1, std::min<int64_t>((N + threads - 1) / threads, cap));
@@ -1300,14 +1324,15 @@ hpf_status_t launch_advance(const float* R, float* R_next, float* Vel, const uin
     auto* Fo = reinterpret_cast<float3*>(F_out);
     const bool thermo = th.thr != 0, r0z = r0 == 0.0f;
     const bool nt = pipe && streamed_bytes(N, D, K, m, 0) > kStreamHintBytes;
-    const AdvFn fn = pipe ? (nt ? advance_fn<true, true>(thermo, r0z) : advance_fn<true, false>(thermo, r0z))
-                          : advance_fn<false, false>(thermo, r0z);
+    const AdvFn fn = !pipe            ? advance_fn<false, false, kPreBonds>(thermo, r0z)
+                     : D <= kPreBonds ? advance_pipe_fn<kPreBonds>(nt, thermo, r0z)
+                                      : advance_pipe_fn<kPreBondsWide>(nt, thermo, r0z);
     hipLaunchKernelGGL(fn, g, bl, 0, s, Rp, Rn, Vp, T, N, m, K, Gp, bonds, D, k, r0, box, inv_mass, dt, Fo,
                        e_part, kin_part, th);
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }
 
-template <bool kR0Zero, int kThreads, bool kPipe, bool kThermo, bool kNT>
+template <bool kR0Zero, int kThreads, bool kPipe, bool kThermo, bool kNT, int kD>
 static hpf_status_t launch_advance_scatter_t(const float3* Rp, float3* Rn, float3* Vp, const uint8_t* T, int64_t N,
                                              const TileK& tk, int K, const float3* Gp, const int32_t* bonds, int D,
                                              float k, float r0, const BoxK& box, const float* inv_mass, float dt,
@@ -1316,7 +1341,7 @@ static hpf_status_t launch_advance_scatter_t(const float3* Rp, float3* Rn, float
                                              double* kin_part, const ThermoK& th, hipStream_t s)
 {
     const size_t smem = sizeof(unsigned long long) * (size_t)K * tk.P * tk.P * tk.P;
-    const void* fn = reinterpret_cast<const void*>(k_advance_scatter<kR0Zero, kThreads, kPipe, kThermo, kNT>);
+    const void* fn = reinterpret_cast<const void*>(k_advance_scatter<kR0Zero, kThreads, kPipe, kThermo, kNT, kD>);
     if (smem > 65536 &&
         hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
         return HPF_EINVAL;
@@ -1324,7 +1349,7 @@ static hpf_status_t launch_advance_scatter_t(const float3* Rp, float3* Rn, float
     // uneven bricks; larger meshes walk their bricks with HPF_NPART workgroups
     const int64_t nb = std::min<int64_t>(tk.ntiles + 1, HPF_NPART);
     const dim3 g((unsigned)nb), bl(kThreads);
-    hipLaunchKernelGGL((k_advance_scatter<kR0Zero, kThreads, kPipe, kThermo, kNT>), g, bl, smem, s, Rp, Rn, Vp, T, N, tk,
+    hipLaunchKernelGGL((k_advance_scatter<kR0Zero, kThreads, kPipe, kThermo, kNT, kD>), g, bl, smem, s, Rp, Rn, Vp, T, N, tk,
                        K, Gp, bonds, D, k, r0, box, inv_mass, dt, cell_start, partials, counts, Fo, e_part, kin_part,
                        th);
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
@@ -1335,16 +1360,28 @@ using LaunchFn = hpf_status_t (*)(const float3*, float3*, float3*, const uint8_t
                                   const uint32_t*, unsigned long long*, unsigned long long*, float3*, double*,
                                   double*, const ThermoK&, hipStream_t);
 
-template <bool kPipe, bool kNT>
+template <bool kPipe, bool kNT, int kD>
 static LaunchFn scatter_launch_fn(bool wide, bool thermo, bool r0z)
 {
+    if (thermo) {
+        if (wide)
+            return r0z ? launch_advance_scatter_t<true, kASThreadsWide, kPipe, true, kNT, kD>
+                       : launch_advance_scatter_t<false, kASThreadsWide, kPipe, true, kNT, kD>;
+        return r0z ? launch_advance_scatter_t<true, kASThreadsThermo, kPipe, true, kNT, kD>
+                   : launch_advance_scatter_t<false, kASThreadsThermo, kPipe, true, kNT, kD>;
+    }
     if (wide)
-        return launch_advance_scatter_t<true, kASThreadsWide, kPipe, false, kNT>;
-    if (r0z)
-        return thermo ? launch_advance_scatter_t<true, kASThreadsDefault, kPipe, true, kNT>
-                      : launch_advance_scatter_t<true, kASThreadsDefault, kPipe, false, kNT>;
-    return thermo ? launch_advance_scatter_t<false, kASThreadsDefault, kPipe, true, kNT>
-                  : launch_advance_scatter_t<false, kASThreadsDefault, kPipe, false, kNT>;
+        return r0z ? launch_advance_scatter_t<true, kASThreadsWide, kPipe, false, kNT, kD>
+                   : launch_advance_scatter_t<false, kASThreadsWide, kPipe, false, kNT, kD>;
+    return r0z ? launch_advance_scatter_t<true, kASThreadsDefault, kPipe, false, kNT, kD>
+               : launch_advance_scatter_t<false, kASThreadsDefault, kPipe, false, kNT, kD>;
+}
+
+template <int kD>
+static LaunchFn scatter_pipe_fn(bool nt, bool wide, bool thermo, bool r0z)
+{
+    return nt ? scatter_launch_fn<true, true, kD>(wide, thermo, r0z)
+              : scatter_launch_fn<true, false, kD>(wide, thermo, r0z);
 }
 
 hpf_status_t launch_advance_scatter(const float* R, float* R_next, float* Vel, const uint8_t* T, int64_t N,
@@ -1359,19 +1396,19 @@ hpf_status_t launch_advance_scatter(const float* R, float* R_next, float* Vel, c
     auto* Vp = reinterpret_cast<float3*>(Vel);
     auto* Gp = reinterpret_cast<const float3*>(G);
     auto* Fo = reinterpret_cast<float3*>(F_out);
-    // the software-pipelined bead loop serves bond tables of up to kPreBonds rows and
+    // the software-pipelined bead loop serves bond tables of up to kPreBondsWide rows and
     // gradient meshes of up to kBufMeshBytes
-    const bool pipe = D <= kPreBonds && (int64_t)K * tk.m.nm * 12 <= kBufMeshBytes;
+    const bool pipe = D <= kPreBondsWide && (int64_t)K * tk.m.nm * 12 <= kBufMeshBytes;
     const bool thermo = th.thr != 0, r0z = r0 == 0.0f;
     // A deposit box of more than 80 KiB (16-cell bricks) leaves room for one workgroup per
-    // CU: with r0 = 0 and no thermostat the pass then takes 768 threads (3 waves per SIMD;
-    // 1024 threads would cap it at 128 VGPRs, which spills); the others keep 512.
-    const bool wide = r0z && !thermo && sizeof(unsigned long long) * (size_t)K * tk.P * tk.P * tk.P > 80 * 1024;
+    // CU: the pass then takes 768 threads (3 waves per SIMD; 1024 threads would cap it at 128
+    // VGPRs, which spills).
+    const bool wide = sizeof(unsigned long long) * (size_t)K * tk.P * tk.P * tk.P > 80 * 1024;
     const int64_t box_bytes = (int64_t)sizeof(unsigned long long) * K * tk.P * tk.P * tk.P * tk.ntiles;
     const bool nt = pipe && streamed_bytes(N, D, K, tk.m, box_bytes) > kStreamHintBytes;
-    const LaunchFn launch = pipe ? (nt ? scatter_launch_fn<true, true>(wide, thermo, r0z)
-                                       : scatter_launch_fn<true, false>(wide, thermo, r0z))
-                                 : scatter_launch_fn<false, false>(wide, thermo, r0z);
+    const LaunchFn launch = !pipe            ? scatter_launch_fn<false, false, kPreBonds>(wide, thermo, r0z)
+                            : D <= kPreBonds ? scatter_pipe_fn<kPreBonds>(nt, wide, thermo, r0z)
+                                             : scatter_pipe_fn<kPreBondsWide>(nt, wide, thermo, r0z);
     return launch(Rp, Rn, Vp, T, N, tk, K, Gp, bonds, D, k, r0, box, inv_mass, dt, cell_start, partials, counts, Fo,
                   e_part, kin_part, th, s);
 }

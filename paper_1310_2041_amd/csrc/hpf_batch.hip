@@ -328,7 +328,7 @@ __global__ __launch_bounds__(kASThreadsBatch) void k_batch_advance_scatter(
                 BeadLoads<kPreBonds> L;
                 if constexpr (kNT)
                     __builtin_amdgcn_s_setprio(1);
-                bead_issue<kThermo, kNT>(L, cur, i, m, K, Gr, R, Vel, Ntot, th);
+                bead_issue<false, kThermo, kNT>(L, cur, i, m, K, Gr, R, Vel, Ntot, th);
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (kNT)
                     __builtin_amdgcn_s_setprio(0);
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(kASThreadsBatch) void k_batch_advance_scatter(
                 bead_fetch<kThermo, kNT>(nxt, min(i + kASThreadsBatch, last - 1), R, Vel, T, bonds, D, Ntot, nullptr,
                                     th);
                 __builtin_amdgcn_sched_barrier(0);
-                const float3 rn = bead_finish<kR0Zero, kThermo, kNT>(i, cur, L, R_next, Vel, Ntot, D, k, r0, rp.box, dt,
+                const float3 rn = bead_finish<false, kR0Zero, kThermo, kNT>(true, i, cur, L, R_next, Vel, Ntot, D, k, r0, rp.box, dt,
                                                                 hdt,
                                                        nullptr, acc, e, bad_bead, bad_bond, nonfinite, th, tstep);
                 const int t = cur.t;

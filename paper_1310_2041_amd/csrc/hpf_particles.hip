@@ -70,27 +70,13 @@ struct BoxK {
 
 // ------------------------------------------------------- device functions --
 
-// Trilinear interpolation of the gradient at a bead from the 8 corner values
-// g[a], a = x + 2y + 4z, with the exact FP32 dyadic 1-D weights (separable
-// form of -sum_a (W_a / 2^48) G(c + a)).
-__device__ __forceinline__ float3 interp8(const BeadCell& b, const float3 (&g)[8])
+// The y and z steps of the trilinear interpolation from the four x sums e(y, z).
+__device__ __forceinline__ float3 interp_yz(const BeadCell& b, const float3& e00, const float3& e10,
+                                            const float3& e01, const float3& e11)
 {
-    const float ax1 = (float)b.q[0] * kInvOne, ax0 = (float)(kOne - b.q[0]) * kInvOne;
     const float ay1 = (float)b.q[1] * kInvOne, ay0 = (float)(kOne - b.q[1]) * kInvOne;
     const float az1 = (float)b.q[2] * kInvOne, az0 = (float)(kOne - b.q[2]) * kInvOne;
-    float3 e00, e10, e01, e11, f0, f1, f;
-    e00.x = ax0 * g[0].x + ax1 * g[1].x;
-    e00.y = ax0 * g[0].y + ax1 * g[1].y;
-    e00.z = ax0 * g[0].z + ax1 * g[1].z;
-    e10.x = ax0 * g[2].x + ax1 * g[3].x;
-    e10.y = ax0 * g[2].y + ax1 * g[3].y;
-    e10.z = ax0 * g[2].z + ax1 * g[3].z;
-    e01.x = ax0 * g[4].x + ax1 * g[5].x;
-    e01.y = ax0 * g[4].y + ax1 * g[5].y;
-    e01.z = ax0 * g[4].z + ax1 * g[5].z;
-    e11.x = ax0 * g[6].x + ax1 * g[7].x;
-    e11.y = ax0 * g[6].y + ax1 * g[7].y;
-    e11.z = ax0 * g[6].z + ax1 * g[7].z;
+    float3 f0, f1, f;
     f0.x = ay0 * e00.x + ay1 * e10.x;
     f0.y = ay0 * e00.y + ay1 * e10.y;
     f0.z = ay0 * e00.z + ay1 * e10.z;
@@ -101,6 +87,22 @@ __device__ __forceinline__ float3 interp8(const BeadCell& b, const float3 (&g)[8
     f.y = -(az0 * f0.y + az1 * f1.y);
     f.z = -(az0 * f0.z + az1 * f1.z);
     return f;
+}
+
+// Trilinear interpolation of the gradient at a bead from the 8 corner values
+// g[a], a = x + 2y + 4z, with the exact FP32 dyadic 1-D weights (separable
+// form of -sum_a (W_a / 2^48) G(c + a)).
+__device__ __forceinline__ float3 interp8(const BeadCell& b, const float3 (&g)[8])
+{
+    const float ax1 = (float)b.q[0] * kInvOne, ax0 = (float)(kOne - b.q[0]) * kInvOne;
+    float3 e[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        e[a].x = ax0 * g[2 * a].x + ax1 * g[2 * a + 1].x;
+        e[a].y = ax0 * g[2 * a].y + ax1 * g[2 * a + 1].y;
+        e[a].z = ax0 * g[2 * a].z + ax1 * g[2 * a + 1].z;
+    }
+    return interp_yz(b, e[0], e[1], e[2], e[3]);
 }
 
 // The 8 corner values of cell b from species t's gradient mesh in memory.
@@ -124,9 +126,9 @@ __device__ __forceinline__ void corners_global(const BeadCell& b, int t, const M
     g[7] = Gk[r11 + x1];
 }
 
-// corners_global with 32-bit offsets into one buffer resource over the gradient mesh
-// (at most kBufMeshBytes, which the launches check): the offsets need no 64-bit address
-// arithmetic and keep fewer registers live while the loads are in flight.
+// The pipelined passes load corners with 32-bit offsets into one buffer resource over the
+// gradient mesh (at most kBufMeshBytes, which the launches check): the offsets need no 64-bit
+// address arithmetic and keep fewer registers live while the loads are in flight.
 constexpr int64_t kBufMeshBytes = 0x7fffffff;
 
 __device__ __forceinline__ void corners_buffer(const BeadCell& b, int t, const MeshK& m,
@@ -148,6 +150,79 @@ __device__ __forceinline__ void corners_buffer(const BeadCell& b, int t, const M
         const v3f v = __builtin_amdgcn_raw_buffer_load_b96(rs, (int)(off[a] * 12u), 0, 0);
         g[a] = make_float3(v.x, v.y, v.z);
     }
+}
+
+// The value of the neighbouring lane (lane ^ 1), by a DPP move; both lanes must be active.
+__device__ __forceinline__ uint32_t pair_swap(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);
+}
+__device__ __forceinline__ float pair_swap(float v) { return __uint_as_float(pair_swap(__float_as_uint(v))); }
+
+// Corner loads of two beads by two neighbouring lanes: for each of the 4 corner rows of a bead
+// the even lane loads the lower x corner and the odd lane the upper one, first for the even
+// lane's bead (g[0..3]), then for the odd lane's (g[4..7]). The two x corners are neighbours in
+// memory, so a wavefront's load touches 32 lines instead of 64 (a load that hits L1 takes 33
+// cycles instead of 64, one that misses 71 instead of 140). It costs some 20 registers, which
+// only the workgroup of 768 threads, alone on its CU, has to spare: there the 10M-bead blend's
+// step goes from 315 to 309 us; elsewhere it costs a workgroup per CU, or in a batch gains
+// nothing.
+__device__ __forceinline__ void corners_pair(const BeadCell& b, int t, const MeshK& m,
+                                             const float3* __restrict__ G, float3 (&g)[8])
+{
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float3*>(G), 0, (int)kBufMeshBytes, 0x00020000);
+    const bool odd = threadIdx.x & 1;
+    const uint32_t Mx = m.M[0], My = m.M[1];
+    const uint32_t x0 = b.c[0], x1 = next_wrap(b.c[0], m.M[0]);
+    const uint32_t y0 = b.c[1], y1 = next_wrap(b.c[1], m.M[1]);
+    const uint32_t z0 = b.c[2], z1 = next_wrap(b.c[2], m.M[2]);
+    const uint32_t tb = (uint32_t)t * (uint32_t)m.nm;
+    const uint32_t row[4] = {tb + (z0 * My + y0) * Mx, tb + (z0 * My + y1) * Mx, tb + (z1 * My + y0) * Mx,
+                             tb + (z1 * My + y1) * Mx};
+    typedef float v3f __attribute__((ext_vector_type(3)));
+    uint32_t o1[4], o2[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const uint32_t lo = (row[a] + x0) * 12u, hi = (row[a] + x1) * 12u;
+        const uint32_t other = pair_swap(odd ? lo : hi);
+        o1[a] = odd ? other : lo;
+        o2[a] = odd ? hi : other;
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const v3f v = __builtin_amdgcn_raw_buffer_load_b96(rs, (int)o1[a], 0, 0);
+        g[a] = make_float3(v.x, v.y, v.z);
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const v3f v = __builtin_amdgcn_raw_buffer_load_b96(rs, (int)o2[a], 0, 0);
+        g[4 + a] = make_float3(v.x, v.y, v.z);
+    }
+}
+
+// interp8 on the values of corners_pair, bit for bit: each lane forms the x products of the
+// corners it holds, the neighbour's are added by a DPP add (a sum of two does not depend on its
+// order), and each lane keeps its own bead's four sums for the y and z steps. Both lanes must be
+// active.
+__device__ __forceinline__ float3 interp8_pair(const BeadCell& b, const float3 (&g)[8])
+{
+    const bool odd = threadIdx.x & 1;
+    const float ax1 = (float)b.q[0] * kInvOne, ax0 = (float)(kOne - b.q[0]) * kInvOne;
+    const float other = pair_swap(odd ? ax0 : ax1);
+    const float w1 = odd ? other : ax0, w2 = odd ? ax1 : other;
+    float3 e[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const float x1 = w1 * g[a].x, y1 = w1 * g[a].y, z1 = w1 * g[a].z;
+        const float x2 = w2 * g[4 + a].x, y2 = w2 * g[4 + a].y, z2 = w2 * g[4 + a].z;
+        const float sx1 = x1 + pair_swap(x1), sy1 = y1 + pair_swap(y1), sz1 = z1 + pair_swap(z1);
+        const float sx2 = x2 + pair_swap(x2), sy2 = y2 + pair_swap(y2), sz2 = z2 + pair_swap(z2);
+        e[a].x = odd ? sx2 : sx1;
+        e[a].y = odd ? sy2 : sy1;
+        e[a].z = odd ? sz2 : sz1;
+    }
+    return interp_yz(b, e[0], e[1], e[2], e[3]);
 }
 
 // Field force on one bead (eq. 6). False (and zero force) for a bead that
@@ -867,10 +942,10 @@ struct BeadLoads {
     bool ok;
 };
 
-// Cell of the bead, its 8 corner loads (corners_buffer; a bead that cannot be binned
+// Cell of the bead, the corner loads of its lane pair (corners_pair; a bead that cannot be binned
 // loads the corners of cell 0 and gets no field force) and its partner loads (an index
 // outside [0, N) loads the bead itself; the bond is then skipped or flagged).
-template <bool kThermo, bool kNT, int kD>
+template <bool kPair, bool kThermo, bool kNT, int kD>
 __device__ __forceinline__ void bead_issue(BeadLoads<kD>& L, BeadIn<kD>& p, int64_t i, const MeshK& m, int K,
                                            const float3* __restrict__ G, const float3* __restrict__ R,
                                            const float3* __restrict__ Vel, int64_t N, const ThermoK& th)
@@ -882,7 +957,10 @@ __device__ __forceinline__ void bead_issue(BeadLoads<kD>& L, BeadIn<kD>& p, int6
     BeadCell c = L.b;
     if (!L.ok)
         c.c[0] = c.c[1] = c.c[2] = 0;
-    corners_buffer(c, L.ok ? p.t : 0, m, G, L.g);
+    if (kPair)
+        corners_pair(c, L.ok ? p.t : 0, m, G, L.g);
+    else
+        corners_buffer(c, L.ok ? p.t : 0, m, G, L.g);
 #pragma unroll
     for (int b = 0; b < kD; ++b) {
         const int32_t j = p.j[b];
@@ -890,8 +968,8 @@ __device__ __forceinline__ void bead_issue(BeadLoads<kD>& L, BeadIn<kD>& p, int6
     }
 }
 
-template <bool kR0Zero, bool kThermo, bool kNT, int kD>
-__device__ __forceinline__ float3 bead_finish(int64_t i, const BeadIn<kD>& p, const BeadLoads<kD>& L,
+template <bool kPair, bool kR0Zero, bool kThermo, bool kNT, int kD>
+__device__ __forceinline__ float3 bead_finish(bool live, int64_t i, const BeadIn<kD>& p, const BeadLoads<kD>& L,
                                               float3* __restrict__ R_next, float3* __restrict__ Vel, int64_t N,
                                               int D, float k, float r0, const BoxK& box, float dt, float hdt,
                                               float3* __restrict__ F_out, KinAcc& acc, double& e, bool& bad_bead,
@@ -899,8 +977,15 @@ __device__ __forceinline__ float3 bead_finish(int64_t i, const BeadIn<kD>& p, co
 {
     float3 r = p.r;
     float3 ff = make_float3(0.0f, 0.0f, 0.0f);
-    if (L.ok)
+    if (kPair) {
+        const float3 fp = interp8_pair(L.b, L.g);
+        if (!live)                       // the odd lane of a range's last, half-filled pair
+            return r;
+        if (L.ok)
+            ff = fp;
+    } else if (L.ok) {
         ff = interp8(L.b, L.g);
+    }
     bad_bead |= !L.ok;
     // bond forces: the operations of bond_sum
     float3 fb = make_float3(0.0f, 0.0f, 0.0f);
@@ -978,7 +1063,7 @@ __global__ __launch_bounds__(kAdvPipeThreads) void k_advance(const float3* __res
             BeadLoads<kD> L;
             if constexpr (kNT)
                 __builtin_amdgcn_s_setprio(1);
-            bead_issue<kThermo, kNT>(L, cur, i, m, K, G, R, Vel, N, th);
+            bead_issue<false, kThermo, kNT>(L, cur, i, m, K, G, R, Vel, N, th);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (kNT)
                 __builtin_amdgcn_s_setprio(0);
@@ -986,7 +1071,7 @@ __global__ __launch_bounds__(kAdvPipeThreads) void k_advance(const float3* __res
             bead_fetch<kThermo, kNT>(nxt, i + w.stride < w.end ? i + w.stride : i, R, Vel, T, bonds, D, N, inv_mass,
                                 th);
             __builtin_amdgcn_sched_barrier(0);
-            bead_finish<kR0Zero, kThermo, kNT>(i, cur, L, R_next, Vel, N, D, k, r0, box, dt, hdt, F_out, acc, e,
+            bead_finish<false, kR0Zero, kThermo, kNT>(true, i, cur, L, R_next, Vel, N, D, k, r0, box, dt, hdt, F_out, acc, e,
                                           bad_bead, bad_bond, nonfinite, th, tstep);
             cur = nxt;
         }
@@ -1089,25 +1174,33 @@ k_advance_scatter(
                 // after this bead's corner and partner loads (the scheduling barriers keep
                 // that order) and stay in flight through its arithmetic; a thread's last
                 // bead fetches a valid bead again.
+                constexpr bool kPair = kASThreads == kASThreadsWide;
+                const int odd = kPair ? threadIdx.x & 1 : 0;   // a pair of lanes goes on together
                 int64_t i = first + threadIdx.x;
                 BeadIn<kD> cur;
-                if (i < last)
-                    bead_fetch<kThermo, kNT>(cur, i, R, Vel, T, bonds, D, N, inv_mass, th);
-                for (; i < last; i += kASThreads) {
+                if (i - odd < last)
+                    bead_fetch<kThermo, kNT>(cur, min(i, last - 1), R, Vel, T, bonds, D, N, inv_mass, th);
+                for (; i - odd < last; i += kASThreads) {
+                    const bool live = i < last;
+                    const int64_t ic = kPair ? min(i, last - 1) : i;
                     BeadLoads<kD> L;
                     if constexpr (kNT)
                         __builtin_amdgcn_s_setprio(1);
-                    bead_issue<kThermo, kNT>(L, cur, i, m, K, G, R, Vel, N, th);
+                    bead_issue<kPair, kThermo, kNT>(L, cur, ic, m, K, G, R, Vel, N, th);
                     __builtin_amdgcn_sched_barrier(0);
                     if constexpr (kNT)
                         __builtin_amdgcn_s_setprio(0);
                     BeadIn<kD> nxt;
                     bead_fetch<kThermo, kNT>(nxt, min(i + kASThreads, last - 1), R, Vel, T, bonds, D, N, inv_mass, th);
                     __builtin_amdgcn_sched_barrier(0);
-                    const float3 rn = bead_finish<kR0Zero, kThermo, kNT>(i, cur, L, R_next, Vel, N, D, k, r0, box, dt, hdt,
-                                                           F_out, acc, e, bad_bead, bad_bond, nonfinite, th,
-                                                           tstep);
+                    const float3 rn = bead_finish<kPair, kR0Zero, kThermo, kNT>(live, ic, cur, L, R_next, Vel, N, D,
+                                                                                k, r0, box, dt, hdt, F_out, acc, e,
+                                                                                bad_bead, bad_bond, nonfinite, th,
+                                                                                tstep);
                     const int t = cur.t;
+                    cur = nxt;
+                    if (kPair && !live)
+                        continue;
                     BeadCell b;
                     int lx, ly, lz;
                     if (bead_cell(rn, m, b) && t < K &&
@@ -1115,7 +1208,6 @@ k_advance_scatter(
                         box_deposit(dbox, P, t, lx, ly, lz, b);
                     else
                         bad_bead |= !deposit_global(rn, t, K, m, counts);
-                    cur = nxt;
                 }
             } else {
                 for (int64_t i = first + threadIdx.x; i < last; i += kASThreads) {

@@ -108,24 +108,24 @@ __device__ __forceinline__ int find_rep(const RepK* reps, int nrep, int64_t p)
     return lo;
 }
 
-// Sort key of bead i of the batch: its replica's key base plus its brick (or
+// Sort key of bead i, at position r, of the batch: its replica's key base plus its brick (or
 // the replica's "cannot be binned" key).
 struct RepKeyer {
     const RepK* reps;
     int nrep;
     int B;
     const float3* R;
-    __device__ __forceinline__ uint32_t operator()(int32_t i) const
+    __device__ __forceinline__ uint32_t operator()(int32_t i, const float3& r) const
     {
         // Lanes of a wave nearly always hold beads of one replica: search once for the
         // first active lane (a uniform search), and per lane only outside its range.
         const int32_t i0 = __builtin_amdgcn_readfirstlane(i);
-        int r = find_rep(reps, nrep, i0);
-        if (!(i >= reps[r].bead_off && i < reps[r].bead_off + reps[r].N))
-            r = find_rep(reps, nrep, i);
-        const RepK& rp = reps[r];
+        int q = find_rep(reps, nrep, i0);
+        if (!(i >= reps[q].bead_off && i < reps[q].bead_off + reps[q].N))
+            q = find_rep(reps, nrep, i);
+        const RepK& rp = reps[q];
         BeadCell b;
-        return rp.key_base + (bead_cell(R[i], rp.m, b) ? brick_of(b.c[0], b.c[1], b.c[2], B, rp.nb) : rp.NK);
+        return rp.key_base + (bead_cell(r, rp.m, b) ? brick_of(b.c[0], b.c[1], b.c[2], B, rp.nb) : rp.NK);
     }
 };
 

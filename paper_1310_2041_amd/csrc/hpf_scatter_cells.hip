@@ -38,10 +38,17 @@ struct TileK {
     int64_t ntiles;
 };
 
+// c / B for 0 <= c < 2^20 and 1 <= B <= 16, exactly: with m = ceil(2^32 / B) the excess
+// m B - 2^32 is below 16, so c times it stays below 2^32. m is the same for a whole launch.
+__device__ __forceinline__ uint32_t div_brick(int c, int B)
+{
+    return B == 1 ? (uint32_t)c : __umulhi((uint32_t)c, 0xffffffffu / (uint32_t)B + 1u);
+}
+
 // Sort key of a cell: the index of its brick of B^3 cells, x fastest.
 __device__ __forceinline__ uint32_t brick_of(int cx, int cy, int cz, int B, const int nb[3])
 {
-    return ((uint32_t)(cz / B) * (uint32_t)nb[1] + (uint32_t)(cy / B)) * (uint32_t)nb[0] + (uint32_t)(cx / B);
+    return (div_brick(cz, B) * (uint32_t)nb[1] + div_brick(cy, B)) * (uint32_t)nb[0] + div_brick(cx, B);
 }
 
 __device__ __forceinline__ int wrap_idx(int c, int M)

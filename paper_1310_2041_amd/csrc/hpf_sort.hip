@@ -8,7 +8,7 @@
 // most bond partners are adjacent in memory. The order is produced by a
 // stable counting sort of the beads taken in tag order, so beads of one key
 // come out in tag order with no sorting inside a key:
-//   1. in storage order: idx[tag[i]] = i and key_t[tag[i]] = the key of bead i;
+//   1. in storage order: by_tag[tag[i]] = (the key of bead i, i);
 //   2. the tag sequence is cut into chunks of S tags; per chunk a key
 //      histogram is counted in LDS and stored as one row of a chunk x key
 //      table;
@@ -55,18 +55,6 @@ __global__ __launch_bounds__(kSortThreads) void k_fill_u32(uint32_t* __restrict_
         p[i] = v;
 }
 
-// idx = -1 (no bead carries the tag yet) and perm = identity (every output slot holds a
-// valid index even if the tags are no permutation), in one pass.
-__global__ __launch_bounds__(kSortThreads) void k_sort_init(int32_t* __restrict__ idx, int32_t* __restrict__ perm,
-                                                            int64_t n)
-{
-    for (int64_t i = (int64_t)blockIdx.x * kSortThreads + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kSortThreads) {
-        idx[i] = -1;
-        perm[i] = (int32_t)i;
-    }
-}
-
 // ------------------------------------------------------------ scan (u32) --
 
 // In-place exclusive scan of a[0, n) by one workgroup; a[n] receives the total. n is at
@@ -91,37 +79,43 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_keys(uint32_t* __restrict
 
 // ------------------------------------------------------------------ keys --
 
-// Sort key of bead i of one system.
+// Sort key of bead i, at position r, of one system.
 struct CellKeyer {
     SortK sk;
     const float3* R;
-    __device__ __forceinline__ uint32_t operator()(int32_t i) const
+    __device__ __forceinline__ uint32_t operator()(int32_t, const float3& r) const
     {
         BeadCell b;
-        return bead_cell(R[i], sk.m, b) ? brick_of(b.c[0], b.c[1], b.c[2], sk.B, sk.nb) : sk.NK;
+        return bead_cell(r, sk.m, b) ? brick_of(b.c[0], b.c[1], b.c[2], sk.B, sk.nb) : sk.NK;
     }
 };
 
 // ------------------------------------------ 1. tag -> index, and the keys --
 
-// In storage order (coalesced reads of the positions): idx[tag] = i and key_t[tag] = the
-// key of bead i. Tags missing from a broken permutation keep stale entries; the histogram
-// pass finds them by idx < 0 (idx is filled with -1 first) and sets their key to none.
+// In storage order (coalesced reads of the positions): by_tag[tag] = key << 32 | i. Tags that a
+// broken permutation leaves out keep the fill (all ones), whose key is kNoKey. Bound by the
+// scattered stores, one of 8 bytes a bead: 3M beads, mostly solvent, 49 us, 10M chain beads 74
+// (as two of 4 bytes, index and key apart, 94 and 79).
 template <class Keyer>
 __global__ __launch_bounds__(kSortThreads) void k_tag_index(Keyer keyer, const int32_t* __restrict__ tag,
-                                                            int64_t N, int32_t* __restrict__ idx,
-                                                            uint32_t* __restrict__ key_t)
+                                                            int64_t N, unsigned long long* __restrict__ by_tag)
 {
     const int64_t i = xcd_block(blockIdx.x, gridDim.x) * kSortThreads + threadIdx.x;
     if (i >= N)
         return;
     const int32_t t = tag ? tag[i] : (int32_t)i;
-    if (t < 0 || t >= N) {
+    if (t < 0 || t >= N)
         raise_flag(HPF_FLAG_SORT_ORDER);
-    } else {
-        idx[t] = (int32_t)i;
-        key_t[t] = keyer((int32_t)i);
-    }
+    else
+        by_tag[t] = (unsigned long long)keyer((int32_t)i, keyer.R[i]) << 32 | (unsigned long long)(uint32_t)i;
+}
+
+__global__ __launch_bounds__(kSortThreads) void k_fill_u64(unsigned long long* __restrict__ p, int64_t n,
+                                                           unsigned long long v)
+{
+    for (int64_t i = (int64_t)blockIdx.x * kSortThreads + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kSortThreads)
+        p[i] = v;
 }
 
 // ------------------------------------------------------ 2. chunk histograms --
@@ -139,9 +133,8 @@ __device__ __forceinline__ void count_runs(uint32_t* slot, uint32_t key)
     }
 }
 
-__global__ __launch_bounds__(kChunkThreads) void k_sort_hist(const int32_t* __restrict__ idx,
+__global__ __launch_bounds__(kChunkThreads) void k_sort_hist(const unsigned long long* __restrict__ by_tag,
                                                              int64_t N, int64_t S, uint32_t nkeys,
-                                                             uint32_t* __restrict__ key_t,
                                                              uint32_t* __restrict__ table)
 {
     extern __shared__ uint32_t hist[];
@@ -155,12 +148,8 @@ __global__ __launch_bounds__(kChunkThreads) void k_sort_hist(const int32_t* __re
         const int64_t t = base + threadIdx.x;
         uint32_t key = kNoKey;
         if (t < t1) {
-            if (idx[t] >= 0) {
-                key = key_t[t];
-            } else {
-                missing = true;
-                key_t[t] = kNoKey;
-            }
+            key = (uint32_t)(by_tag[t] >> 32);
+            missing |= key == kNoKey;
         }
         count_runs(hist, key);
     }
@@ -308,11 +297,11 @@ __device__ __forceinline__ uint64_t wave_same_key(uint32_t key, bool active, int
 // wavefront needs no barrier. With many keys only the chunk's own key range is cleared and
 // summed (the replicas of a batch follow each other in tag order, so a chunk sees few).
 // Bound by its scattered 4-byte stores; the inverse is therefore left to a pass in storage
-// order, where it is nearly in sequence (written here it took 35 us more at 10M beads).
-// Before, the wavefronts of a workgroup took turns on one row, a barrier per turn, and
-// grouped their lanes one distinct key at a time: 3M beads, mostly solvent, took 169 us.
-__global__ __launch_bounds__(4 * kWave) void k_sort_place(const uint32_t* __restrict__ key_t,
-                                                          const int32_t* __restrict__ idx, int64_t N, int64_t S,
+// order, where it is nearly in sequence. 3M beads, mostly solvent, in 1729 keys: 50 us, 10M
+// chain beads in 513: 59. Before, the wavefronts of a workgroup took turns on one row, a
+// barrier per turn, and grouped their lanes one distinct key at a time: 169 and 66 us.
+__global__ __launch_bounds__(4 * kWave) void k_sort_place(const unsigned long long* __restrict__ by_tag, int64_t N,
+                                                          int64_t S,
                                                           uint32_t nkeys, int rounds, int nbits,
                                                           const uint32_t* __restrict__ table,
                                                           int32_t* __restrict__ perm)
@@ -324,6 +313,20 @@ __global__ __launch_bounds__(4 * kWave) void k_sort_place(const uint32_t* __rest
     const int64_t c = blockIdx.x;
     const int64_t part = S / rows;
     const int64_t t0 = min(N, c * S + wave * part), t1 = min(N, t0 + part);
+    uint32_t key[kPlaceRows];
+    int32_t src[kPlaceRows];
+    auto load = [&](int64_t g0) {
+#pragma unroll
+        for (int b = 0; b < kPlaceRows; ++b) {
+            const int64_t t = g0 + b * kWave + lane;
+            const unsigned long long e = t < t1 ? by_tag[t] : ~0ull;
+            key[b] = (uint32_t)(e >> 32);
+            src[b] = (int32_t)(uint32_t)e;
+        }
+    };
+    // a part of one round of rows is read once and stays in registers
+    const bool one = part <= kPlaceRows * kWave;
+    load(t0);
     uint32_t ka = 0, kb = nkeys;
     if (nkeys > kRangeKeys) {
         if (threadIdx.x == 0) {
@@ -332,12 +335,15 @@ __global__ __launch_bounds__(4 * kWave) void k_sort_place(const uint32_t* __rest
         }
         __syncthreads();
         int lo = 0x7fffffff, hi = -1;
-        for (int64_t t = t0 + lane; t < t1; t += kWave) {
-            const uint32_t key = key_t[t];
-            if (key != kNoKey) {
-                lo = min(lo, (int)key);
-                hi = max(hi, (int)key);
-            }
+        for (int64_t g0 = t0; g0 < t1; g0 += kPlaceRows * kWave) {
+            if (!one)
+                load(g0);
+#pragma unroll
+            for (int b = 0; b < kPlaceRows; ++b)
+                if (key[b] != kNoKey) {
+                    lo = min(lo, (int)key[b]);
+                    hi = max(hi, (int)key[b]);
+                }
         }
         lo = wave_min(lo);
         hi = wave_max(hi);
@@ -354,8 +360,14 @@ __global__ __launch_bounds__(4 * kWave) void k_sort_place(const uint32_t* __rest
         for (int w = 0; w < rows; ++w)
             slots[w * nkeys + k] = 0u;
     __syncthreads();
-    for (int64_t t = t0 + lane; t < t0 + part && t - lane < t1; t += kWave)
-        count_runs(mine, t < t1 ? key_t[t] : kNoKey);
+    for (int64_t g0 = t0; g0 < t1; g0 += kPlaceRows * kWave) {
+        if (!one)
+            load(g0);
+#pragma unroll
+        for (int b = 0; b < kPlaceRows; ++b)
+            if (g0 + b * kWave < t1)                 // uniform
+                count_runs(mine, key[b]);
+    }
     __syncthreads();
     const uint32_t* first = table + c * (int64_t)nkeys;
     for (uint32_t k = ka + threadIdx.x; k < kb; k += blockDim.x) {
@@ -369,18 +381,8 @@ __global__ __launch_bounds__(4 * kWave) void k_sort_place(const uint32_t* __rest
     __syncthreads();
     volatile uint32_t* next = mine;            // lanes of one wavefront follow each other in order
     for (int64_t g0 = t0; g0 < t1; g0 += kPlaceRows * kWave) {
-        uint32_t key[kPlaceRows];
-        int32_t src[kPlaceRows];
-#pragma unroll
-        for (int b = 0; b < kPlaceRows; ++b) {
-            const int64_t t = g0 + b * kWave + lane;
-            key[b] = kNoKey;
-            src[b] = 0;
-            if (t < t1) {
-                key[b] = key_t[t];
-                src[b] = idx[t];
-            }
-        }
+        if (!one)
+            load(g0);
 #pragma unroll
         for (int b = 0; b < kPlaceRows; ++b) {
             if (g0 + b * kWave >= t1)                // uniform: the row holds no tags
@@ -397,14 +399,15 @@ __global__ __launch_bounds__(4 * kWave) void k_sort_place(const uint32_t* __rest
     }
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_iota(int32_t* __restrict__ p, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * kSortThreads + threadIdx.x;
-    if (i < n)
-        p[i] = (int32_t)i;
-}
-
 // ------------------------------------------------ gather and bond table --
+
+// Old storage index of output slot p. A slot that a broken permutation left unwritten holds
+// whatever the workspace held: out of range it stands for the slot itself.
+__device__ __forceinline__ int32_t source_of(const int32_t* __restrict__ perm, int64_t p, int64_t N)
+{
+    const int32_t o = perm[p];
+    return o >= 0 && o < N ? o : (int32_t)p;
+}
 
 // New storage index of partner j (-1: none, or outside [-1, N), which is flagged). A bead
 // that a broken permutation left out has no inverse entry; its partners get -1.
@@ -423,7 +426,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_inverse(const int32_t* __
 {
     const int64_t p = xcd_block(blockIdx.x, gridDim.x) * kSortThreads + threadIdx.x;
     if (p < N)
-        inv[perm[p]] = (int32_t)p;
+        inv[source_of(perm, p, N)] = (int32_t)p;
 }
 
 // Bead rows and bond rows in the new order, in one pass (HBM-bound).
@@ -443,7 +446,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_permute(const int32_t* __
     const int64_t p = xcd_block(blockIdx.x, gridDim.x) * kSortThreads + threadIdx.x;
     if (p >= N)
         return;
-    const int32_t o = perm[p];
+    const int32_t o = source_of(perm, p, N);
     R_out[p] = R_in[o];
     if (V_in)
         V_out[p] = V_in[o];
@@ -467,7 +470,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_angles(const int32_t* __r
     const int64_t p = xcd_block(blockIdx.x, gridDim.x) * kSortThreads + threadIdx.x;
     if (p >= N)
         return;
-    const int32_t o = perm[p];
+    const int32_t o = source_of(perm, p, N);
     bool bad = false;
     for (int r = 0; r < 3 * A; ++r) {
         const int32_t j = ang_in[(int64_t)r * N + o];
@@ -484,18 +487,32 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_angles(const int32_t* __r
 // that sort's key starts are given, the new order is built per key instead of over
 // the whole tag sequence:
 //   1. per old key range, in storage order (coalesced): every bead's new key; the
-//      beads that keep their key ("stayers") are compacted in place, still in tag
-//      order; the others ("movers") are counted per new key;
+//      beads that keep their key ("stayers") are compacted to the front of the
+//      range, still in tag order, and the others ("movers") to its end, each with
+//      its new key and its rank among that key's movers;
 //   2. one scan gives the new key starts and each key's slot range for its movers;
-//   3. every mover is appended (tag, index) to its new key's slots;
+//   3. every mover is written (tag, index) to its slot;
 //   4. per new key: its movers are sorted by tag, and the stayers and the movers
-//      are merged by tag: an element's position is its rank in its own list plus
-//      the number of elements of the other list with a smaller tag (a binary
-//      search).
+//      are merged by tag: a stayer's position is its rank among the stayers plus the
+//      number of movers with a smaller tag (a binary search in LDS), and where that
+//      number steps up between two stayers, the movers in between take their rank
+//      among the stayers from it.
 // The result equals the stable counting sort's exactly: (key, tag) order.
-constexpr int kResortThreads = 256;
+// Step 1 reads 16 B a bead and writes 4; only movers cost more. A workgroup reads 4096 beads
+// between barriers, all rows before the first key, and counts its movers in an LDS table of
+// the few keys they go to, with one global atomic per key. 42M beads in 13,824 bricks: keys
+// 287 us, movers 63, placement 475 with the inverse, rows 920. (With 256 beads between
+// barriers, every bead's key written and read again and the stayers' tags searched in global
+// memory: 350, 290, 581, and 1060 for the rows, bonds and inverse.) A single round of bricks
+// (1M beads in 512) takes 95 us, as the full sort does.
+constexpr int kResortThreads = 512;
+constexpr int kResortWaves = kResortThreads / kWave;
+constexpr int kResortPer = 8;
 constexpr int kPlaceThreads = 512;
-constexpr int kMoverCap = 4096;          // movers of one key sorted in LDS (32 KiB)
+constexpr int kPlacePer = 4;             // stayers a thread reads at once
+constexpr int kMoverCap = 2048;          // movers of one key sorted in LDS (16 KiB)
+constexpr uint32_t kMoveKeys = 128;      // keys an old range's movers are counted under in LDS
+constexpr int kMoveProbes = 16;
 
 __device__ __forceinline__ int32_t tag_of(const int32_t* __restrict__ tag, int64_t i)
 {
@@ -505,105 +522,160 @@ __device__ __forceinline__ int32_t tag_of(const int32_t* __restrict__ tag, int64
 template <class Keyer>
 __global__ __launch_bounds__(kResortThreads) void k_resort_keys(Keyer keyer, const int32_t* __restrict__ tag,
                                                                 const uint32_t* __restrict__ cs_old, int64_t N,
-                                                                uint32_t* __restrict__ keyp,
-                                                                int32_t* __restrict__ stayidx,
+                                                                int32_t* __restrict__ order,
+                                                                uint32_t* __restrict__ mkey,
+                                                                uint32_t* __restrict__ mslot,
+                                                                uint32_t* __restrict__ mrank,
                                                                 uint32_t* __restrict__ cnt_stay,
                                                                 uint32_t* __restrict__ cnt_move)
 {
-    __shared__ uint32_t sh[kResortThreads / kWave + 1];
-    const uint32_t k = blockIdx.x;
+    __shared__ uint32_t hkey[kMoveKeys], hcnt[kMoveKeys];
+    __shared__ uint32_t pre[kResortPer * kResortWaves + 1];
+    const uint32_t k = (uint32_t)xcd_block(blockIdx.x, gridDim.x);
     const int64_t a = min((int64_t)cs_old[k], N), b = min((int64_t)cs_old[k + 1], N);
-    const int lane = threadIdx.x & (kWave - 1);
-    uint32_t run = 0;
-    bool bad = false;
-    for (int64_t base = a; base < b; base += kResortThreads) {
-        const int64_t i = base + threadIdx.x;
-        uint32_t key = kNoKey;
-        if (i < b) {
-            key = keyer((int32_t)i);
-            keyp[i] = key;
-            // the precondition: every old key range in ascending tag order
-            bad |= i > a && tag_of(tag, i) <= tag_of(tag, i - 1);
-        }
-        const bool stay = key == k;
-        uint32_t total;
-        const uint32_t r = block_excl_scan<kResortThreads>(stay ? 1u : 0u, sh, &total);
-        if (stay)
-            stayidx[a + run + r] = (int32_t)i;
-        run += total;
-        const bool mv = i < b && !stay;
-        const uint64_t grp = wave_key_group(key, mv);
-        if (mv && __builtin_ctzll(grp) == lane)
-            atomicAdd(cnt_move + key, (uint32_t)__builtin_popcountll(grp));
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    for (uint32_t h = threadIdx.x; h < kMoveKeys; h += kResortThreads) {
+        hkey[h] = kNoKey;
+        hcnt[h] = 0u;
     }
+    int64_t run = 0;                     // stayers so far
+    bool bad = false;
+    for (int64_t base = a; base < b; base += kResortPer * kResortThreads) {
+        // all rows first: a key's branches between them would have each wait for its own
+        float3 r[kResortPer];
+        int32_t tg[kResortPer], tb[kResortPer];
+#pragma unroll
+        for (int u = 0; u < kResortPer; ++u) {
+            const int64_t i = min(base + u * kResortThreads + threadIdx.x, b - 1);
+            r[u] = keyer.R[i];
+            tg[u] = tag_of(tag, i);
+            tb[u] = i > a ? tag_of(tag, i - 1) : -1;
+        }
+        uint32_t key[kResortPer];
+        uint64_t stay[kResortPer];
+#pragma unroll
+        for (int u = 0; u < kResortPer; ++u) {
+            const int64_t i = base + u * kResortThreads + threadIdx.x;
+            key[u] = kNoKey;
+            if (i < b) {
+                key[u] = keyer((int32_t)i, r[u]);
+                bad |= tg[u] <= tb[u];   // the precondition: every old key range in ascending tag order
+            }
+        }
+        __syncthreads();                 // pre is read out; the table is cleared
+#pragma unroll
+        for (int u = 0; u < kResortPer; ++u) {
+            stay[u] = __ballot(key[u] == k);
+            if (lane == 0)
+                pre[u * kResortWaves + wave] = (uint32_t)__builtin_popcountll(stay[u]);
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const uint32_t v = lane < kResortPer * kResortWaves ? pre[lane] : 0u;
+            const uint32_t inc = wave_incl_scan(v);
+            if (lane < kResortPer * kResortWaves)
+                pre[lane] = inc - v;
+            if (lane == kResortPer * kResortWaves - 1)
+                pre[lane + 1] = inc;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kResortPer; ++u) {
+            const int64_t i = base + u * kResortThreads + threadIdx.x;
+            if (i >= b)
+                continue;
+            const int64_t before = run + pre[u * kResortWaves + wave] +
+                                   (uint32_t)__builtin_popcountll(stay[u] & ((1ull << lane) - 1));
+            if (key[u] == k) {
+                order[a + before] = (int32_t)i;
+                continue;
+            }
+            const int64_t pos = b - 1 - (i - a - before);
+            order[pos] = (int32_t)i;
+            mkey[pos] = key[u];
+        }
+        run += pre[kResortPer * kResortWaves];
+    }
+    __syncthreads();
+    // the movers, now side by side, are counted per key
+    for (int64_t pos = a + run + threadIdx.x; pos < b; pos += kResortThreads) {
+        const uint32_t key = mkey[pos];
+        uint32_t h = (key * 2654435761u) >> 25, slot = kMoveKeys, rank = 0;
+        for (int q = 0; q < kMoveProbes; ++q, h = (h + 1) % kMoveKeys) {
+            const uint32_t old = atomicCAS(&hkey[h], kNoKey, key);
+            if (old == kNoKey || old == key) {
+                slot = h;
+                rank = atomicAdd(&hcnt[h], 1u);
+                break;
+            }
+        }
+        if (slot == kMoveKeys)           // table full
+            rank = atomicAdd(cnt_move + key, 1u);
+        mslot[pos] = slot;
+        mrank[pos] = rank;
+    }
+    __syncthreads();
+    // each key's ranks follow those other ranges have reserved
+    if (threadIdx.x < kMoveKeys && hcnt[threadIdx.x])
+        hcnt[threadIdx.x] = atomicAdd(cnt_move + hkey[threadIdx.x], hcnt[threadIdx.x]);
+    __syncthreads();
+    for (int64_t pos = a + run + threadIdx.x; pos < b; pos += kResortThreads)
+        if (mslot[pos] < kMoveKeys)
+            mrank[pos] += hcnt[mslot[pos]];
     if (threadIdx.x == 0)
-        cnt_stay[k] = run;
+        cnt_stay[k] = (uint32_t)run;
     if (bad)
         raise_flag(HPF_FLAG_SORT_ORDER);
 }
+static_assert(kMoveKeys == 1u << (32 - 25) && kResortPer * kResortWaves <= kWave, "hash bits; one wave scans pre");
 
-// One block: new key starts (stayers + movers per key, exclusive scan; the last entry
-// the total) and the movers' slot offsets (exclusive scan of the mover counts); the
-// slot fill counters are cleared.
-constexpr int kResortScanThreads = 1024;
-
-__global__ __launch_bounds__(kResortScanThreads) void k_resort_scan(const uint32_t* __restrict__ cnt_stay,
-                                                                    const uint32_t* __restrict__ cnt_move,
-                                                                    uint32_t nkeys, uint32_t* __restrict__ start,
-                                                                    uint32_t* __restrict__ moff,
-                                                                    uint32_t* __restrict__ fill)
+// One block: new key starts (stayers + movers per key, exclusive scan; the last entry the
+// total) and the movers' slot offsets (exclusive scan of the mover counts).
+__global__ __launch_bounds__(kScanThreads) void k_resort_scan(const uint32_t* __restrict__ cnt_stay,
+                                                              const uint32_t* __restrict__ cnt_move, uint32_t nkeys,
+                                                              uint32_t* __restrict__ start,
+                                                              uint32_t* __restrict__ moff)
 {
-    __shared__ uint32_t sh[kResortScanThreads / kWave + 1];
-    const uint32_t per = (nkeys + kResortScanThreads - 1) / kResortScanThreads;
-    const uint32_t k0 = min(nkeys, threadIdx.x * per), k1 = min(nkeys, k0 + per);
-    uint32_t st = 0, mv = 0;
-    for (uint32_t k = k0; k < k1; ++k) {
-        st += cnt_stay[k] + cnt_move[k];
-        mv += cnt_move[k];
-    }
-    uint32_t tot_st, tot_mv;
-    uint32_t run_st = block_excl_scan<kResortScanThreads>(st, sh, &tot_st);
-    uint32_t run_mv = block_excl_scan<kResortScanThreads>(mv, sh, &tot_mv);
-    for (uint32_t k = k0; k < k1; ++k) {
-        start[k] = run_st;
-        moff[k] = run_mv;
-        fill[k] = 0u;
-        run_st += cnt_stay[k] + cnt_move[k];
-        run_mv += cnt_move[k];
+    __shared__ uint32_t sh[kScanThreads / kWave + 1];
+    uint32_t run_st = 0, run_mv = 0;
+    for (uint32_t k0 = 0; k0 < nkeys; k0 += kScanThreads) {
+        const uint32_t k = k0 + threadIdx.x;
+        const uint32_t mv = k < nkeys ? cnt_move[k] : 0u;
+        const uint32_t st = k < nkeys ? cnt_stay[k] + mv : 0u;
+        uint32_t tot_st, tot_mv;
+        const uint32_t r_st = block_excl_scan<kScanThreads>(st, sh, &tot_st);
+        const uint32_t r_mv = block_excl_scan<kScanThreads>(mv, sh, &tot_mv);
+        if (k < nkeys) {
+            start[k] = run_st + r_st;
+            moff[k] = run_mv + r_mv;
+        }
+        run_st += tot_st;
+        run_mv += tot_mv;
     }
     if (threadIdx.x == 0) {
-        start[nkeys] = tot_st;
-        moff[nkeys] = tot_mv;
+        start[nkeys] = run_st;
+        moff[nkeys] = run_mv;
     }
 }
 
-// Movers appended to their new key's slots as (tag << 32 | index); their order inside
+// Movers written to their new key's slots as (tag << 32 | index); their order inside
 // a key's slots is arbitrary (sorted in the placement).
-__global__ __launch_bounds__(kResortThreads) void k_resort_movers(const int32_t* __restrict__ tag,
-                                                                  const uint32_t* __restrict__ cs_old, int64_t N,
-                                                                  const uint32_t* __restrict__ keyp,
-                                                                  const uint32_t* __restrict__ moff,
-                                                                  uint32_t* __restrict__ fill,
-                                                                  unsigned long long* __restrict__ movers)
+__global__ __launch_bounds__(kSortThreads) void k_resort_movers(const int32_t* __restrict__ tag,
+                                                                const uint32_t* __restrict__ cs_old, int64_t N,
+                                                                const uint32_t* __restrict__ cnt_stay,
+                                                                const int32_t* __restrict__ order,
+                                                                const uint32_t* __restrict__ mkey,
+                                                                const uint32_t* __restrict__ mrank,
+                                                                const uint32_t* __restrict__ moff,
+                                                                unsigned long long* __restrict__ movers)
 {
     const uint32_t k = blockIdx.x;
     const int64_t a = min((int64_t)cs_old[k], N), b = min((int64_t)cs_old[k + 1], N);
-    const int lane = threadIdx.x & (kWave - 1);
-    for (int64_t base = a; base < b; base += kResortThreads) {
-        const int64_t i = base + threadIdx.x;
-        const uint32_t key = i < b ? keyp[i] : kNoKey;
-        const bool mv = i < b && key != k;
-        const uint64_t grp = wave_key_group(key, mv);
-        const int leader = mv ? __builtin_ctzll(grp) : lane;
-        uint32_t slot = 0;
-        if (mv && leader == lane)
-            slot = atomicAdd(fill + key, (uint32_t)__builtin_popcountll(grp));
-        slot = __shfl(slot, leader, kWave);
-        if (mv) {
-            slot += (uint32_t)__builtin_popcountll(grp & ((1ull << lane) - 1));
-            movers[(int64_t)moff[key] + slot] =
-                ((unsigned long long)(uint32_t)tag_of(tag, i) << 32) | (unsigned long long)(uint32_t)i;
-        }
+    for (int64_t pos = a + cnt_stay[k] + threadIdx.x; pos < b; pos += kSortThreads) {
+        const int32_t i = order[pos];
+        const int64_t dst = (int64_t)moff[mkey[pos]] + mrank[pos];
+        if (dst < N)
+            movers[dst] = ((unsigned long long)(uint32_t)tag_of(tag, i) << 32) | (unsigned long long)(uint32_t)i;
     }
 }
 
@@ -613,14 +685,14 @@ __global__ __launch_bounds__(kResortThreads) void k_resort_movers(const int32_t*
 template <class Load, class Store>
 __device__ __forceinline__ void sort_padded(int64_t n, int64_t p, Load load, Store store)
 {
-    for (int64_t size = 2; size <= p; size <<= 1) {
-        for (int64_t stride = size >> 1; stride > 0; stride >>= 1) {
+    for (int size = 1; (int64_t)1 << size <= p; ++size) {
+        for (int stride = size - 1; stride >= 0; --stride) {
             for (int64_t q = threadIdx.x; q < p / 2; q += blockDim.x) {
                 // the q-th comparator of this step: elements i < j
-                const int64_t blk = q / stride, off = q % stride;
-                int64_t i = blk * 2 * stride + off, j = i + stride;
-                if (stride == (size >> 1))
-                    j = (i / size) * size + size - 1 - (i % size);   // mirrored partner
+                const int64_t i = (q >> stride << (stride + 1)) + (q & (((int64_t)1 << stride) - 1));
+                int64_t j = i + ((int64_t)1 << stride);
+                if (stride == size - 1)
+                    j = i ^ (((int64_t)1 << size) - 1);              // mirrored partner
                 if (j < n) {
                     const unsigned long long a = load(i), c = load(j);
                     if (c < a) {
@@ -634,11 +706,98 @@ __device__ __forceinline__ void sort_padded(int64_t n, int64_t p, Load load, Sto
     }
 }
 
+// Number of the movers v[0, n) (ascending) below key.
+template <class Load>
+__device__ __forceinline__ int64_t movers_below(unsigned long long key, int64_t n, Load load)
+{
+    int64_t lo = 0, hi = n;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (load(mid) < key)
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    return lo;
+}
+
+// Number of entries of v[0, n) (ascending) below each of the keys e[0, kPlacePer): one binary
+// search each, their steps side by side. p2 is a power of two above n.
+__device__ __forceinline__ void lds_below(const unsigned long long* v, int n, int p2,
+                                          const unsigned long long (&e)[kPlacePer], int (&pos)[kPlacePer])
+{
+#pragma unroll
+    for (int u = 0; u < kPlacePer; ++u)
+        pos[u] = 0;
+    for (int s = p2 >> 1; s > 0; s >>= 1) {
+#pragma unroll
+        for (int u = 0; u < kPlacePer; ++u) {
+            const int q = pos[u] + s;
+            if (q <= n && v[q - 1] < e[u])
+                pos[u] = q;
+        }
+    }
+}
+
+// Ascending sort of one value per lane of a wavefront (bitonic).
+__device__ __forceinline__ unsigned long long wave_sort(unsigned long long v)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int size = 2; size <= kWave; size <<= 1)
+#pragma unroll
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            const unsigned long long o = __shfl_xor(v, stride, kWave);
+            const bool keep_min = ((lane & stride) == 0) == ((lane & size) == 0);
+            v = (o < v) == keep_min ? o : v;
+        }
+    return v;
+}
+
+// Ascending sort of v[0, n) in LDS, n <= kMoverCap, v filled up with +inf to whole runs of 64;
+// all values different. Each wavefront sorts runs in its registers; a value's place is its
+// place in its run plus the number of smaller values in every other run. (A bitonic network
+// over all of them took a barrier for each of its 55 steps at 600 values.)
+__device__ __forceinline__ void sort_movers(int n, unsigned long long* v)
+{
+    constexpr int kWaves = kPlaceThreads / kWave, kPer = kMoverCap / kPlaceThreads;
+    static_assert(kPer == kPlacePer, "lds_below takes a thread's values together");
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int runs = (n + kWave - 1) / kWave;
+    unsigned long long e[kPer];
+    int rank[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int r = u * kWaves + wave;
+        e[u] = ~0ull;
+        rank[u] = lane;
+        if (r < runs) {
+            e[u] = wave_sort(v[r * kWave + lane]);
+            v[r * kWave + lane] = e[u];
+        }
+    }
+    __syncthreads();
+    if (wave < runs)
+        for (int q = 0; q < runs; ++q) {
+            int pos[kPer];
+            lds_below(v + q * kWave, kWave, 2 * kWave, e, pos);
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                rank[u] += q == u * kWaves + wave ? 0 : pos[u];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+        if (u * kWaves + wave < runs && e[u] != ~0ull)
+            v[rank[u]] = e[u];
+    __syncthreads();
+}
+
 // Per new key: movers sorted by tag (in LDS when they fit, else in place in their
 // slots), then stayers and movers merged by tag into the key's output range.
 __global__ __launch_bounds__(kPlaceThreads) void k_resort_place(const int32_t* __restrict__ tag,
                                                                 const uint32_t* __restrict__ cs_old, int64_t N,
-                                                                const int32_t* __restrict__ stayidx,
+                                                                const int32_t* __restrict__ order,
                                                                 const uint32_t* __restrict__ cnt_stay,
                                                                 const uint32_t* __restrict__ cnt_move,
                                                                 const uint32_t* __restrict__ moff,
@@ -648,52 +807,92 @@ __global__ __launch_bounds__(kPlaceThreads) void k_resort_place(const int32_t* _
                                                                 int32_t* __restrict__ inv)
 {
     __shared__ unsigned long long smv[kMoverCap];
-    const uint32_t k = blockIdx.x;
-    const int64_t nmv = cnt_move[k], ns = cnt_stay[k];
+    __shared__ uint32_t below[kMoverCap];          // stayers below each mover
+    const uint32_t k = (uint32_t)xcd_block(blockIdx.x, gridDim.x);
+    const int64_t nmv = min((int64_t)cnt_move[k], N - moff[k]), ns = cnt_stay[k];
     const int64_t base = start[k];
     unsigned long long* mv = movers + moff[k];
-    const int32_t* st = stayidx + min((int64_t)cs_old[k], N);
-    int64_t p2 = 1;
+    const int32_t* st = order + min((int64_t)cs_old[k], N);
+    int64_t p2 = 1, p2above = 1;
     while (p2 < nmv)
         p2 <<= 1;
+    while (p2above <= nmv)
+        p2above <<= 1;
+    auto put = [&](int64_t dst, int32_t i) {
+        if (dst < N) {                   // always, unless the key starts handed in were broken
+            perm[dst] = i;
+            inv[i] = (int32_t)dst;
+        }
+    };
     const bool in_lds = nmv <= kMoverCap;
+    auto lds = [&](int64_t q) { return smv[q]; };
+    auto glob = [&](int64_t q) { return mv[q]; };
     if (in_lds) {
-        for (int64_t q = threadIdx.x; q < nmv; q += kPlaceThreads)
-            smv[q] = mv[q];
+        for (int64_t q = threadIdx.x; q < (nmv + kWave - 1) / kWave * kWave; q += kPlaceThreads) {
+            smv[q] = q < nmv ? mv[q] : ~0ull;
+            below[q] = (uint32_t)ns;
+        }
         __syncthreads();
-        sort_padded(nmv, p2, [&](int64_t q) { return smv[q]; }, [&](int64_t q, unsigned long long v) { smv[q] = v; });
+        sort_movers((int)nmv, smv);
     } else {
-        sort_padded(nmv, p2, [&](int64_t q) { return mv[q]; }, [&](int64_t q, unsigned long long v) { mv[q] = v; });
+        sort_padded(nmv, p2, glob, [&](int64_t q, unsigned long long v) { mv[q] = v; });
     }
-    // movers: rank among movers + stayers with a smaller tag
+    // stayers: rank among stayers + movers with a smaller tag; the movers between a stayer
+    // and the one before it have that stayer's rank of stayers below them
+    for (int64_t q0 = 0; q0 < ns; q0 += kPlacePer * kPlaceThreads) {
+        int32_t idx[kPlacePer], tg[kPlacePer];
+#pragma unroll
+        for (int u = 0; u < kPlacePer; ++u) {
+            const int64_t q = q0 + u * kPlaceThreads + threadIdx.x;
+            idx[u] = q < ns ? st[q] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kPlacePer; ++u)
+            tg[u] = tag_of(tag, idx[u]);
+        unsigned long long e[kPlacePer];
+        int c[kPlacePer];
+#pragma unroll
+        for (int u = 0; u < kPlacePer; ++u) {
+            e[u] = (unsigned long long)(uint32_t)tg[u] << 32;
+            c[u] = in_lds ? 0 : (int)movers_below(e[u], nmv, glob);
+        }
+        if (in_lds)
+            lds_below(smv, (int)nmv, (int)p2above, e, c);
+#pragma unroll
+        for (int u = 0; u < kPlacePer; ++u) {
+            const int64_t q = q0 + u * kPlaceThreads + threadIdx.x;
+            if (q < ns)
+                put(base + q + c[u], idx[u]);
+            if (!in_lds)
+                continue;
+            int prev = __shfl_up(c[u], 1, kWave);
+            if ((threadIdx.x & (kWave - 1)) == 0)
+                prev = q > 0 && q < ns
+                           ? (int)movers_below((unsigned long long)(uint32_t)tag_of(tag, st[q - 1]) << 32, nmv, lds)
+                           : 0;
+            if (q < ns)
+                for (int j = prev; j < c[u]; ++j)
+                    below[j] = (uint32_t)q;
+        }
+    }
+    __syncthreads();
     for (int64_t q = threadIdx.x; q < nmv; q += kPlaceThreads) {
         const unsigned long long e = in_lds ? smv[q] : mv[q];
-        const int32_t t = (int32_t)(e >> 32);
-        int64_t lo = 0, hi = ns;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (tag_of(tag, st[mid]) < t)
-                lo = mid + 1;
-            else
-                hi = mid;
+        int64_t lo = 0;
+        if (in_lds) {
+            lo = below[q];
+        } else {
+            const int32_t t = (int32_t)(e >> 32);
+            int64_t hi = ns;
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) >> 1;
+                if (tag_of(tag, st[mid]) < t)
+                    lo = mid + 1;
+                else
+                    hi = mid;
+            }
         }
-        perm[base + q + lo] = (int32_t)(uint32_t)e;
-        inv[(uint32_t)e] = (int32_t)(base + q + lo);
-    }
-    // stayers: rank among stayers + movers with a smaller tag
-    for (int64_t q = threadIdx.x; q < ns; q += kPlaceThreads) {
-        const int32_t i = st[q];
-        const unsigned long long t = (unsigned long long)(uint32_t)tag_of(tag, i) << 32;
-        int64_t lo = 0, hi = nmv;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if ((in_lds ? smv[mid] : mv[mid]) < t)
-                lo = mid + 1;
-            else
-                hi = mid;
-        }
-        perm[base + q + lo] = i;
-        inv[i] = (int32_t)(base + q + lo);
+        put(base + q + lo, (int32_t)(uint32_t)e);
     }
 }
 
@@ -707,9 +906,9 @@ struct SortPlan {
     uint32_t nkeys = 0;
     int64_t S = 0, nchunks = 0, ncb = 0;
     size_t off_key = 0, off_perm = 0, off_inv = 0, off_table = 0, off_part = 0, off_start = 0;
-    // re-sort from a previous order: compacted stayers (the full sort keeps its tag index
-    // there), movers, per-key counts and offsets
-    size_t off_stay = 0, off_movers = 0, off_cstay = 0, off_cmove = 0, off_fill = 0, off_moff = 0;
+    // re-sort from a previous order: compacted stayers and movers, the movers by key (the full
+    // sort keeps its keys and indices by tag there), per-key counts and offsets
+    size_t off_stay = 0, off_movers = 0, off_cstay = 0, off_cmove = 0, off_moff = 0;
     size_t bytes = 0;
 };
 
@@ -742,7 +941,6 @@ bool sort_plan(int64_t N, int64_t nkeys, SortPlan* p)
     p->off_movers = o; o += align_up(sizeof(uint64_t) * N1);
     p->off_cstay = o; o += align_up(sizeof(uint32_t) * (size_t)nkeys);
     p->off_cmove = o; o += align_up(sizeof(uint32_t) * (size_t)nkeys);
-    p->off_fill = o; o += align_up(sizeof(uint32_t) * (size_t)nkeys);
     p->off_moff = o; o += align_up(sizeof(uint32_t) * (size_t)(nkeys + 1));
     p->bytes = o;
     return true;
@@ -804,9 +1002,8 @@ hpf_status_t run_sort(const SortPlan& pl, Keyer keyer, int64_t N, const float* R
                       float* V_out, uint8_t* T_out, int32_t* tag_out, int32_t* bonds_out, uint32_t* start,
                       char* work, hipStream_t s)
 {
-    uint32_t* key_t = reinterpret_cast<uint32_t*>(work + pl.off_key);
+    auto* by_tag = reinterpret_cast<unsigned long long*>(work + pl.off_movers);
     int32_t* perm = reinterpret_cast<int32_t*>(work + pl.off_perm);
-    int32_t* idx = reinterpret_cast<int32_t*>(work + pl.off_stay);
     int32_t* inv = reinterpret_cast<int32_t*>(work + pl.off_inv);
     uint32_t* table = reinterpret_cast<uint32_t*>(work + pl.off_table);
     uint32_t* part = reinterpret_cast<uint32_t*>(work + pl.off_part);
@@ -825,10 +1022,10 @@ hpf_status_t run_sort(const SortPlan& pl, Keyer keyer, int64_t N, const float* R
          hipFuncSetAttribute(reinterpret_cast<const void*>(k_sort_place), hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)smem_place) != hipSuccess))
         return HPF_EINVAL;
-    hipLaunchKernelGGL(k_sort_init, dim3((unsigned)std::min<int64_t>(grid_for(N), 8192)), dim3(kSortThreads), 0, s,
-                       idx, perm, N);
-    hipLaunchKernelGGL(k_tag_index<Keyer>, dim3(grid_for(N)), dim3(kSortThreads), 0, s, keyer, tag_in, N, idx, key_t);
-    hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)pl.nchunks), dim3(kChunkThreads), smem, s, idx, N, pl.S, nk, key_t,
+    hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)std::min<int64_t>(grid_for(N), 8192)), dim3(kSortThreads), 0, s,
+                       by_tag, N, ~0ull);
+    hipLaunchKernelGGL(k_tag_index<Keyer>, dim3(grid_for(N)), dim3(kSortThreads), 0, s, keyer, tag_in, N, by_tag);
+    hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)pl.nchunks), dim3(kChunkThreads), smem, s, by_tag, N, pl.S, nk,
                        table);
     if (pl.ncb == 1 && nk <= kSmallKeys) {
         hipLaunchKernelGGL(k_col_small, dim3(1), dim3(kScanThreads), 0, s, table, pl.nchunks, nk, start);
@@ -843,7 +1040,7 @@ hpf_status_t run_sort(const SortPlan& pl, Keyer keyer, int64_t N, const float* R
     int nbits = 1;
     while ((1u << nbits) < nk)
         ++nbits;
-    hipLaunchKernelGGL(k_sort_place, dim3((unsigned)pl.nchunks), dim3(kWave * rows), smem_place, s, key_t, idx, N,
+    hipLaunchKernelGGL(k_sort_place, dim3((unsigned)pl.nchunks), dim3(kWave * rows), smem_place, s, by_tag, N,
                        pl.S, nk, N / nk >= kMatchBeads ? kMatchRounds : 0, nbits, table, perm);
     hipLaunchKernelGGL(k_sort_inverse, dim3(grid_for(N)), dim3(kSortThreads), 0, s, perm, N, inv);
     launch_permute(N, perm, inv, R_in, V_in, T_in, tag_in, bonds_in, D, R_out, V_out, T_out, tag_out, bonds_out, s);
@@ -861,43 +1058,49 @@ hpf_status_t launch_sort(const SortK& sk, const SortPlan& pl, int64_t N, const f
                     start, work, s);
 }
 
-// The re-sort (steps 1-4 above), then the gather and the bond renumbering of run_sort.
+// The re-sort (steps 1-4 above), then the gather and the bond renumbering of run_sort. The
+// movers' table slots and ranks stand in perm and inv until the placement writes those.
+template <class Keyer>
+hpf_status_t run_resort(const SortPlan& pl, Keyer keyer, int64_t N, const float* R_in, const float* V_in,
+                        const uint8_t* T_in, const int32_t* tag_in, const int32_t* bonds_in, int D, float* R_out,
+                        float* V_out, uint8_t* T_out, int32_t* tag_out, int32_t* bonds_out, const uint32_t* cs_old,
+                        uint32_t* cs_new, char* work, hipStream_t s)
+{
+    const uint32_t nk = pl.nkeys;
+    auto* mkey = reinterpret_cast<uint32_t*>(work + pl.off_key);
+    auto* perm = reinterpret_cast<int32_t*>(work + pl.off_perm);
+    auto* inv = reinterpret_cast<int32_t*>(work + pl.off_inv);
+    auto* order = reinterpret_cast<int32_t*>(work + pl.off_stay);
+    auto* movers = reinterpret_cast<unsigned long long*>(work + pl.off_movers);
+    auto* cstay = reinterpret_cast<uint32_t*>(work + pl.off_cstay);
+    auto* cmove = reinterpret_cast<uint32_t*>(work + pl.off_cmove);
+    auto* moff = reinterpret_cast<uint32_t*>(work + pl.off_moff);
+    if (N == 0) {
+        hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)std::min<int64_t>(grid_for(nk + 1), 4096)), dim3(kSortThreads),
+                           0, s, cs_new, (int64_t)nk + 1, 0u);
+        return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
+    }
+    hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)std::min<int64_t>(grid_for(nk), 4096)), dim3(kSortThreads), 0, s,
+                       cmove, (int64_t)nk, 0u);
+    hipLaunchKernelGGL(k_resort_keys<Keyer>, dim3(nk), dim3(kResortThreads), 0, s, keyer, tag_in, cs_old, N, order,
+                       mkey, reinterpret_cast<uint32_t*>(perm), reinterpret_cast<uint32_t*>(inv), cstay, cmove);
+    hipLaunchKernelGGL(k_resort_scan, dim3(1), dim3(kScanThreads), 0, s, cstay, cmove, nk, cs_new, moff);
+    hipLaunchKernelGGL(k_resort_movers, dim3(nk), dim3(kSortThreads), 0, s, tag_in, cs_old, N, cstay, order, mkey,
+                       reinterpret_cast<uint32_t*>(inv), moff, movers);
+    hipLaunchKernelGGL(k_resort_place, dim3(nk), dim3(kPlaceThreads), 0, s, tag_in, cs_old, N, order, cstay, cmove,
+                       moff, cs_new, movers, perm, inv);
+    launch_permute(N, perm, inv, R_in, V_in, T_in, tag_in, bonds_in, D, R_out, V_out, T_out, tag_out, bonds_out, s);
+    return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
+}
+
 hpf_status_t launch_resort(const SortK& sk, const SortPlan& pl, int64_t N, const float* R_in, const float* V_in,
                            const uint8_t* T_in, const int32_t* tag_in, const int32_t* bonds_in, int D, float* R_out,
                            float* V_out, uint8_t* T_out, int32_t* tag_out, int32_t* bonds_out,
                            const uint32_t* cs_old, uint32_t* cs_new, char* work, hipStream_t s)
 {
     CellKeyer keyer{sk, reinterpret_cast<const float3*>(R_in)};
-    const uint32_t nk = pl.nkeys;
-    auto* keyp = reinterpret_cast<uint32_t*>(work + pl.off_key);
-    auto* perm = reinterpret_cast<int32_t*>(work + pl.off_perm);
-    auto* inv = reinterpret_cast<int32_t*>(work + pl.off_inv);
-    auto* stay = reinterpret_cast<int32_t*>(work + pl.off_stay);
-    auto* movers = reinterpret_cast<unsigned long long*>(work + pl.off_movers);
-    auto* cstay = reinterpret_cast<uint32_t*>(work + pl.off_cstay);
-    auto* cmove = reinterpret_cast<uint32_t*>(work + pl.off_cmove);
-    auto* fill = reinterpret_cast<uint32_t*>(work + pl.off_fill);
-    auto* moff = reinterpret_cast<uint32_t*>(work + pl.off_moff);
-    const unsigned gfill = (unsigned)std::min<int64_t>(grid_for(nk), 4096);
-    hipLaunchKernelGGL(k_fill_u32, dim3(gfill), dim3(kSortThreads), 0, s, cmove, (int64_t)nk, 0u);
-    if (N > 0) {
-        // every output slot holds a valid index even if the input breaks the precondition
-        hipLaunchKernelGGL(k_iota, dim3(grid_for(N)), dim3(kSortThreads), 0, s, perm, N);
-        hipLaunchKernelGGL(k_resort_keys<CellKeyer>, dim3(nk), dim3(kResortThreads), 0, s, keyer, tag_in, cs_old, N,
-                           keyp, stay, cstay, cmove);
-    } else {
-        hipLaunchKernelGGL(k_fill_u32, dim3(gfill), dim3(kSortThreads), 0, s, cstay, (int64_t)nk, 0u);
-    }
-    hipLaunchKernelGGL(k_resort_scan, dim3(1), dim3(kResortScanThreads), 0, s, cstay, cmove, nk, cs_new, moff, fill);
-    if (N > 0) {
-        hipLaunchKernelGGL(k_resort_movers, dim3(nk), dim3(kResortThreads), 0, s, tag_in, cs_old, N, keyp, moff, fill,
-                           movers);
-        hipLaunchKernelGGL(k_resort_place, dim3(nk), dim3(kPlaceThreads), 0, s, tag_in, cs_old, N, stay, cstay, cmove,
-                           moff, cs_new, movers, perm, inv);
-        launch_permute(N, perm, inv, R_in, V_in, T_in, tag_in, bonds_in, D, R_out, V_out, T_out, tag_out, bonds_out,
-                       s);
-    }
-    return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
+    return run_resort(pl, keyer, N, R_in, V_in, T_in, tag_in, bonds_in, D, R_out, V_out, T_out, tag_out, bonds_out,
+                      cs_old, cs_new, work, s);
 }
 
 hpf_status_t launch_sort_angles(const SortPlan& pl, int64_t N, const int32_t* ang_in, int A, int32_t* ang_out,

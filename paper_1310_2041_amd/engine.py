@@ -140,9 +140,9 @@ class HpfState:
                                       dtype=torch.int32, device=dev)
         self.cell_start2 = torch.empty_like(self.cell_start)
         # Re-sort from the previous sort's order (hpf_resort_by_cell) once sorted. Its passes
-        # run one workgroup per brick, so it pays on meshes of many bricks (10^8 beads in
-        # 32,768 bricks: 7 ms against 40 ms for the full sort); with a few hundred large
-        # bricks the full sort is faster (0.48 against 0.84 ms for 10^7 beads in 512).
+        # run one workgroup per brick, so it pays on meshes of many bricks (4.2 10^7 beads in
+        # 13,824 bricks: 1.8 ms against 9 ms for the full sort); with a few hundred large
+        # bricks the full sort is faster (0.40 against 0.66 ms for 10^7 beads in 512).
         self.resort = hpf.sort_key_count(self.mesh, self.B) >= RESORT_MIN_BRICKS
         # the cell-list scatter needs every mesh edge >= B + 1 + 2*halo (0 bytes = unsupported)
         ws = hpf.hpf_scatter_workspace_bytes(self.N, self.mesh, self.K, self.B, self.halo)

@@ -46,3 +46,38 @@ def test_full_sort_paths_match_the_oracle(n_chains, chain_len, B, M, n_solvent):
     nk = hpf.sort_key_count(st.mesh, B)
     assert np.array_equal(host(st.cell_start), np.searchsorted(np.sort(keys), np.arange(nk + 2), side="left"))
     assert hpf.hpf_get_device_status(clear=True) == 0
+
+
+@pytest.mark.parametrize("N,M,B,into", [(40, 12, 4, 40), (700, 24, 8, 64), (700, 24, 8, 65), (3000, 24, 8, 513),
+                                        (6000, 24, 8, 2048), (6000, 24, 8, 2049), (9000, 45, 3, 0)])
+def test_resort_movers_match_the_oracle(N, M, B, into):
+    """`into` beads of a sorted system move into one brick (the runs of 64, the LDS capacity of
+    2048 movers); into = 0: every bead leaves one brick for more bricks than the LDS table of
+    destinations holds."""
+    rng = np.random.default_rng(into + N)
+    L = 1.0 * M
+    R = (rng.random((N, 3)) * (L if into else B)).astype(np.float32)
+    s = wl.small_system(N // 10, 10, L, M, seed=2)
+    s.R[:] = R[: s.N]
+    st = engine.HpfState.from_system(s, sort_brick=B, halo=0)
+    st.sort()
+    pos = st.R.cpu().numpy().copy()
+    if into:
+        pick = rng.permutation(s.N)[:into]
+        pos[pick] = (B + rng.random((into, 3)) * B).astype(np.float32)
+    else:
+        pos = (rng.random((s.N, 3)) * L).astype(np.float32)
+    st.R.copy_(torch.from_numpy(pos))
+    st.resort = True
+    tag = host(st.tag)
+    perm, keys = oracle.sort_perm(pos, tag, s.L, s.M, B)
+    bonds = host(st.bonds)[:, perm]
+    inv = np.empty(s.N, dtype=np.int64)
+    inv[perm] = np.arange(s.N)
+    st.sort()
+    assert np.array_equal(host(st.tag), tag[perm])
+    assert np.array_equal(host(st.R), pos[perm])
+    assert np.array_equal(host(st.bonds), np.where(bonds >= 0, inv[np.maximum(bonds, 0)], -1))
+    nk = hpf.sort_key_count(st.mesh, B)
+    assert np.array_equal(host(st.cell_start), np.searchsorted(np.sort(keys), np.arange(nk + 2), side="left"))
+    assert hpf.hpf_get_device_status(clear=True) == 0

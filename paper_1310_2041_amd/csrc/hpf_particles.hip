@@ -328,7 +328,8 @@ __device__ __forceinline__ float3 bond_sum(int64_t i, const float3& xi, const fl
             bad = true;
             continue;
         }
-        bond_add<kR0Zero>(xi, R[j], k, r0, box, f, ei);
+        const float3 xj = R[j];
+        bond_add<kR0Zero>(xi, xj, k, r0, box, f, ei);
     }
     return f;
 }
@@ -511,10 +512,12 @@ __device__ __forceinline__ void angle_sum(int64_t i, const float3& xi, const flo
 {
     for (int r = first; r < A; ++r) {
         const AngleRow a = angle_row(angles, r, N, i);
-        if (angle_valid(a, N, ak))
-            angle_add(a.code, xi, R[a.p], R[a.q], ak, box, f, ei, energy);
-        else
+        if (angle_valid(a, N, ak)) {
+            const float3 xp = R[a.p], xq = R[a.q];
+            angle_add(a.code, xi, xp, xq, ak, box, f, ei, energy);
+        } else {
             bad |= a.p >= 0;
+        }
     }
 }
 
@@ -1029,7 +1032,7 @@ __device__ __forceinline__ float3 bead_finish(bool live, int64_t i, const BeadIn
 // (4% faster at 10M beads than 256); the general loop keeps kPThreads.
 constexpr int kAdvPipeThreads = 512;
 
-template <bool kR0Zero, bool kPipe, bool kThermo, bool kNT, int kD>
+template <bool kR0Zero, bool kPipe, bool kThermo, bool kNT>
 __global__ __launch_bounds__(kAdvPipeThreads) void k_advance(const float3* __restrict__ R,
                                                        float3* __restrict__ R_next,
                                                        float3* __restrict__ Vel,
@@ -1056,18 +1059,18 @@ __global__ __launch_bounds__(kAdvPipeThreads) void k_advance(const float3* __res
         // rows): a thread's beads are i, i + stride, ... (one per chunk of its walk), and
         // the next one's own loads stay in flight through this one's arithmetic
         int64_t i = w.first + threadIdx.x;
-        BeadIn<kD> cur;
+        BeadIn<kPreBonds> cur;
         if (i < w.end)
             bead_fetch<kThermo, kNT>(cur, i, R, Vel, T, bonds, D, N, inv_mass, th);
         for (; i < w.end; i += w.stride) {
-            BeadLoads<kD> L;
+            BeadLoads<kPreBonds> L;
             if constexpr (kNT)
                 __builtin_amdgcn_s_setprio(1);
             bead_issue<false, kThermo, kNT>(L, cur, i, m, K, G, R, Vel, N, th);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (kNT)
                 __builtin_amdgcn_s_setprio(0);
-            BeadIn<kD> nxt;
+            BeadIn<kPreBonds> nxt;
             bead_fetch<kThermo, kNT>(nxt, i + w.stride < w.end ? i + w.stride : i, R, Vel, T, bonds, D, N, inv_mass,
                                 th);
             __builtin_amdgcn_sched_barrier(0);
@@ -1382,18 +1385,13 @@ using AdvFn = void (*)(const float3*, float3*, float3*, const uint8_t*, int64_t,
                        const int32_t*, int, float, float, BoxK, const float*, float, float3*, double*, double*,
                        ThermoK);
 
-template <bool kPipe, bool kNT, int kD>
+template <bool kPipe, bool kNT>
 static AdvFn advance_fn(bool thermo, bool r0z)
 {
-    return thermo ? (r0z ? k_advance<true, kPipe, true, kNT, kD> : k_advance<false, kPipe, true, kNT, kD>)
-                  : (r0z ? k_advance<true, kPipe, false, kNT, kD> : k_advance<false, kPipe, false, kNT, kD>);
+    return thermo ? (r0z ? k_advance<true, kPipe, true, kNT> : k_advance<false, kPipe, true, kNT>)
+                  : (r0z ? k_advance<true, kPipe, false, kNT> : k_advance<false, kPipe, false, kNT>);
 }
 
-template <int kD>
-static AdvFn advance_pipe_fn(bool nt, bool thermo, bool r0z)
-{
-    return nt ? advance_fn<true, true, kD>(thermo, r0z) : advance_fn<true, false, kD>(thermo, r0z);
-}
 
 hpf_status_t launch_advance(const float* R, float* R_next, float* Vel, const uint8_t* T, int64_t N,
                             const MeshK& m, int K, const float* G, const int32_t* bonds, int D, float k,
@@ -1402,9 +1400,10 @@ hpf_status_t launch_advance(const float* R, float* R_next, float* Vel, const uin
 {
     if (N == 0 && !e_part && !kin_part)
         return HPF_OK;
-    // the software-pipelined bead loop serves bond tables of up to kPreBondsWide rows and
-    // gradient meshes of up to kBufMeshBytes
-    const bool pipe = D <= kPreBondsWide && (int64_t)K * m.nm * 12 <= kBufMeshBytes;
+    // the software-pipelined bead loop serves bond tables of up to kPreBonds rows and gradient
+    // meshes of up to kBufMeshBytes (three rows, whose velocities come with the corners, ran
+    // slower in it: 2.5M beads of stars 96 us against 71 in the plain loop)
+    const bool pipe = D <= kPreBonds && (int64_t)K * m.nm * 12 <= kBufMeshBytes;
     const int threads = pipe ? kAdvPipeThreads : kPThreads;
     const int64_t cap = (e_part || kin_part) ? HPF_NPART : (1 << 20);
     const int64_t nb = std::max<int64_t>(1, std::min<int64_t>((N + threads - 1) / threads, cap));
@@ -1416,9 +1415,8 @@ hpf_status_t launch_advance(const float* R, float* R_next, float* Vel, const uin
     auto* Fo = reinterpret_cast<float3*>(F_out);
     const bool thermo = th.thr != 0, r0z = r0 == 0.0f;
     const bool nt = pipe && streamed_bytes(N, D, K, m, 0) > kStreamHintBytes;
-    const AdvFn fn = !pipe            ? advance_fn<false, false, kPreBonds>(thermo, r0z)
-                     : D <= kPreBonds ? advance_pipe_fn<kPreBonds>(nt, thermo, r0z)
-                                      : advance_pipe_fn<kPreBondsWide>(nt, thermo, r0z);
+    const AdvFn fn = pipe ? (nt ? advance_fn<true, true>(thermo, r0z) : advance_fn<true, false>(thermo, r0z))
+                          : advance_fn<false, false>(thermo, r0z);
     hipLaunchKernelGGL(fn, g, bl, 0, s, Rp, Rn, Vp, T, N, m, K, Gp, bonds, D, k, r0, box, inv_mass, dt, Fo,
                        e_part, kin_part, th);
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
@@ -1452,21 +1450,25 @@ using LaunchFn = hpf_status_t (*)(const float3*, float3*, float3*, const uint8_t
                                   const uint32_t*, unsigned long long*, unsigned long long*, float3*, double*,
                                   double*, const ThermoK&, hipStream_t);
 
+// (A null function stands for a form that the rule for `pipe` below never asks for.)
 template <bool kPipe, bool kNT, int kD>
 static LaunchFn scatter_launch_fn(bool wide, bool thermo, bool r0z)
 {
-    if (thermo) {
-        if (wide)
-            return r0z ? launch_advance_scatter_t<true, kASThreadsWide, kPipe, true, kNT, kD>
-                       : launch_advance_scatter_t<false, kASThreadsWide, kPipe, true, kNT, kD>;
-        return r0z ? launch_advance_scatter_t<true, kASThreadsThermo, kPipe, true, kNT, kD>
-                   : launch_advance_scatter_t<false, kASThreadsThermo, kPipe, true, kNT, kD>;
-    }
+    if (thermo && wide)
+        return r0z ? launch_advance_scatter_t<true, kASThreadsWide, kPipe, true, kNT, kD>
+                   : launch_advance_scatter_t<false, kASThreadsWide, kPipe, true, kNT, kD>;
     if (wide)
         return r0z ? launch_advance_scatter_t<true, kASThreadsWide, kPipe, false, kNT, kD>
                    : launch_advance_scatter_t<false, kASThreadsWide, kPipe, false, kNT, kD>;
-    return r0z ? launch_advance_scatter_t<true, kASThreadsDefault, kPipe, false, kNT, kD>
-               : launch_advance_scatter_t<false, kASThreadsDefault, kPipe, false, kNT, kD>;
+    if constexpr (kNT && kD > kPreBonds) {
+        return nullptr;
+    } else {
+        if (thermo)
+            return r0z ? launch_advance_scatter_t<true, kASThreadsThermo, kPipe, true, kNT, kD>
+                       : launch_advance_scatter_t<false, kASThreadsThermo, kPipe, true, kNT, kD>;
+        return r0z ? launch_advance_scatter_t<true, kASThreadsDefault, kPipe, false, kNT, kD>
+                   : launch_advance_scatter_t<false, kASThreadsDefault, kPipe, false, kNT, kD>;
+    }
 }
 
 template <int kD>
@@ -1488,19 +1490,26 @@ hpf_status_t launch_advance_scatter(const float* R, float* R_next, float* Vel, c
     auto* Vp = reinterpret_cast<float3*>(Vel);
     auto* Gp = reinterpret_cast<const float3*>(G);
     auto* Fo = reinterpret_cast<float3*>(F_out);
-    // the software-pipelined bead loop serves bond tables of up to kPreBondsWide rows and
-    // gradient meshes of up to kBufMeshBytes
-    const bool pipe = D <= kPreBondsWide && (int64_t)K * tk.m.nm * 12 <= kBufMeshBytes;
     const bool thermo = th.thr != 0, r0z = r0 == 0.0f;
     // A deposit box of more than 80 KiB (16-cell bricks) leaves room for one workgroup per
     // CU: the pass then takes 768 threads (3 waves per SIMD; 1024 threads would cap it at 128
     // VGPRs, which spills).
     const bool wide = sizeof(unsigned long long) * (size_t)K * tk.P * tk.P * tk.P > 80 * 1024;
     const int64_t box_bytes = (int64_t)sizeof(unsigned long long) * K * tk.P * tk.P * tk.P * tk.ntiles;
-    const bool nt = pipe && streamed_bytes(N, D, K, tk.m, box_bytes) > kStreamHintBytes;
+    const bool streams = streamed_bytes(N, D, K, tk.m, box_bytes) > kStreamHintBytes;
+    // The software-pipelined bead loop serves gradient meshes of up to kBufMeshBytes and bond
+    // tables of up to kPreBonds rows, or of kPreBondsWide where the wide workgroup or the caches
+    // make up for velocities that come with the corners (600,000 beads of stars: 32 us against
+    // 36 in the plain loop; 8M in 16-cell bricks: the step 343 us against 519; 2.5M in 8-cell
+    // bricks, streaming: 120 against 117).
+    const bool pipe = (int64_t)K * tk.m.nm * 12 <= kBufMeshBytes &&
+                      (D <= kPreBonds || (D <= kPreBondsWide && (wide || !streams)));
+    const bool nt = pipe && streams;
     const LaunchFn launch = !pipe            ? scatter_launch_fn<false, false, kPreBonds>(wide, thermo, r0z)
                             : D <= kPreBonds ? scatter_pipe_fn<kPreBonds>(nt, wide, thermo, r0z)
                                              : scatter_pipe_fn<kPreBondsWide>(nt, wide, thermo, r0z);
+    if (!launch)
+        return HPF_EINVAL;
     return launch(Rp, Rn, Vp, T, N, tk, K, Gp, bonds, D, k, r0, box, inv_mass, dt, cell_start, partials, counts, Fo,
                   e_part, kin_part, th, s);
 }

@@ -158,8 +158,16 @@ class HpfState:
         self.G = (torch.zeros if composition_list else torch.empty)((self.K, nm, 3), dtype=torch.float32,
                                                                     device=dev)
         self.part = torch.zeros((N_ROWS, hpf.HPF_NPART), dtype=torch.float64, device=dev)
+        self._rows_of = None           # the buffer that self._rows are views of
         self.energy = torch.zeros(8, dtype=torch.float64, device=dev)
         self.steps_done = 0
+
+    def rows(self):
+        """(W, E_bond, KE to Pz, E_angle): views of the partial-sum buffer, made once per buffer."""
+        if self._rows_of is not self.part:
+            self._rows_of = self.part
+            self._rows = (self.part[ROW_W], self.part[ROW_EB], self.part[ROW_KE:ROW_KE + 4], self.part[ROW_EA])
+        return self._rows
 
     def set_thermostat(self, rate: float, kT: float | None = None, seed: int = 1, tag_offset: int = 0):
         """NVT with the Andersen thermostat (Integration methods section): every step each bead
@@ -252,7 +260,7 @@ class HpfState:
         """Counts, potential and (centred stencil) gradient of the current positions."""
         self.scatter(stream)
         hpf.hpf_field_potential(self.counts, self.mesh, self.field, self.V,
-                                self.part[ROW_W] if (report or self.field_every > 1) else None,
+                                self.rows()[0] if (report or self.field_every > 1) else None,
                                 stream, present=self.present)
         if self.stencil == "centred":
             hpf.hpf_field_gradient(self.V, self.mesh, self.K, self.G, stream, present=self.present)
@@ -270,14 +278,14 @@ class HpfState:
 
     def bond_forces(self, report=False, stream=None):
         hpf.bond_forces(self.R, self.bonds if self.bonds.shape[0] else None, self.k_bond, self.r0,
-                        self.box, self.F, self.part[ROW_EB] if report else None, stream)
+                        self.box, self.F, self.rows()[1] if report else None, stream)
 
     def angle_forces(self, report=False, stream=None):
         if self.angles is None:
             return
         k, th, fm = self.angle_params
         hpf.angle_forces(self.R, self.angles, k, th, fm, self.box, self.F,
-                         self.part[ROW_EA] if report else None, stream)
+                         self.rows()[3] if report else None, stream)
 
     def forces(self, report=False, stream=None, rebuild=True):
         self.field_forces(report, stream, rebuild)
@@ -293,7 +301,7 @@ class HpfState:
                                    self.cell_start, self.B, self.halo, self.strays, self.scatter_work, stream=stream)
             hpf.hpf_field_potential_cells(self.strays, self.N, self.mesh, self.field, self.B, self.halo,
                                           self.scatter_work, self.V,
-                                          self.part[ROW_W] if (report or self.field_every > 1) else None, stream,
+                                          self.rows()[0] if (report or self.field_every > 1) else None, stream,
                                           present=self.present)
             if self.stencil == "centred":
                 hpf.hpf_field_gradient(self.V, self.mesh, self.K, self.G, stream, present=self.present)
@@ -304,15 +312,15 @@ class HpfState:
             if rebuild:
                 self.rebuild(report, stream)
         self.density_pending = False
-        kin = self.part[ROW_KE:ROW_KE + 4] if report else None
+        kin = self.rows()[2] if report else None
         th = self.thermostat()
         stag = self.stencil == "staggered"
         k, theta0, form = self.angle_params
         hpf.hpf_force_kick(self.R, self.T, self.mesh, self.K, self.V if stag else self.G,
                            self.bonds if self.bonds.shape[0] else None, self.k_bond, self.r0, self.box, self.F,
                            self.Vel, self.dt, stag, self.angles, k, theta0, form,
-                           e_part=self.part[ROW_EB] if report else None,
-                           ea_part=self.part[ROW_EA] if report and self.angles is not None else None,
+                           e_part=self.rows()[1] if report else None,
+                           ea_part=self.rows()[3] if report and self.angles is not None else None,
                            kin_part=kin if th is None else None, stream=stream)
         if th is not None:
             hpf.hpf_andersen(self.Vel, th, kin_part=kin, stream=stream)
@@ -344,7 +352,7 @@ class HpfState:
             self.sort(stream)
         self.forces(report=True, stream=stream)
         hpf.verlet_step(None, self.Vel, torch.zeros_like(self.F), self.dt, self.box, 2,
-                        kin_part=self.part[ROW_KE:ROW_KE + 4], stream=stream)
+                        kin_part=self.rows()[2], stream=stream)
         hpf.hpf_reduce_partials(self.part, N_ROWS, self.energy, stream)
 
     # ------------------------------------------------------------ fused path
@@ -376,7 +384,7 @@ class HpfState:
     def potential(self, report=False, stream=None):
         """Counts and potential of the current positions: finish the deposit the last fused
         pass made and form V in one pass, or scatter from scratch and then form V."""
-        w = self.part[ROW_W] if report else None
+        w = self.rows()[0] if report else None
         if self.density_pending:
             hpf.hpf_field_potential_cells(self.counts, self.N, self.mesh, self.field, self.B, self.halo,
                                           self.scatter_work, self.V, w, stream, present=self.present)
@@ -394,8 +402,8 @@ class HpfState:
         leaves them so). Without `deposit` (the next step keeps the field) the plain pass runs
         instead of the depositing one; the beads move the same either way."""
         bonds = self.bonds if self.bonds.shape[0] else None
-        e_part = self.part[ROW_EB] if report else None
-        kin_part = self.part[ROW_KE:ROW_KE + 4] if report else None
+        e_part = self.rows()[1] if report else None
+        kin_part = self.rows()[2] if report else None
         F_out = self.F if self.keep_force else None
         th = self.thermostat()
         self.density_pending = False

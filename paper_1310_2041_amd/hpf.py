@@ -198,26 +198,31 @@ def _check(fn: str, status: int):
 
 def _stream(stream):
     if stream is None:
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        # the current stream's handle without building a torch.cuda.Stream (4 us a call)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     if isinstance(stream, torch.cuda.Stream):
-        return C.c_void_p(stream.cuda_stream)
-    return C.c_void_p(int(stream))
+        return stream.cuda_stream
+    return int(stream)
 
 
 def _dev(t: torch.Tensor | None, name: str, dtype=None, shape=None, allow_none=False):
+    """Device address of a tensor that is as the call expects it (None when it is empty)."""
     if t is None:
         if allow_none:
             return None
         raise ValueError(f"{name} is required")
-    if not t.is_cuda:
-        raise ValueError(f"{name} must be a GPU tensor")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    if dtype is not None and t.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
-        raise ValueError(f"{name} has dtype {t.dtype}, expected {dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return C.c_void_p(t.data_ptr()) if t.numel() else None
+    # one test for the usual case; what fails it is looked at again for its message
+    if not (t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is dtype) and
+            (shape is None or t.shape == shape)):
+        if not t.is_cuda:
+            raise ValueError(f"{name} must be a GPU tensor")
+        if not t.is_contiguous():
+            raise ValueError(f"{name} must be contiguous")
+        if dtype is not None and t.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
+            raise ValueError(f"{name} has dtype {t.dtype}, expected {dtype}")
+        if shape is not None and tuple(t.shape) != tuple(shape):
+            raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
+    return t.data_ptr() if t.numel() else None
 
 
 _U64 = (torch.int64, torch.uint64) if hasattr(torch, "uint64") else (torch.int64,)
@@ -243,7 +248,8 @@ def make_field(K: int, kT: float, inv_kappa: float, chi) -> Field:
 
 
 def _nm(mesh: Mesh) -> int:
-    return mesh.M[0] * mesh.M[1] * mesh.M[2]
+    x, y, z = mesh.M
+    return x * y * z
 
 
 def _box(mesh_or_box):
@@ -544,10 +550,8 @@ def hpf_sort_workspace_bytes(N: int, mesh: Mesh, B: int = 8) -> int:
 def sort_key_count(mesh: Mesh, B: int = 8) -> int:
     """NK: number of sort keys, one per brick of B^3 cells (cell_start needs NK + 2)."""
     B = B or 8
-    n = 1
-    for d in range(3):
-        n *= (mesh.M[d] + B - 1) // B
-    return n
+    x, y, z = mesh.M
+    return -(-x // B) * -(-y // B) * -(-z // B)
 
 
 def hpf_resort_by_cell(mesh: Mesh, B: int, R_in, Vel_in, T_in, tag_in, bonds_in, R_out, Vel_out,

@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kASThreadsBatch) void k_batch_advance_scatter(
     double* __restrict__ e_part, double* __restrict__ kin_part, int nslot, ThermoK th)
 {
     extern __shared__ unsigned long long dbox[];
-    __shared__ double scratch[kASThreadsBatch / kWave];
+    __shared__ double scratch[5 * kASThreadsBatch / kWave];
     const int64_t li = xcd_block(blockIdx.x, gridDim.x);
     const ItemK it = items[li];
     const RepK& rp = reps[it.rep];
@@ -382,44 +382,34 @@ __global__ __launch_bounds__(kASThreadsBatch) void k_batch_advance_scatter(
         raise_flag(HPF_FLAG_BAD_BOND);
     if (nonfinite)
         raise_flag(HPF_FLAG_NONFINITE);
-    if (e_part) {
-        const double s = block_sum(e, scratch);
-        if (threadIdx.x == 0)
-            e_part[li] = s;
-    }
-    if (kin_part)
-        acc.store_rows(kin_part, nslot, li, scratch);
+    store_energies(e, acc, e_part, kin_part, nslot, li, scratch);
 }
 
-// per replica: energies {KE, E_bond, W, E_tot, Px, Py, Pz, 0} from the item
-// partials, each summed in item order by one lane
-__global__ __launch_bounds__(64) void k_batch_reduce(const int64_t* __restrict__ bead_items,
-                                                     const int64_t* __restrict__ mesh_items,
-                                                     const double* __restrict__ w_part,
-                                                     const double* __restrict__ e_part,
-                                                     const double* __restrict__ kin_part, int nslot,
-                                                     double* __restrict__ out)
+// per replica: energies {KE, E_bond, W, E_tot, Px, Py, Pz, 0} from the item partials: wavefront
+// c sums row c (lane l the items l, l + 64, ..., then the wave sum). One lane per row, item after
+// item, took 65-77 us for a sweep of 64 replicas, all of it memory latency.
+constexpr int kBatchRows = 6;
+
+__global__ __launch_bounds__(kBatchRows * kWave) void k_batch_reduce(const int64_t* __restrict__ bead_items,
+                                                                     const int64_t* __restrict__ mesh_items,
+                                                                     const double* __restrict__ w_part,
+                                                                     const double* __restrict__ e_part,
+                                                                     const double* __restrict__ kin_part, int nslot,
+                                                                     double* __restrict__ out)
 {
-    __shared__ double sums[6];
+    __shared__ double sums[kBatchRows];
     const int r = blockIdx.x;
-    const int c = threadIdx.x;
-    if (c < 6) {
-        double s = 0.0;
-        if (c == 0) {
-            for (int64_t i = mesh_items[r]; i < mesh_items[r + 1]; ++i)
-                s += w_part[i];
-        } else if (c == 1) {
-            for (int64_t i = bead_items[r]; i < bead_items[r + 1]; ++i)
-                s += e_part[i];
-        } else {
-            const double* row = kin_part + (int64_t)(c - 2) * nslot;
-            for (int64_t i = bead_items[r]; i < bead_items[r + 1]; ++i)
-                s += row[i];
-        }
+    const int c = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+    const int64_t* items = c == 0 ? mesh_items : bead_items;
+    const double* row = c == 0 ? w_part : c == 1 ? e_part : kin_part + (int64_t)(c - 2) * nslot;
+    double s = 0.0;
+    for (int64_t i = items[r] + lane; i < items[r + 1]; i += kWave)
+        s += row[i];
+    s = wave_sum(s);
+    if (lane == 0)
         sums[c] = s;
-    }
     __syncthreads();
-    if (c == 0) {
+    if (threadIdx.x == 0) {
         double* o = out + (int64_t)r * 8;
         o[0] = sums[2];                    // KE
         o[1] = sums[1];                    // E_bond
@@ -829,7 +819,7 @@ static hpf_status_t batch_particles(hpf_batch* b, bool prime, bool report, hipSt
         hipLaunchKernelGGL(k_add_i64, dim3(1), dim3(1), 0, s, tstep, (int64_t)1);
     b->rcur = 1 - b->rcur;
     if (report)
-        hipLaunchKernelGGL(k_batch_reduce, dim3(b->nrep), dim3(64), 0, s,
+        hipLaunchKernelGGL(k_batch_reduce, dim3(b->nrep), dim3(kBatchRows * kWave), 0, s,
                            b->at<int64_t>(fused ? L.off_adv_ioff : L.off_bead_ioff),
                            b->at<int64_t>(b->w_bricks ? L.off_brick_ioff : L.off_mesh_ioff),
                            b->at<double>(L.off_wpart), e, kp, nslot, b->at<double>(L.off_energy));

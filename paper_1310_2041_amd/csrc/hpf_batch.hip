@@ -61,7 +61,7 @@ __device__ __forceinline__ TileK tile_of(const RepK& r, int B, int h)
 
 // ------------------------------------------------------------- cell scatter
 
-__global__ __launch_bounds__(kTcThreads) void k_batch_scatter_bricks(const RepK* __restrict__ reps,
+__global__ __launch_bounds__(kScBrickThreads) void k_batch_scatter_bricks(const RepK* __restrict__ reps,
                                                                      const ItemK* __restrict__ items,
                                                                      int B, int h, int K,
                                                                      const float3* __restrict__ R,
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kTcThreads) void k_batch_scatter_bricks(const RepK*
     const RepK& rp = reps[it.rep];
     const TileK tk = tile_of(rp, B, h);
     const int P = tk.P;
-    scatter_brick_body(R, T, K, tk, cell_start + rp.key_base, it.begin,
+    scatter_brick_body<kScBrickThreads>(R, T, K, tk, cell_start + rp.key_base, it.begin,
                        partials + (rp.brick_off + it.begin) * (int64_t)K * P * P * P, strays);
 }
 
@@ -129,22 +129,28 @@ struct RepKeyer {
     }
 };
 
-// Strays of all replicas (global indices in one list) and each replica's
-// beads that the sort could not bin, with global atomics.
+// Strays of all replicas, brick by brick, and each replica's beads that the sort could not bin,
+// with global atomics.
 __global__ __launch_bounds__(kTcThreads) void k_batch_scatter_strays(const RepK* __restrict__ reps, int nrep,
+                                                                     const ItemK* __restrict__ items, int64_t nitems,
                                                                      int K, const float3* __restrict__ R,
                                                                      const uint8_t* __restrict__ T,
                                                                      const uint32_t* __restrict__ cell_start,
                                                                      const uint32_t* __restrict__ strays,
                                                                      unsigned long long* __restrict__ counts)
 {
-    const int64_t nstray = strays[0];
     bool bad = false;
-    for (int64_t j = (int64_t)blockIdx.x * kTcThreads + threadIdx.x; j < nstray;
-         j += (int64_t)gridDim.x * kTcThreads) {
-        const int64_t p = strays[1 + j];
-        const RepK& rp = reps[find_rep(reps, nrep, p)];
-        bad |= !deposit_global(R[p], T[p], K, rp.m, counts + (int64_t)K * rp.moff);
+    const int64_t per = (nitems + gridDim.x - 1) / gridDim.x;
+    const int64_t end = min(nitems, ((int64_t)blockIdx.x + 1) * per);
+    for (int64_t b0 = (int64_t)blockIdx.x * per; b0 < end; b0 += kTcThreads) {
+        const ItemK it = items[min(b0 + threadIdx.x, nitems - 1)];
+        const uint32_t* range = cell_start + reps[it.rep].key_base + it.begin;
+        for_each_stray(strays, min((int64_t)kTcThreads, end - b0), 0, 1, range[0], range[1],
+                       [&](int64_t q, uint32_t p) {
+                           const RepK& rp = reps[items[b0 + q].rep];
+                           bad |= !deposit_global(R[p], T[p], K, rp.m, counts + (int64_t)K * rp.moff);
+                       });
+        __syncthreads();
     }
     // unbinned tails: replica r's beads with key key_base_r + NK_r
     for (int r = blockIdx.x; r < nrep; r += gridDim.x) {
@@ -714,13 +720,12 @@ static hpf_status_t batch_fields(hpf_batch* b, bool report, hipStream_t s)
         if (smem > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(k_batch_scatter_bricks),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
             return HPF_EINVAL;
-        hipLaunchKernelGGL(k_zero_u32_one, dim3(1), dim3(1), 0, s, strays);
-        hipLaunchKernelGGL(k_batch_scatter_bricks, dim3((unsigned)b->n_brick_items), dim3(kTcThreads), smem, s, reps,
+        hipLaunchKernelGGL(k_batch_scatter_bricks, dim3((unsigned)b->n_brick_items), dim3(kScBrickThreads), smem, s, reps,
                            b->at<ItemK>(L.off_brick_items), B, h, K, R, T, cs, partials, strays);
         hipLaunchKernelGGL(k_batch_scatter_sum<false>, dim3((unsigned)b->n_brick_items), sum_block(b->n_brick_items),
                            0, s, reps, b->at<ItemK>(L.off_brick_items), B, h, K, partials, counts);
-        hipLaunchKernelGGL(k_batch_scatter_strays, dim3(256), dim3(kTcThreads), 0, s, reps, b->nrep, K, R, T, cs,
-                           strays, counts);
+        hipLaunchKernelGGL(k_batch_scatter_strays, dim3(256), dim3(kTcThreads), 0, s, reps, b->nrep,
+                           b->at<ItemK>(L.off_brick_items), b->n_brick_items, K, R, T, cs, strays, counts);
         if (hpf_status_t st = batch_potential(b, K, counts, w, s))
             return st;
         b->w_bricks = false;
@@ -1013,13 +1018,12 @@ hpf_status_t hpf_batch_density(hpf_batch_t* b, uint64_t* counts_out, void* strea
         const auto* R = reinterpret_cast<const float3*>(b->buf.R[b->rcur]);
         const uint8_t* T = b->buf.T[b->scur];
         const uint32_t* cs = b->at<uint32_t>(L.off_start);
-        hipLaunchKernelGGL(k_zero_u32_one, dim3(1), dim3(1), 0, s, strays);
-        hipLaunchKernelGGL(k_batch_scatter_bricks, dim3((unsigned)b->n_brick_items), dim3(kTcThreads), smem, s, reps,
+        hipLaunchKernelGGL(k_batch_scatter_bricks, dim3((unsigned)b->n_brick_items), dim3(kScBrickThreads), smem, s, reps,
                            bi, B, h, K, R, T, cs, partials, strays);
         hipLaunchKernelGGL(k_batch_scatter_sum<false>, dim3((unsigned)b->n_brick_items), sum_block(b->n_brick_items),
                            0, s, reps, bi, B, h, K, partials, out);
-        hipLaunchKernelGGL(k_batch_scatter_strays, dim3(256), dim3(kTcThreads), 0, s, reps, b->nrep, K, R, T, cs,
-                           strays, out);
+        hipLaunchKernelGGL(k_batch_scatter_strays, dim3(256), dim3(kTcThreads), 0, s, reps, b->nrep, bi,
+                           b->n_brick_items, K, R, T, cs, strays, out);
     }
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }

@@ -21,12 +21,13 @@
 // free, so the counts equal those of hpf_density_scatter bit for bit.
 #include "hpf_common.hpp"
 
+#include <algorithm>
+
 namespace hpf {
 
 constexpr int kTcThreads = 256;
 constexpr int kTcMaxB = 16;
 constexpr int kTcMaxHalo = 2;
-constexpr int kStrayStage = 1024;   // strays a workgroup stages in LDS before appending
 
 struct TileK {
     MeshK m;
@@ -129,12 +130,29 @@ __device__ __forceinline__ void box_deposit(unsigned long long* box, int P, int 
 // bead that drifted at most h cells reaches points [x0 - h, x0 + B + h]). A
 // thread takes kScBatch consecutive beads, so the lanes of one LDS atomic
 // mostly sit in different cells. The box goes to a per-brick partial buffer
-// with plain stores. Beads outside the box (strays) and beads that cannot be
-// binned are staged and appended to the stray list.
-constexpr int kScBatch = 4;
+// with plain stores.
+//
+// Beads outside the box (strays) are listed in place: the brick's own stretch
+// of a buffer of one entry per bead holds them from its first entry on, and
+// their number in its last. When all of the brick's beads are strays there is
+// no entry to spare for the number and no need of a list. So nothing is
+// cleared beforehand and no workgroup waits for another's reservation.
+//
+// A workgroup alone on its CU is bound by its own chain (clear the box, load, deposit, store), so
+// it takes the most threads there are: that is where no CU gets a second one, for want of bricks
+// or of LDS. Otherwise 512 threads measure best. The three passes, with 256 threads of four
+// beads / 512 of two / 1024 of two: 20,000 beads in 27 bricks 15.1 / 12.4 / 11.7 us; 3M beads in
+// 216 bricks of 16 cells 72.1 / 50.6 / 42.5, in 1,728 of 8 cells 39.6 / 38.8 / 50.6; 1M in 512
+// bricks 22.5 / 19.3 / 21.1.
+constexpr int kScBatch = 2;
+constexpr int kScBrickThreads = 512;
+constexpr int kScLoneThreads = 1024;
+constexpr int64_t kCus = 256;
+constexpr size_t kLdsPerCu = 160 * 1024;
 
 // Deposit of the beads listed in `brick` (cell_start of this system, i.e.
 // already offset for batched systems) into an LDS box, stored to `out`.
+template <int kThreads>
 __device__ __forceinline__ void scatter_brick_body(const float3* __restrict__ R, const uint8_t* __restrict__ T,
                                                    int K, const TileK& tk,
                                                    const uint32_t* __restrict__ cell_start, int64_t brick,
@@ -142,11 +160,12 @@ __device__ __forceinline__ void scatter_brick_body(const float3* __restrict__ R,
                                                    uint32_t* __restrict__ strays)
 {
     extern __shared__ unsigned long long smem[];
-    __shared__ uint32_t stray_buf[kStrayStage];
-    __shared__ uint32_t stray_n, stray_base;
+    __shared__ uint32_t stray_n;
     const int tid = threadIdx.x;
     const int B = tk.B, h = tk.h, P = tk.P;
     const int Mx = tk.m.M[0], My = tk.m.M[1], Mz = tk.m.M[2];
+    const uint32_t first = cell_start[brick];
+    const uint32_t last = cell_start[brick + 1];
     const int bx = (int)(brick % tk.nb[0]);
     const int by = (int)((brick / tk.nb[0]) % tk.nb[1]);
     const int bz = (int)(brick / ((int64_t)tk.nb[0] * tk.nb[1]));
@@ -155,14 +174,12 @@ __device__ __forceinline__ void scatter_brick_body(const float3* __restrict__ R,
     const int P2 = P * P, P3 = P2 * P;
     const int nbox = K * P3;
     unsigned long long* box = smem;
-    for (int e = tid; e < nbox; e += kTcThreads)
+    for (int e = tid; e < nbox; e += kThreads)
         box[e] = 0ull;
     if (tid == 0)
         stray_n = 0;
     __syncthreads();
-    const uint32_t first = cell_start[brick];
-    const uint32_t last = cell_start[brick + 1];
-    for (uint32_t j0 = first; j0 < last; j0 += kTcThreads * kScBatch) {
+    for (uint32_t j0 = first; j0 < last; j0 += kThreads * kScBatch) {
         float3 rj[kScBatch];
         int tj[kScBatch];
         const uint32_t jb = j0 + tid * kScBatch;
@@ -183,38 +200,31 @@ __device__ __forceinline__ void scatter_brick_body(const float3* __restrict__ R,
             int lx, ly, lz;
             const bool ok = bead_cell(rj[u], tk.m, b) && t < K;
             if (!ok || !brick_box_cell(b, tk.m, x0, y0, z0, ox, oy, oz, h, lx, ly, lz)) {
-                const uint32_t slot = atomicAdd(&stray_n, 1u);
-                if (slot < (uint32_t)kStrayStage)
-                    stray_buf[slot] = p;
-                else
-                    strays[1 + atomicAdd(strays, 1u)] = p;       // stage full: direct append
+                const uint32_t slot = first + atomicAdd(&stray_n, 1u);
+                if (slot < last - 1)
+                    strays[slot] = p;
                 continue;
             }
             box_deposit(box, P, t, lx, ly, lz, b);
         }
     }
     __syncthreads();
-    // one global reservation per workgroup for its staged strays
-    const uint32_t nst = min(stray_n, (uint32_t)kStrayStage);
-    if (tid == 0 && nst)
-        stray_base = atomicAdd(strays, nst);
-    __syncthreads();
-    for (uint32_t i = tid; i < nst; i += kTcThreads)
-        strays[1 + stray_base + i] = stray_buf[i];
-    for (int e = tid; e < nbox; e += kTcThreads)
+    if (tid == 0 && first < last)
+        strays[last - 1] = stray_n;
+    for (int e = tid; e < nbox; e += kThreads)
         out[e] = box[e];
 }
 
-__global__ __launch_bounds__(kTcThreads) void k_scatter_bricks(const float3* __restrict__ R,
-                                                               const uint8_t* __restrict__ T, int K,
-                                                               TileK tk,
-                                                               const uint32_t* __restrict__ cell_start,
-                                                               unsigned long long* __restrict__ partials,
-                                                               uint32_t* __restrict__ strays)
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_scatter_bricks(const float3* __restrict__ R,
+                                                             const uint8_t* __restrict__ T, int K, TileK tk,
+                                                             const uint32_t* __restrict__ cell_start,
+                                                             unsigned long long* __restrict__ partials,
+                                                             uint32_t* __restrict__ strays)
 {
     const int64_t brick = xcd_block(blockIdx.x, gridDim.x);
     const int P = tk.P;
-    scatter_brick_body(R, T, K, tk, cell_start, brick, partials + brick * (int64_t)K * P * P * P, strays);
+    scatter_brick_body<kThreads>(R, T, K, tk, cell_start, brick, partials + brick * (int64_t)K * P * P * P, strays);
 }
 
 // Pass 2: one thread per mesh point sums the partial boxes that cover it and
@@ -457,29 +467,60 @@ __device__ __forceinline__ bool deposit_global(const float3& r, int t, int K, co
     return true;
 }
 
+// The strays of n <= kTcThreads bricks, deposited by the whole workgroup; thread i < n brings the
+// bead range of brick i and reads the length of its list, so that the chain of reads is walked
+// once and not brick after brick. With parts > 1, every parts-th turn of each list from `part` on.
+template <class Deposit>
+__device__ __forceinline__ void for_each_stray(const uint32_t* __restrict__ strays, int64_t n, int part, int parts,
+                                               uint32_t first, uint32_t last, Deposit deposit)
+{
+    __shared__ uint32_t at[kTcThreads], len[kTcThreads];
+    __shared__ uint8_t whole[kTcThreads];
+    const int tid = threadIdx.x;
+    bool any = false;
+    if (tid < n) {
+        at[tid] = first;
+        const uint32_t ns = first < last ? strays[last - 1] : 0u;
+        len[tid] = ns;
+        whole[tid] = ns == last - first;
+        any = ns != 0;
+    }
+    if (!__syncthreads_or(any))
+        return;
+    for (int64_t q = 0; q < n; ++q)
+        for (uint32_t i = part * kTcThreads + tid; i < len[q]; i += parts * kTcThreads)
+            deposit(q, whole[q] ? at[q] + i : strays[at[q] + i]);
+}
+
+// Workgroups of the stray pass, and how many share a brick's list when there are few bricks.
+constexpr int kStrayBlocks = 512;
+
 // Global-atomic deposit of the stray beads and of the beads the sort could not
 // bin (storage indices [cell_start[NK], N)).
 __global__ __launch_bounds__(kTcThreads) void k_scatter_strays(const float3* __restrict__ R,
                                                                const uint8_t* __restrict__ T, int64_t N,
-                                                               int K, MeshK m, uint32_t NK,
+                                                               int K, MeshK m, uint32_t NK, int parts,
                                                                const uint32_t* __restrict__ cell_start,
                                                                const uint32_t* __restrict__ strays,
                                                                unsigned long long* __restrict__ counts)
 {
-    const int64_t nstray = strays[0];
-    const int64_t tail0 = cell_start[NK];
-    const int64_t total = nstray + (N - tail0);
     bool bad = false;
-    for (int64_t j = (int64_t)blockIdx.x * kTcThreads + threadIdx.x; j < total;
-         j += (int64_t)gridDim.x * kTcThreads) {
-        const int64_t p = j < nstray ? (int64_t)strays[1 + j] : tail0 + (j - nstray);
-        bad |= !deposit_global(R[p], T[p], K, m, counts);
+    const int64_t groups = gridDim.x / parts, g = blockIdx.x / parts;
+    const int64_t per = (NK + groups - 1) / groups;
+    const int64_t end = min((int64_t)NK, (g + 1) * per);
+    for (int64_t b0 = g * per; b0 < end; b0 += kTcThreads) {
+        const int64_t b = min(b0 + threadIdx.x, (int64_t)NK - 1);
+        for_each_stray(strays, min((int64_t)kTcThreads, end - b0), blockIdx.x % parts, parts, cell_start[b],
+                       cell_start[b + 1],
+                       [&](int64_t, uint32_t p) { bad |= !deposit_global(R[p], T[p], K, m, counts); });
+        __syncthreads();
     }
+    for (int64_t p = (int64_t)cell_start[NK] + (int64_t)blockIdx.x * kTcThreads + threadIdx.x; p < N;
+         p += (int64_t)gridDim.x * kTcThreads)
+        bad |= !deposit_global(R[p], T[p], K, m, counts);
     if (bad)
         raise_flag(HPF_FLAG_BAD_BEAD);
 }
-
-__global__ void k_zero_u32_one(uint32_t* p) { *p = 0u; }
 
 size_t scatter_cells_smem(int K, int P)
 {
@@ -498,19 +539,26 @@ hpf_status_t launch_scatter_cells(const float* R, const uint8_t* T, int64_t N, c
     auto* c = reinterpret_cast<unsigned long long*>(counts);
     auto* Rp = reinterpret_cast<const float3*>(R);
     const size_t smem = scatter_cells_smem(K, tk.P);
-    if (smem > 65536) {
+    auto go = [&](auto kernel, int threads) {
         // gfx950 has 160 KiB of LDS per CU; opt in above the 64 KiB default
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_scatter_bricks),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
+        if (smem > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                (int)smem) != hipSuccess)
             return HPF_EINVAL;
-    }
-    hipLaunchKernelGGL(k_zero_u32_one, dim3(1), dim3(1), 0, s, strays);
-    hipLaunchKernelGGL(k_scatter_bricks, dim3((unsigned)tk.ntiles), dim3(kTcThreads), smem, s, Rp, T, K, tk,
-                       cell_start, partials, strays);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tk.ntiles), dim3(threads), smem, s, Rp, T, K, tk, cell_start,
+                           partials, strays);
+        return HPF_OK;
+    };
+    const bool lone = tk.ntiles <= kCus || 2 * smem > kLdsPerCu;
+    const hpf_status_t st = lone ? go(k_scatter_bricks<kScLoneThreads>, kScLoneThreads)
+                                 : go(k_scatter_bricks<kScBrickThreads>, kScBrickThreads);
+    if (st != HPF_OK)
+        return st;
     hipLaunchKernelGGL(k_scatter_sum<false>, dim3((unsigned)tk.ntiles), sum_block(tk.ntiles), 0, s, partials, tk, K,
                        c);
-    hipLaunchKernelGGL(k_scatter_strays, dim3(512), dim3(kTcThreads), 0, s, Rp, T, N, K, tk.m, tk.NK,
-                       cell_start, strays, c);
+    const int parts = (int)std::max<int64_t>(1, kStrayBlocks / tk.NK);
+    hipLaunchKernelGGL(k_scatter_strays, dim3(kStrayBlocks / parts * parts), dim3(kTcThreads), 0, s, Rp, T, N, K,
+                       tk.m, tk.NK, parts, cell_start, strays, c);
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }
 

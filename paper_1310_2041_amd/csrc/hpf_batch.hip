@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kFPThreads) void k_batch_finish_potential(const Rep
     const TileK tk = tile_of(rp, B, h);
     const int P = tk.P;
     bool over = false;
-    const double wsum = finish_potential_brick<K>(cov, partials + rp.brick_off * (int64_t)K * P * P * P, tk, rp.p,
+    const double wsum = finish_potential_brick<K, true>(cov, partials + rp.brick_off * (int64_t)K * P * P * P, tk, rp.p,
                                                   counts + (int64_t)K * rp.moff, V + (int64_t)K * rp.moff,
                                                   it.begin, over, nullptr);
     if (over)

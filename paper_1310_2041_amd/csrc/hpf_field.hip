@@ -139,8 +139,9 @@ constexpr int kFPThreads = 256;
 
 // One brick of the fused finish + potential: all threads of the workgroup
 // call it; it begins with a barrier (the previous brick's cover lists may
-// still be read) and returns this thread's field-energy terms.
-template <int K>
+// still be read) and returns this thread's field-energy terms. Without kSeam
+// no point may lie in more than two boxes along an axis.
+template <int K, bool kSeam>
 __device__ __forceinline__ double finish_potential_brick(Cover (&cov)[3][kTcMaxB],
                                                          const unsigned long long* __restrict__ partials,
                                                          const TileK& tk, const PotK& p,
@@ -176,19 +177,13 @@ __device__ __forceinline__ double finish_potential_brick(Cover (&cov)[3][kTcMaxB
             n[k] = counts[(int64_t)k * nm + dst];
             held |= n[k] != 0ull;
         }
-        if (cover2_ok(cx, cy, cz)) {
+        if (!kSeam || cover2_ok(cx, cy, cz)) {
             const Cover2 c2 = cover2(cx, cy, cz);
 #pragma unroll
             for (int k = 0; k < K; ++k)
                 n[k] += cover2_sum(partials, c2, (int64_t)k * P3);
         } else {
-            for (int a = 0; a < cz.n; ++a)
-                for (int b2 = 0; b2 < cy.n; ++b2)
-                    for (int c = 0; c < cx.n; ++c) {
-#pragma unroll
-                        for (int k = 0; k < K; ++k)
-                            n[k] += partials[cz.off[a] + cy.off[b2] + cx.off[c] + (int64_t)k * P3];
-                    }
+            add_covers<K>(partials, cx, cy, cz, P3, n);
         }
         // the counts are cleared where they held anything (the few points that beads
         // outside their boxes reached); the others are zero already
@@ -203,7 +198,7 @@ __device__ __forceinline__ double finish_potential_brick(Cover (&cov)[3][kTcMaxB
     return wsum;
 }
 
-template <int K>
+template <int K, bool kSeam>
 __global__ __launch_bounds__(kFPThreads) void k_finish_potential(const unsigned long long* __restrict__ partials,
                                                                  TileK tk, PotK p,
                                                                  unsigned long long* __restrict__ counts,
@@ -220,7 +215,7 @@ __global__ __launch_bounds__(kFPThreads) void k_finish_potential(const unsigned 
     double wsum = 0.0;
     bool over = false;
     for (int64_t brick = w.first; brick < w.end; brick += w.stride)
-        wsum += finish_potential_brick<K>(cov, partials, tk, p, counts, V, brick, over, present);
+        wsum += finish_potential_brick<K, kSeam>(cov, partials, tk, p, counts, V, brick, over, present);
     if (over)
         raise_flag(HPF_FLAG_OVERFLOW);
     if (w_part) {
@@ -238,8 +233,11 @@ static hpf_status_t launch_finish_potential_k(const unsigned long long* partials
     // one brick per workgroup where the partial slots allow it (the dispatcher then
     // balances uneven bricks), else bricks walked by HPF_NPART workgroups
     const int64_t nb = std::min<int64_t>(tk.ntiles, HPF_NPART);
-    hipLaunchKernelGGL(k_finish_potential<K>, dim3((unsigned)nb), dim3(kFPThreads), 0, s, partials, tk, p, counts, V,
-                       w_part, present);
+    // a mesh that is even enough takes the form without the seam's nine loads, which cost 20 of its
+    // 91 registers (K = 2): 64^3 points, 8.2 us without them and 8.5 with
+    const auto kernel = two_boxes_at_most(tk) ? k_finish_potential<K, false> : k_finish_potential<K, true>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kFPThreads), 0, s, partials, tk, p, counts, V, w_part,
+                       present);
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }
 

@@ -17,8 +17,8 @@
 //      starts (cell_start);
 //   4. per chunk the beads are placed in tag order: each wavefront takes a
 //      contiguous part of the chunk with its own row of running slots, and its
-//      lanes that share a key take consecutive slots. The permutation and its
-//      inverse are written together.
+//      lanes that share a key take consecutive slots;
+//   5. the permutation's inverse, in storage order.
 // No step needs a global atomic, and the result does not depend on the input
 // order. Finally one pass gathers the bead arrays and the renumbered bond table
 // into the output buffers.

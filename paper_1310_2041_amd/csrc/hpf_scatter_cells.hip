@@ -518,27 +518,29 @@ __device__ __forceinline__ bool deposit_global(const float3& r, int t, int K, co
 
 // The strays of n <= kTcThreads bricks, deposited by the whole workgroup; thread i < n brings the
 // bead range of brick i and reads the length of its list, so that the chain of reads is walked
-// once and not brick after brick. With parts > 1, every parts-th turn of each list from `part` on.
+// once and not brick after brick. Lengths and entries are held to the brick's range, so that a
+// buffer that another call writes meanwhile gives wrong counts and no wild access. With parts > 1, every parts-th turn of each list from `part` on.
 template <class Deposit>
 __device__ __forceinline__ void for_each_stray(const uint32_t* __restrict__ strays, int64_t n, int part, int parts,
                                                uint32_t first, uint32_t last, Deposit deposit)
 {
-    __shared__ uint32_t at[kTcThreads], len[kTcThreads];
-    __shared__ uint8_t whole[kTcThreads];
+    __shared__ uint32_t at[kTcThreads], len[kTcThreads], beads[kTcThreads];
     const int tid = threadIdx.x;
     bool any = false;
     if (tid < n) {
         at[tid] = first;
-        const uint32_t ns = first < last ? strays[last - 1] : 0u;
-        len[tid] = ns;
-        whole[tid] = ns == last - first;
-        any = ns != 0;
+        beads[tid] = first < last ? last - first : 0u;
+        len[tid] = first < last ? min(strays[last - 1], last - first) : 0u;
+        any = len[tid] != 0;
     }
     if (!__syncthreads_or(any))
         return;
     for (int64_t q = 0; q < n; ++q)
-        for (uint32_t i = part * kTcThreads + tid; i < len[q]; i += parts * kTcThreads)
-            deposit(q, whole[q] ? at[q] + i : strays[at[q] + i]);
+        for (uint32_t i = part * kTcThreads + tid; i < len[q]; i += parts * kTcThreads) {
+            const uint32_t p = len[q] == beads[q] ? at[q] + i : strays[at[q] + i];
+            if (p - at[q] < beads[q])
+                deposit(q, p);
+        }
 }
 
 // Workgroups of the stray pass, and how many share a brick's list when there are few bricks.

@@ -306,9 +306,9 @@ __global__ __launch_bounds__(4 * kWave) void k_sort_place(const unsigned long lo
                                                           const uint32_t* __restrict__ table,
                                                           int32_t* __restrict__ perm)
 {
-    extern __shared__ uint32_t slots[];
-    __shared__ uint32_t range[2];
+    extern __shared__ uint32_t slots[];                  // place_lds(nkeys, rows) bytes
     const int rows = (int)(blockDim.x / kWave);
+    uint32_t* range = slots + (size_t)rows * nkeys;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int64_t c = blockIdx.x;
     const int64_t part = S / rows;
@@ -981,15 +981,24 @@ static void launch_permute(int64_t N, const int32_t* perm, const int32_t* inv, c
                        T_out, tag_out, bonds_out);
 }
 
-// Wavefronts of a placement workgroup: as many slot rows of nkeys u32 as give the most
-// wavefronts per CU in its 160 KiB of LDS (4 up to 10,240 keys, then 2 or 1; a row of the
-// largest key count is 144 KiB).
+// LDS of a placement workgroup: its slot rows of nkeys u32 and the two ends of its key range.
+// The kernel has none besides, so this is all that a launch asks for.
+static constexpr size_t place_lds(uint32_t nkeys, int rows)
+{
+    return sizeof(uint32_t) * ((size_t)nkeys * rows + 2);
+}
+
+// Wavefronts of a placement workgroup: 4, 2 or 1, whichever number of slot rows packs the most
+// rows into a CU's LDS, and the larger of equals. A number whose workgroup does not fit is out:
+// 4 above 10,239 keys, 2 above 20,479. One row fits at every key count.
+static_assert(place_lds(kMaxSortKeys, 1) <= kLdsPerCu, "one slot row of the largest key count fits a CU");
+
 static int place_rows(uint32_t nkeys)
 {
-    const size_t lds = 160 * 1024, row = sizeof(uint32_t) * (size_t)nkeys;
+    const size_t row = sizeof(uint32_t) * (size_t)nkeys;
     int best = 1;
     for (int rows = 2; rows <= 4; rows *= 2)
-        if (rows * (lds / (row * rows)) >= best * (lds / (row * best)))
+        if (place_lds(nkeys, rows) <= kLdsPerCu && rows * (kLdsPerCu / (row * rows)) >= best * (kLdsPerCu / (row * best)))
             best = rows;
     return best;
 }
@@ -1015,7 +1024,7 @@ hpf_status_t run_sort(const SortPlan& pl, Keyer keyer, int64_t N, const float* R
     }
     const size_t smem = sizeof(uint32_t) * nk;
     const int rows = place_rows(nk);
-    const size_t smem_place = smem * rows;
+    const size_t smem_place = place_lds(nk, rows);
     if ((smem > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(k_sort_hist),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) ||
         (smem_place > 65536 &&

@@ -81,14 +81,36 @@ __global__ __launch_bounds__(kTcThreads) void k_batch_scatter_bricks(const RepK*
                        partials + (rp.brick_off + it.begin) * (int64_t)K * P * P * P, strays);
 }
 
+// Bead range of brick item b.
+__device__ __forceinline__ void item_range(const RepK* __restrict__ reps, const ItemK* __restrict__ items,
+                                           const uint32_t* __restrict__ cell_start, int64_t b, uint32_t& first,
+                                           uint32_t& last)
+{
+    const ItemK it = items[b];
+    const uint32_t* range = cell_start + reps[it.rep].key_base + it.begin;
+    first = range[0];
+    last = range[1];
+}
+
+// (with strays, kFindBlocks workgroups before those of the bricks, as in k_scatter_sum)
 template <bool kAdd>
 __global__ __launch_bounds__(kSumThreads) void k_batch_scatter_sum(const RepK* __restrict__ reps,
                                                            const ItemK* __restrict__ items, int B, int h,
-                                                           int K,
+                                                           int K, int64_t Ntot,
+                                                           const uint32_t* __restrict__ cell_start,
+                                                           uint32_t* __restrict__ strays,
                                                            const unsigned long long* __restrict__ partials,
                                                            unsigned long long* __restrict__ counts)
 {
-    const int64_t li = xcd_block(blockIdx.x, gridDim.x);
+    const int skip = strays ? kFindBlocks : 0;
+    if ((int)blockIdx.x < skip) {
+        if (blockIdx.x == 0)
+            find_long_lists(strays, Ntot, gridDim.x - skip, [&](int64_t b, uint32_t& first, uint32_t& last) {
+                item_range(reps, items, cell_start, b, first, last);
+            });
+        return;
+    }
+    const int64_t li = xcd_block(blockIdx.x - skip, gridDim.x - skip);
     const ItemK it = items[li];
     const RepK& rp = reps[it.rep];
     const TileK tk = tile_of(rp, B, h);
@@ -135,25 +157,23 @@ struct RepKeyer {
 // with global atomics.
 __global__ __launch_bounds__(kTcThreads) void k_batch_scatter_strays(const RepK* __restrict__ reps, int nrep,
                                                                      const ItemK* __restrict__ items, int64_t nitems,
-                                                                     int K, const float3* __restrict__ R,
+                                                                     int64_t Ntot, int K,
+                                                                     const float3* __restrict__ R,
                                                                      const uint8_t* __restrict__ T,
                                                                      const uint32_t* __restrict__ cell_start,
                                                                      const uint32_t* __restrict__ strays,
                                                                      unsigned long long* __restrict__ counts)
 {
     bool bad = false;
-    const int64_t per = (nitems + gridDim.x - 1) / gridDim.x;
-    const int64_t end = min(nitems, ((int64_t)blockIdx.x + 1) * per);
-    for (int64_t b0 = (int64_t)blockIdx.x * per; b0 < end; b0 += kTcThreads) {
-        const ItemK it = items[min(b0 + threadIdx.x, nitems - 1)];
-        const uint32_t* range = cell_start + reps[it.rep].key_base + it.begin;
-        for_each_stray(strays, min((int64_t)kTcThreads, end - b0), 0, 1, range[0], range[1],
-                       [&](int64_t q, uint32_t p) {
-                           const RepK& rp = reps[items[b0 + q].rep];
-                           bad |= !deposit_global(R[p], T[p], K, rp.m, counts + (int64_t)K * rp.moff);
-                       });
-        __syncthreads();
-    }
+    auto deposit = [&](const RepK& rp, uint32_t p) {
+        bad |= !deposit_global(R[p], T[p], K, rp.m, counts + (int64_t)K * rp.moff);
+    };
+    deposit_own_lists(strays, nitems, blockIdx.x, gridDim.x, 0, 1,
+                      [&](int64_t b, uint32_t& first, uint32_t& last) {
+                          item_range(reps, items, cell_start, b, first, last);
+                      },
+                      [&](int64_t b, uint32_t p) { deposit(reps[items[b].rep], p); });
+    deposit_shared_lists(strays, Ntot, [&](uint32_t p) { deposit(reps[find_rep(reps, nrep, p)], p); });
     // unbinned tails: replica r's beads with key key_base_r + NK_r
     for (int r = blockIdx.x; r < nrep; r += gridDim.x) {
         const RepK& rp = reps[r];
@@ -685,6 +705,23 @@ static hpf_status_t batch_potential(hpf_batch* b, int K, unsigned long long* cou
     return HPF_OK;
 }
 
+// The second and third pass of the batch's cell scatter (a prime number of workgroups takes the
+// lists, as in the single systems').
+constexpr int kBatchStrayGroups = 251;
+
+static void launch_batch_sum_and_strays(const hpf_batch* b, int B, int h, int K, const float3* R, const uint8_t* T,
+                                        const uint32_t* cs, uint32_t* strays, const unsigned long long* partials,
+                                        unsigned long long* counts, hipStream_t s)
+{
+    const RepK* reps = b->at<RepK>(b->L.off_reps);
+    const ItemK* items = b->at<ItemK>(b->L.off_brick_items);
+    hipLaunchKernelGGL(k_batch_scatter_sum<false>, dim3((unsigned)b->n_brick_items + kFindBlocks),
+                       sum_block(b->n_brick_items), 0, s, reps, items, B, h, K, b->L.Ntot, cs, strays, partials,
+                       counts);
+    hipLaunchKernelGGL(k_batch_scatter_strays, dim3(kBatchStrayGroups), dim3(kTcThreads), 0, s, reps, b->nrep, items,
+                       b->n_brick_items, b->L.Ntot, K, R, T, cs, strays, counts);
+}
+
 static hpf_status_t batch_fields(hpf_batch* b, bool report, hipStream_t s)
 {
     const BatchLayout& L = b->L;
@@ -724,10 +761,7 @@ static hpf_status_t batch_fields(hpf_batch* b, bool report, hipStream_t s)
             return HPF_EINVAL;
         hipLaunchKernelGGL(k_batch_scatter_bricks, dim3((unsigned)b->n_brick_items), dim3(kTcThreads), smem, s, reps,
                            b->at<ItemK>(L.off_brick_items), B, h, K, R, T, cs, partials, strays);
-        hipLaunchKernelGGL(k_batch_scatter_sum<false>, dim3((unsigned)b->n_brick_items), sum_block(b->n_brick_items),
-                           0, s, reps, b->at<ItemK>(L.off_brick_items), B, h, K, partials, counts);
-        hipLaunchKernelGGL(k_batch_scatter_strays, dim3(256), dim3(kTcThreads), 0, s, reps, b->nrep,
-                           b->at<ItemK>(L.off_brick_items), b->n_brick_items, K, R, T, cs, strays, counts);
+        launch_batch_sum_and_strays(b, B, h, K, R, T, cs, strays, partials, counts, s);
         if (hpf_status_t st = batch_potential(b, K, counts, w, s))
             return st;
         b->w_bricks = false;
@@ -1010,7 +1044,8 @@ hpf_status_t hpf_batch_density(hpf_batch_t* b, uint64_t* counts_out, void* strea
                            hipMemcpyDeviceToDevice, s) != hipSuccess)
             return HPF_EHIP;
         hipLaunchKernelGGL(k_batch_scatter_sum<true>, dim3((unsigned)b->n_brick_items), sum_block(b->n_brick_items),
-                           0, s, reps, bi, B, h, K, partials, out);
+                           0, s, reps, bi, B, h, K, (int64_t)0, (const uint32_t*)nullptr, (uint32_t*)nullptr,
+                           partials, out);
     } else {
         const size_t smem = scatter_cells_smem(K, P);
         if (smem > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(k_batch_scatter_bricks),
@@ -1022,10 +1057,7 @@ hpf_status_t hpf_batch_density(hpf_batch_t* b, uint64_t* counts_out, void* strea
         const uint32_t* cs = b->at<uint32_t>(L.off_start);
         hipLaunchKernelGGL(k_batch_scatter_bricks, dim3((unsigned)b->n_brick_items), dim3(kTcThreads), smem, s, reps,
                            bi, B, h, K, R, T, cs, partials, strays);
-        hipLaunchKernelGGL(k_batch_scatter_sum<false>, dim3((unsigned)b->n_brick_items), sum_block(b->n_brick_items),
-                           0, s, reps, bi, B, h, K, partials, out);
-        hipLaunchKernelGGL(k_batch_scatter_strays, dim3(256), dim3(kTcThreads), 0, s, reps, b->nrep, bi,
-                           b->n_brick_items, K, R, T, cs, strays, out);
+        launch_batch_sum_and_strays(b, B, h, K, R, T, cs, strays, partials, out, s);
     }
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }

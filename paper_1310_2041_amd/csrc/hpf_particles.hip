@@ -1568,7 +1568,7 @@ hpf_status_t launch_scatter_finish(const unsigned long long* partials, const Til
                                    unsigned long long* counts, hipStream_t s)
 {
     hipLaunchKernelGGL(k_scatter_sum<true>, dim3((unsigned)tk.ntiles), sum_block(tk.ntiles), 0, s, partials, tk, K,
-                       counts);
+                       (int64_t)0, (const uint32_t*)nullptr, (uint32_t*)nullptr, counts);
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }
 

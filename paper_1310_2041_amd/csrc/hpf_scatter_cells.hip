@@ -474,12 +474,91 @@ constexpr int64_t kSumFewBricks = 2048;
 
 static dim3 sum_block(int64_t ntiles) { return dim3(ntiles < kSumFewBricks ? kSumThreads : kSumThreads / 2); }
 
+// A brick's list of strays: its bead range and the list's length. Lengths are held to the
+// range, so that a buffer that another call writes meanwhile gives wrong counts and no wild access.
+struct StrayList {
+    uint32_t at, beads, len;
+    bool shared;
+};
+
+constexpr uint32_t kSharedList = 1u << 31;           // in a list's length: all workgroups take part
+constexpr uint32_t kLongList = 2048;                 // strays above which a list is shared
+constexpr uint32_t kLongLists = 31;                  // as many as the 64 entries behind the lists hold
+
+__device__ __forceinline__ StrayList stray_list(const uint32_t* __restrict__ strays, uint32_t first, uint32_t last)
+{
+    StrayList l{first, 0u, 0u, false};
+    if (first < last) {
+        const uint32_t n = strays[last - 1];
+        l.beads = last - first;
+        l.len = min(n & ~kSharedList, l.beads);
+        l.shared = (n & kSharedList) != 0;
+    }
+    return l;
+}
+
+// The box sums' launch ends before the strays' begins, so it finds the long lists for it, in one
+// workgroup beside those of the bricks: marks them, and writes their number and ranges behind the
+// lists (N entries). range(b, first, last) gives the bead range of list b < n. While a list was
+// its brick's workgroup's alone, 1M beads that had all left one brick took 17.5 ms, and 3M in a
+// droplet of 40^3 cells of 192^3 4.0; now 1.9 and 1.4.
+constexpr int kScanLists = 4;
+
+template <class Range>
+__device__ __forceinline__ void find_long_lists(uint32_t* __restrict__ strays, int64_t N, int64_t n, Range range)
+{
+    __shared__ uint32_t found;
+    if (threadIdx.x == 0)
+        found = 0u;
+    __syncthreads();
+    uint32_t* out = strays + N;
+    for (int64_t b0 = threadIdx.x; b0 < n; b0 += kScanLists * (int64_t)blockDim.x) {
+        uint32_t first[kScanLists], last[kScanLists];
+        StrayList l[kScanLists];
+#pragma unroll
+        for (int u = 0; u < kScanLists; ++u)
+            range(min(b0 + u * (int64_t)blockDim.x, n - 1), first[u], last[u]);
+#pragma unroll
+        for (int u = 0; u < kScanLists; ++u)
+            l[u] = stray_list(strays, first[u], last[u]);
+#pragma unroll
+        for (int u = 0; u < kScanLists; ++u) {
+            if (b0 + u * (int64_t)blockDim.x >= n || l[u].len <= kLongList)
+                continue;
+            const uint32_t slot = atomicAdd(&found, 1u);
+            if (slot < kLongLists) {
+                out[1 + 2 * slot] = first[u];
+                out[2 + 2 * slot] = last[u];
+                strays[last[u] - 1] = l[u].len | kSharedList;
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        out[0] = min(found, kLongLists);
+}
+
+// With strays, the launch has kFindBlocks workgroups before those of the bricks (a whole turn of
+// the XCDs, so that a brick's stays on its own); the first finds the long lists.
+constexpr int kFindBlocks = 8;
+
 template <bool kAdd>
 __global__ __launch_bounds__(kSumThreads) void k_scatter_sum(const unsigned long long* __restrict__ partials,
-                                                     TileK tk, int K,
+                                                     TileK tk, int K, int64_t N,
+                                                     const uint32_t* __restrict__ cell_start,
+                                                     uint32_t* __restrict__ strays,
                                                      unsigned long long* __restrict__ counts)
 {
-    scatter_sum_body<kAdd>(partials, tk, K, xcd_block(blockIdx.x, gridDim.x), counts);
+    const int skip = strays ? kFindBlocks : 0;
+    if ((int)blockIdx.x < skip) {
+        if (blockIdx.x == 0)
+            find_long_lists(strays, N, tk.ntiles, [&](int64_t b, uint32_t& first, uint32_t& last) {
+                first = cell_start[b];
+                last = cell_start[b + 1];
+            });
+        return;
+    }
+    scatter_sum_body<kAdd>(partials, tk, K, xcd_block(blockIdx.x - skip, gridDim.x - skip), counts);
 }
 
 __device__ __forceinline__ void atomic_add_u64_agent(unsigned long long* p, unsigned long long v)
@@ -516,24 +595,21 @@ __device__ __forceinline__ bool deposit_global(const float3& r, int t, int K, co
     return true;
 }
 
-// The strays of n <= kTcThreads bricks, deposited by the whole workgroup; thread i < n brings the
-// bead range of brick i and reads the length of its list, so that the chain of reads is walked
-// once and not brick after brick. Lengths and entries are held to the brick's range, so that a
-// buffer that another call writes meanwhile gives wrong counts and no wild access. With parts > 1, every parts-th turn of each list from `part` on.
+// The strays of n <= kTcThreads lists, deposited by the whole workgroup; thread i < n brings
+// list i (read by each thread for its own, so that the chain of reads is walked once and not
+// list after list). With parts > 1, every parts-th turn of each list from `part` on.
 template <class Deposit>
-__device__ __forceinline__ void for_each_stray(const uint32_t* __restrict__ strays, int64_t n, int part, int parts,
-                                               uint32_t first, uint32_t last, Deposit deposit)
+__device__ __forceinline__ void deposit_lists(const uint32_t* __restrict__ strays, int64_t n, int part, int parts,
+                                              const StrayList& mine, Deposit deposit)
 {
     __shared__ uint32_t at[kTcThreads], len[kTcThreads], beads[kTcThreads];
     const int tid = threadIdx.x;
-    bool any = false;
     if (tid < n) {
-        at[tid] = first;
-        beads[tid] = first < last ? last - first : 0u;
-        len[tid] = first < last ? min(strays[last - 1], last - first) : 0u;
-        any = len[tid] != 0;
+        at[tid] = mine.at;
+        beads[tid] = mine.beads;
+        len[tid] = mine.len;
     }
-    if (!__syncthreads_or(any))
+    if (!__syncthreads_or(tid < n && mine.len != 0))
         return;
     for (int64_t q = 0; q < n; ++q)
         for (uint32_t i = part * kTcThreads + tid; i < len[q]; i += parts * kTcThreads) {
@@ -543,8 +619,43 @@ __device__ __forceinline__ void for_each_stray(const uint32_t* __restrict__ stra
         }
 }
 
-// Workgroups of the stray pass, and how many share a brick's list when there are few bricks.
+// The lists of this workgroup's bricks: list g, g + groups, ... of n (range as in
+// find_long_lists), but for the shared ones; deposit(list, bead).
+template <class Range, class Deposit>
+__device__ __forceinline__ void deposit_own_lists(const uint32_t* __restrict__ strays, int64_t n, int64_t g,
+                                                  int64_t groups, int part, int parts, Range range, Deposit deposit)
+{
+    for (int64_t b0 = g; b0 < n; b0 += groups * kTcThreads) {
+        uint32_t first, last;
+        range(min(b0 + groups * threadIdx.x, n - 1), first, last);
+        StrayList l = stray_list(strays, first, last);
+        if (l.shared)
+            l.len = 0u;
+        const int64_t here = min((int64_t)kTcThreads, (n - b0 + groups - 1) / groups);
+        deposit_lists(strays, here, part, parts, l, [&](int64_t q, uint32_t p) { deposit(b0 + groups * q, p); });
+        __syncthreads();
+    }
+}
+
+// The shared lists, by all workgroups.
+template <class Deposit>
+__device__ __forceinline__ void deposit_shared_lists(const uint32_t* __restrict__ strays, int64_t N, Deposit deposit)
+{
+    const uint32_t* in = strays + N;
+    const uint32_t n = min(in[0], kLongLists);
+    if (n == 0)                          // uniform
+        return;
+    const uint32_t q = min(threadIdx.x, n - 1);
+    const uint32_t last = min((int64_t)in[2 + 2 * q], N), first = min(in[1 + 2 * q], last);
+    deposit_lists(strays, n, blockIdx.x, gridDim.x, stray_list(strays, first, last),
+                  [&](int64_t, uint32_t p) { deposit(p); });
+}
+
+// Workgroups of the stray pass: up to kStrayBlocks bricks get one or several each. With more, a
+// workgroup takes every kStrayGroups-th brick, so that neighbouring bricks, which tend to be as
+// full as each other, go to different ones (a prime, which no mesh's strides have for a factor).
 constexpr int kStrayBlocks = 512;
+constexpr int kStrayGroups = 509;
 
 // Global-atomic deposit of the stray beads and of the beads the sort could not
 // bin (storage indices [cell_start[NK], N)).
@@ -556,16 +667,14 @@ __global__ __launch_bounds__(kTcThreads) void k_scatter_strays(const float3* __r
                                                                unsigned long long* __restrict__ counts)
 {
     bool bad = false;
-    const int64_t groups = gridDim.x / parts, g = blockIdx.x / parts;
-    const int64_t per = (NK + groups - 1) / groups;
-    const int64_t end = min((int64_t)NK, (g + 1) * per);
-    for (int64_t b0 = g * per; b0 < end; b0 += kTcThreads) {
-        const int64_t b = min(b0 + threadIdx.x, (int64_t)NK - 1);
-        for_each_stray(strays, min((int64_t)kTcThreads, end - b0), blockIdx.x % parts, parts, cell_start[b],
-                       cell_start[b + 1],
-                       [&](int64_t, uint32_t p) { bad |= !deposit_global(R[p], T[p], K, m, counts); });
-        __syncthreads();
-    }
+    auto deposit = [&](uint32_t p) { bad |= !deposit_global(R[p], T[p], K, m, counts); };
+    deposit_own_lists(strays, NK, blockIdx.x / parts, gridDim.x / parts, blockIdx.x % parts, parts,
+                      [&](int64_t b, uint32_t& first, uint32_t& last) {
+                          first = cell_start[b];
+                          last = cell_start[b + 1];
+                      },
+                      [&](int64_t, uint32_t p) { deposit(p); });
+    deposit_shared_lists(strays, N, deposit);
     for (int64_t p = (int64_t)cell_start[NK] + (int64_t)blockIdx.x * kTcThreads + threadIdx.x; p < N;
          p += (int64_t)gridDim.x * kTcThreads)
         bad |= !deposit_global(R[p], T[p], K, m, counts);
@@ -605,11 +714,12 @@ hpf_status_t launch_scatter_cells(const float* R, const uint8_t* T, int64_t N, c
                                  : go(k_scatter_bricks<kScBrickThreads>, kScBrickThreads);
     if (st != HPF_OK)
         return st;
-    hipLaunchKernelGGL(k_scatter_sum<false>, dim3((unsigned)tk.ntiles), sum_block(tk.ntiles), 0, s, partials, tk, K,
-                       c);
+    hipLaunchKernelGGL(k_scatter_sum<false>, dim3((unsigned)tk.ntiles + kFindBlocks), sum_block(tk.ntiles), 0, s,
+                       partials, tk, K, N, cell_start, strays, c);
     const int parts = (int)std::max<int64_t>(1, kStrayBlocks / tk.NK);
-    hipLaunchKernelGGL(k_scatter_strays, dim3(kStrayBlocks / parts * parts), dim3(kTcThreads), 0, s, Rp, T, N, K,
-                       tk.m, tk.NK, parts, cell_start, strays, c);
+    const int blocks = tk.NK <= kStrayBlocks ? kStrayBlocks / parts * parts : kStrayGroups;
+    hipLaunchKernelGGL(k_scatter_strays, dim3(blocks), dim3(kTcThreads), 0, s, Rp, T, N, K, tk.m, tk.NK, parts,
+                       cell_start, strays, c);
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }
 

@@ -49,11 +49,14 @@ def auto_brick(M, K: int, halo: int) -> int:
 
 
 def _on(stream):
-    """Context in which torch enqueues on `stream` (None: the current stream)."""
+    """Context in which torch enqueues on `stream` (None: the current stream; a stream, or its
+    handle as a number, 0 being the default stream)."""
     if stream is None:
         return contextlib.nullcontext()
-    return torch.cuda.stream(stream if isinstance(stream, torch.cuda.Stream) else
-                             torch.cuda.ExternalStream(int(stream)))
+    if not isinstance(stream, torch.cuda.Stream):
+        # ExternalStream(0) is a new stream, not the default one
+        stream = torch.cuda.ExternalStream(int(stream)) if int(stream) else torch.cuda.default_stream()
+    return torch.cuda.stream(stream)
 
 
 class HpfState:

@@ -1,0 +1,45 @@
+"""GPU: what HpfState.step keeps between steps besides the beads -- the streams it enqueues on and
+its mesh counts -- in the states that a program can leave it in."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_1310_2041_amd import engine, hpf  # noqa: E402
+from synth import workloads as wl  # noqa: E402
+
+
+def _states(n=2, **kw):
+    s = wl.small_system(300, 10, (15.0, 17.5, 16.1), (15, 17, 16), seed=3, n_solvent=700)
+    out = []
+    for _ in range(n):
+        st = engine.HpfState.from_system(s, **kw)
+        st.start(sort=True)
+        out.append(st)
+    return out
+
+
+def _assert_same(a, b):
+    torch.cuda.synchronize()
+    for x, y in zip(a.host_beads(), b.host_beads()):
+        assert np.array_equal(x, y)
+
+
+def test_stream_handle_zero_is_the_default_stream():
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side), engine._on(0):
+        assert torch.cuda.current_stream().cuda_stream == 0
+    with engine._on(side.cuda_stream):
+        assert torch.cuda.current_stream().cuda_stream == side.cuda_stream
+    a, b = _states()
+    for st in (a, b):
+        st.set_thermostat(5.0, seed=4)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        a.run(6, sort_every=4, stream=0)
+    b.run(6, sort_every=4)
+    _assert_same(a, b)

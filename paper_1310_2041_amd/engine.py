@@ -106,6 +106,9 @@ class HpfState:
             raise ValueError("composition_list needs field_every=1 and the centred stencil")
         self.strays = None             # step()'s counts of the beads outside their boxes
         self.density_pending = False   # partial boxes + counts hold the deposit of the current R
+        # No call of this object has left anything in counts. step() deposits past them only then:
+        # else it takes the calls that overwrite and clear them, as a pass that follows expects.
+        self.counts_clear = True
         # when True, the fused passes also store the total force at x_n into F (F_out)
         self.keep_force = False
         # Andersen thermostat (set_thermostat): (p, kT, seed) and the device time level
@@ -204,7 +207,7 @@ class HpfState:
         back in step with the device."""
         d = {k: getattr(self, k) for k in self._SWAPPED}
         d.update(steps_done=self.steps_done, density_pending=self.density_pending,
-                 sorted=self.sorted)
+                 counts_clear=self.counts_clear, sorted=self.sorted)
         return d
 
     def restore(self, d: dict):
@@ -249,6 +252,7 @@ class HpfState:
     def scatter(self, stream=None):
         """Density counts: cell-list owner tiles when sorted, else the generic scatter."""
         self.density_pending = False
+        self.counts_clear = False
         if self.sorted and self.cells_ok:
             hpf.hpf_density_scatter_cells(self.R, self.T, self.mesh, self.K, self.cell_start, self.B,
                                           self.halo, self.counts, self.scatter_work, stream)
@@ -265,6 +269,7 @@ class HpfState:
         hpf.hpf_field_potential(self.counts, self.mesh, self.field, self.V,
                                 self.rows()[0] if (report or self.field_every > 1) else None,
                                 stream, present=self.present)
+        self.counts_clear = True
         if self.stencil == "centred":
             hpf.hpf_field_gradient(self.V, self.mesh, self.K, self.G, stream, present=self.present)
 
@@ -297,7 +302,8 @@ class HpfState:
 
     def step(self, report=False, sort=False, stream=None):
         rebuild = self.rebuilds_field(self.steps_done + 1)
-        if rebuild and not sort and not self.density_pending and self._strays_ready(stream):
+        if (rebuild and not sort and self.counts_clear and not self.density_pending
+                and self._strays_ready(stream)):
             # the half step deposits the new positions; the boxes and the beads outside them
             # (in a counts buffer of its own, zero between steps) become V in one pass
             hpf.hpf_verlet_scatter(self.R, self.Vel, self.F, self.T, self.dt, self.box, self.mesh, self.K,
@@ -395,6 +401,7 @@ class HpfState:
         else:
             self.scatter(stream)
             hpf.hpf_field_potential(self.counts, self.mesh, self.field, self.V, w, stream, present=self.present)
+        self.counts_clear = True
 
     def uses_scatter_advance(self) -> bool:
         return self.advance_mode == "scatter" and self.sorted and self.cells_ok
@@ -411,6 +418,7 @@ class HpfState:
         th = self.thermostat()
         self.density_pending = False
         if deposit and self.uses_scatter_advance():
+            self.counts_clear = False
             hpf.hpf_advance_scatter(self.R, self.R2, self.Vel, self.T, self.mesh, self.K, self.G, bonds,
                                     self.k_bond, self.r0, self.box, self.dt, self.cell_start, self.B,
                                     self.halo, self.counts, self.scatter_work, F_out=F_out, e_part=e_part,

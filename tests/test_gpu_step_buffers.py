@@ -43,3 +43,33 @@ def test_stream_handle_zero_is_the_default_stream():
         a.run(6, sort_every=4, stream=0)
     b.run(6, sort_every=4)
     _assert_same(a, b)
+
+
+@pytest.mark.parametrize("left_by", ["scatter", "prime"])
+def test_step_leaves_no_counts_behind(left_by):
+    """Counts that a density read-out or a deposit never finished left in the buffer are gone
+    after a step that rebuilds the field, so that a depositing pass may follow."""
+    a, b = _states()
+    if left_by == "scatter":
+        a.scatter()
+        assert not a.counts_clear and bool(a.counts.any())
+    else:
+        for st in (a, b):                          # strays: the halo is one cell, the beads move eight
+            st.prime()
+            st.Vel *= 200.0
+            st.step_fused()
+        assert bool(a.counts.any())
+        for st in (a, b):
+            st.density_pending = False
+            st.Vel *= 0.005
+        b.rebuild()
+    a.step(report=True)
+    b.step(report=True)
+    assert not bool(a.counts.any()) and a.counts_clear
+    for st in (a, b):
+        st.prime()
+        st.advance()                               # deposits, from the last gradient
+        st.step_fused(report=True)
+        st.run(2)
+    _assert_same(a, b)
+    assert a.energies()["W"] == b.energies()["W"]

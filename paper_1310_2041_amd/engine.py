@@ -104,7 +104,10 @@ class HpfState:
         # field is rebuilt at every force evaluation and gathered with the deposit's weights.
         if composition_list and (self.field_every != 1 or stencil != "centred"):
             raise ValueError("composition_list needs field_every=1 and the centred stencil")
-        self.strays = None             # step()'s counts of the beads outside their boxes
+        # step()'s counts of the beads outside their boxes (as many bytes as counts), made by the
+        # first step that takes them; without the memory for them step() goes on without
+        self.strays = None
+        self.strays_refused = False
         self.density_pending = False   # partial boxes + counts hold the deposit of the current R
         # No call of this object has left anything in counts. step() deposits past them only then:
         # else it takes the calls that overwrite and clear them, as a pass that follows expects.
@@ -341,13 +344,17 @@ class HpfState:
     def _strays_ready(self, stream=None) -> bool:
         """Whether step() may deposit in its half step: cell-sorted, and the counts buffer of the
         beads outside their boxes exists (made on the step's stream at the first such step that
-        is not being captured)."""
+        is not being captured; a graph whose first step is the state's first holds the separate
+        scatter in it)."""
         if not (self.sorted and self.cells_ok):
             return False
-        if self.strays is None:
+        if self.strays is None and not self.strays_refused:
             with _on(stream):
                 if not torch.cuda.is_current_stream_capturing():
-                    self.strays = torch.zeros((self.K, self.nm), dtype=torch.int64, device=self.R.device)
+                    try:
+                        self.strays = torch.zeros((self.K, self.nm), dtype=torch.int64, device=self.R.device)
+                    except torch.OutOfMemoryError:
+                        self.strays_refused = True
         return self.strays is not None
 
     def _advance_time_level(self, stream=None):

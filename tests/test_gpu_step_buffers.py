@@ -73,3 +73,19 @@ def test_step_leaves_no_counts_behind(left_by):
         st.run(2)
     _assert_same(a, b)
     assert a.energies()["W"] == b.energies()["W"]
+
+
+def test_step_goes_on_without_memory_for_its_strays(monkeypatch):
+    a, b = _states()
+    tried = []
+
+    def no_memory(*args, **kw):
+        tried.append(args)
+        raise torch.OutOfMemoryError("no memory")
+
+    with monkeypatch.context() as m:
+        m.setattr(engine.torch, "zeros", no_memory)
+        a.run(5, sort_every=3)
+    b.run(5, sort_every=3)
+    assert len(tried) == 1 and a.strays is None and b.strays is not None
+    _assert_same(a, b)

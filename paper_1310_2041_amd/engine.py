@@ -108,6 +108,7 @@ class HpfState:
         # first step that takes them; without the memory for them step() goes on without
         self.strays = None
         self.strays_refused = False
+        self.strays_clear = True       # False from their deposit until the potential has taken them
         self.density_pending = False   # partial boxes + counts hold the deposit of the current R
         # No call of this object has left anything in counts. step() deposits past them only then:
         # else it takes the calls that overwrite and clear them, as a pass that follows expects.
@@ -309,12 +310,14 @@ class HpfState:
                 and self._strays_ready(stream)):
             # the half step deposits the new positions; the boxes and the beads outside them
             # (in a counts buffer of its own, zero between steps) become V in one pass
+            self.strays_clear = False
             hpf.hpf_verlet_scatter(self.R, self.Vel, self.F, self.T, self.dt, self.box, self.mesh, self.K,
                                    self.cell_start, self.B, self.halo, self.strays, self.scatter_work, stream=stream)
             hpf.hpf_field_potential_cells(self.strays, self.N, self.mesh, self.field, self.B, self.halo,
                                           self.scatter_work, self.V,
                                           self.rows()[0] if (report or self.field_every > 1) else None, stream,
                                           present=self.present)
+            self.strays_clear = True
             if self.stencil == "centred":
                 hpf.hpf_field_gradient(self.V, self.mesh, self.K, self.G, stream, present=self.present)
         else:
@@ -355,6 +358,10 @@ class HpfState:
                         self.strays = torch.zeros((self.K, self.nm), dtype=torch.int64, device=self.R.device)
                     except torch.OutOfMemoryError:
                         self.strays_refused = True
+        if not self.strays_clear:      # a step was broken off after its deposit
+            with _on(stream):
+                self.strays.zero_()
+            self.strays_clear = True
         return self.strays is not None
 
     def _advance_time_level(self, stream=None):

@@ -89,3 +89,27 @@ def test_step_goes_on_without_memory_for_its_strays(monkeypatch):
     b.run(5, sort_every=3)
     assert len(tried) == 1 and a.strays is None and b.strays is not None
     _assert_same(a, b)
+
+
+def test_step_after_one_that_was_broken_off(monkeypatch):
+    """The calls of a step raise after its deposit; the program starts again from the positions
+    it is left with, as it could when a step's scatter overwrote what an earlier one had left."""
+    a, b = _states()
+    for st in (a, b):
+        st.run(3, sort_every=0)
+        st.Vel *= 200.0                            # strays: the halo is one cell, the beads move eight
+    with monkeypatch.context() as m:
+        def broken(*args, **kw):
+            raise RuntimeError("broken off")
+
+        m.setattr(hpf, "hpf_field_potential_cells", broken)
+        with pytest.raises(RuntimeError, match="broken off"):
+            a.step()
+    assert bool(a.strays.any())
+    hpf.verlet_step(b.R, b.Vel, b.F, b.dt, b.box, 1)
+    for st in (a, b):
+        st.Vel *= 0.005
+        st.start(sort=False)
+        st.run(4, sort_every=0)
+    assert not bool(a.strays.any())
+    _assert_same(a, b)

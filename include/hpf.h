@@ -507,7 +507,9 @@ hpf_status_t hpf_reduce_partials(const double* part, int32_t ncomp, double* out,
  * tag_in       a permutation of [0, N) (the beads' original indices); NULL
  *              uses the input index. A tag outside [0, N) or a repeated tag
  *              sets HPF_FLAG_SORT_ORDER; the output is then not a valid
- *              permutation (every index written stays inside [0, N)).
+ *              permutation (every index written stays inside [0, N)): one bead
+ *              of each valid tag is placed, the slots after them keep the
+ *              beads that stood there, and partners left out become -1.
  * cell_start   nullable uint32[NK + 2] device: cell_start[k] = index of the
  *              first bead with key >= k, i.e. brick k's beads are
  *              [cell_start[k], cell_start[k+1]); cell_start[NK] = number of
@@ -541,7 +543,8 @@ hpf_status_t hpf_sort_by_cell(const hpf_mesh_t* mesh, int32_t B, int64_t N,
  * work            as for hpf_sort_by_cell (hpf_sort_workspace_bytes).
  * If the input is not in an earlier sort's order (a key range out of tag
  * order), HPF_FLAG_SORT_ORDER is set and the output, while a set of valid
- * indices, is not the sorted order.
+ * indices, is not the sorted order; a slot that no bead was placed in keeps the
+ * bead that stood there.
  * ------------------------------------------------------------------------- */
 hpf_status_t hpf_resort_by_cell(const hpf_mesh_t* mesh, int32_t B, int64_t N, const float* R_in,
                                 const float* Vel_in, const uint8_t* T_in, const int32_t* tag_in,

@@ -57,10 +57,25 @@ __global__ __launch_bounds__(kSortThreads) void k_fill_u32(uint32_t* __restrict_
 
 // ------------------------------------------------------------ scan (u32) --
 
+// A broken permutation leaves beads out, which the placement gives no slot, and as many slots
+// at the end: perm and inv are -1 there, so that no output depends on what the workspace held.
+// (By one workgroup, the first to know: slow, but free where nothing is broken.)
+__device__ __forceinline__ void clear_if_broken(uint32_t placed, int64_t N, int32_t* __restrict__ perm,
+                                                int32_t* __restrict__ inv)
+{
+    if (placed < N)
+        for (int64_t i = threadIdx.x; i < N; i += kScanThreads) {
+            inv[i] = -1;
+            if (i >= placed)
+                perm[i] = -1;
+        }
+}
+
 // In-place exclusive scan of a[0, n) by one workgroup; a[n] receives the total. n is at
 // most kMaxSortKeys, so one workgroup reads at most 36 entries per thread, and a single
 // launch replaces three (tiles, tops, add), each of which cost its ~4 us start.
-__global__ __launch_bounds__(kScanThreads) void k_scan_keys(uint32_t* __restrict__ a, uint32_t n)
+__global__ __launch_bounds__(kScanThreads) void k_scan_keys(uint32_t* __restrict__ a, uint32_t n, int64_t N,
+                                                            int32_t* __restrict__ perm, int32_t* __restrict__ inv)
 {
     __shared__ uint32_t sh[kScanThreads / kWave + 1];
     uint32_t run = 0;
@@ -75,6 +90,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_keys(uint32_t* __restrict
     }
     if (threadIdx.x == 0)
         a[n] = run;
+    clear_if_broken(run, N, perm, inv);
 }
 
 // ------------------------------------------------------------------ keys --
@@ -235,7 +251,9 @@ __global__ __launch_bounds__(kSortThreads) void k_col_apply(uint32_t* __restrict
 constexpr uint32_t kSmallKeys = 4096;
 
 __global__ __launch_bounds__(kScanThreads) void k_col_small(uint32_t* __restrict__ table, int64_t nchunks,
-                                                            uint32_t nkeys, uint32_t* __restrict__ start)
+                                                            uint32_t nkeys, uint32_t* __restrict__ start,
+                                                            int64_t N, int32_t* __restrict__ perm,
+                                                            int32_t* __restrict__ inv)
 {
     __shared__ uint32_t sh[kScanThreads / kWave + 1];
     uint32_t base = 0;
@@ -255,6 +273,7 @@ __global__ __launch_bounds__(kScanThreads) void k_col_small(uint32_t* __restrict
     }
     if (threadIdx.x == 0)
         start[nkeys] = base;
+    clear_if_broken(base, N, perm, inv);
 }
 
 // ------------------------------------------------------ 4. placement --
@@ -401,16 +420,16 @@ __global__ __launch_bounds__(4 * kWave) void k_sort_place(const unsigned long lo
 
 // ------------------------------------------------ gather and bond table --
 
-// Old storage index of output slot p. A slot that a broken permutation left unwritten holds
-// whatever the workspace held: out of range it stands for the slot itself.
+// Old storage index of output slot p. One out of range, in a slot that a broken permutation or
+// broken key starts left, stands for the slot itself.
 __device__ __forceinline__ int32_t source_of(const int32_t* __restrict__ perm, int64_t p, int64_t N)
 {
     const int32_t o = perm[p];
     return o >= 0 && o < N ? o : (int32_t)p;
 }
 
-// New storage index of partner j (-1: none, or outside [-1, N), which is flagged). A bead
-// that a broken permutation left out has no inverse entry; its partners get -1.
+// New storage index of partner j (-1: none, or outside [-1, N), which is flagged, or a bead
+// that a broken permutation left out).
 __device__ __forceinline__ int32_t renumbered(int32_t j, const int32_t* __restrict__ inv, int64_t N, bool& bad)
 {
     if (j >= 0 && j < N) {
@@ -425,8 +444,11 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_inverse(const int32_t* __
                                                                int32_t* __restrict__ inv)
 {
     const int64_t p = xcd_block(blockIdx.x, gridDim.x) * kSortThreads + threadIdx.x;
-    if (p < N)
-        inv[source_of(perm, p, N)] = (int32_t)p;
+    if (p >= N)
+        return;
+    const int32_t o = perm[p];
+    if (o >= 0 && o < N)                 // not a slot that a broken permutation left
+        inv[o] = (int32_t)p;
 }
 
 // Bead rows and bond rows in the new order, in one pass (HBM-bound).
@@ -624,8 +646,10 @@ __global__ __launch_bounds__(kResortThreads) void k_resort_keys(Keyer keyer, con
             mrank[pos] += hcnt[mslot[pos]];
     if (threadIdx.x == 0)
         cnt_stay[k] = (uint32_t)run;
-    if (bad)
+    if (bad) {
         raise_flag(HPF_FLAG_SORT_ORDER);
+        cnt_move[gridDim.x] = 1u;        // for k_resort_movers
+    }
 }
 static_assert(kMoveKeys == 1u << (32 - 25) && kResortPer * kResortWaves <= kWave, "hash bits; one wave scans pre");
 
@@ -659,16 +683,20 @@ __global__ __launch_bounds__(kScanThreads) void k_resort_scan(const uint32_t* __
 }
 
 // Movers written to their new key's slots as (tag << 32 | index); their order inside
-// a key's slots is arbitrary (sorted in the placement).
+// a key's slots is arbitrary (sorted in the placement). Where a key range was out of tag order
+// (cnt_move[nkeys] set), the placement may leave slots and beads out: perm and inv, which the
+// ranks are read out of by then, are -1 beforehand.
 __global__ __launch_bounds__(kSortThreads) void k_resort_movers(const int32_t* __restrict__ tag,
                                                                 const uint32_t* __restrict__ cs_old, int64_t N,
                                                                 const uint32_t* __restrict__ cnt_stay,
+                                                                const uint32_t* __restrict__ cnt_move,
                                                                 const int32_t* __restrict__ order,
                                                                 const uint32_t* __restrict__ mkey,
-                                                                const uint32_t* __restrict__ mrank,
                                                                 const uint32_t* __restrict__ moff,
-                                                                unsigned long long* __restrict__ movers)
+                                                                unsigned long long* __restrict__ movers,
+                                                                int32_t* __restrict__ perm, int32_t* inv)
 {
+    const uint32_t* mrank = reinterpret_cast<const uint32_t*>(inv);
     const uint32_t k = blockIdx.x;
     const int64_t a = min((int64_t)cs_old[k], N), b = min((int64_t)cs_old[k + 1], N);
     for (int64_t pos = a + cnt_stay[k] + threadIdx.x; pos < b; pos += kSortThreads) {
@@ -676,6 +704,13 @@ __global__ __launch_bounds__(kSortThreads) void k_resort_movers(const int32_t* _
         const int64_t dst = (int64_t)moff[mkey[pos]] + mrank[pos];
         if (dst < N)
             movers[dst] = ((unsigned long long)(uint32_t)tag_of(tag, i) << 32) | (unsigned long long)(uint32_t)i;
+    }
+    if (cnt_move[gridDim.x]) {
+        __syncthreads();
+        for (int64_t pos = a + threadIdx.x; pos < b; pos += kSortThreads) {
+            perm[pos] = -1;
+            inv[pos] = -1;
+        }
     }
 }
 
@@ -940,7 +975,7 @@ bool sort_plan(int64_t N, int64_t nkeys, SortPlan* p)
     p->off_stay = o; o += align_up(sizeof(int32_t) * N1);
     p->off_movers = o; o += align_up(sizeof(uint64_t) * N1);
     p->off_cstay = o; o += align_up(sizeof(uint32_t) * (size_t)nkeys);
-    p->off_cmove = o; o += align_up(sizeof(uint32_t) * (size_t)nkeys);
+    p->off_cmove = o; o += align_up(sizeof(uint32_t) * (size_t)(nkeys + 1));
     p->off_moff = o; o += align_up(sizeof(uint32_t) * (size_t)(nkeys + 1));
     p->bytes = o;
     return true;
@@ -1037,13 +1072,14 @@ hpf_status_t run_sort(const SortPlan& pl, Keyer keyer, int64_t N, const float* R
     hipLaunchKernelGGL(k_sort_hist, dim3((unsigned)pl.nchunks), dim3(kChunkThreads), smem, s, by_tag, N, pl.S, nk,
                        table);
     if (pl.ncb == 1 && nk <= kSmallKeys) {
-        hipLaunchKernelGGL(k_col_small, dim3(1), dim3(kScanThreads), 0, s, table, pl.nchunks, nk, start);
+        hipLaunchKernelGGL(k_col_small, dim3(1), dim3(kScanThreads), 0, s, table, pl.nchunks, nk, start, N, perm,
+                           inv);
     } else {
         const unsigned gk = (nk + kSortThreads - 1) / kSortThreads;
         const dim3 gcol(gk, (unsigned)pl.ncb);
         hipLaunchKernelGGL(k_col_partial, gcol, dim3(kSortThreads), 0, s, table, pl.nchunks, nk, part);
         hipLaunchKernelGGL(k_col_prefix, dim3(gk), dim3(kSortThreads), 0, s, part, pl.ncb, nk, start);
-        hipLaunchKernelGGL(k_scan_keys, dim3(1), dim3(kScanThreads), 0, s, start, nk);
+        hipLaunchKernelGGL(k_scan_keys, dim3(1), dim3(kScanThreads), 0, s, start, nk, N, perm, inv);
         hipLaunchKernelGGL(k_col_apply, gcol, dim3(kSortThreads), 0, s, table, part, start, pl.nchunks, nk);
     }
     int nbits = 1;
@@ -1090,12 +1126,12 @@ hpf_status_t run_resort(const SortPlan& pl, Keyer keyer, int64_t N, const float*
         return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
     }
     hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)std::min<int64_t>(grid_for(nk), 4096)), dim3(kSortThreads), 0, s,
-                       cmove, (int64_t)nk, 0u);
+                       cmove, (int64_t)nk + 1, 0u);
     hipLaunchKernelGGL(k_resort_keys<Keyer>, dim3(nk), dim3(kResortThreads), 0, s, keyer, tag_in, cs_old, N, order,
                        mkey, reinterpret_cast<uint32_t*>(perm), reinterpret_cast<uint32_t*>(inv), cstay, cmove);
     hipLaunchKernelGGL(k_resort_scan, dim3(1), dim3(kScanThreads), 0, s, cstay, cmove, nk, cs_new, moff);
-    hipLaunchKernelGGL(k_resort_movers, dim3(nk), dim3(kSortThreads), 0, s, tag_in, cs_old, N, cstay, order, mkey,
-                       reinterpret_cast<uint32_t*>(inv), moff, movers);
+    hipLaunchKernelGGL(k_resort_movers, dim3(nk), dim3(kSortThreads), 0, s, tag_in, cs_old, N, cstay, cmove,
+                       order, mkey, moff, movers, perm, inv);
     hipLaunchKernelGGL(k_resort_place, dim3(nk), dim3(kPlaceThreads), 0, s, tag_in, cs_old, N, order, cstay, cmove,
                        moff, cs_new, movers, perm, inv);
     launch_permute(N, perm, inv, R_in, V_in, T_in, tag_in, bonds_in, D, R_out, V_out, T_out, tag_out, bonds_out, s);

@@ -1,0 +1,82 @@
+"""GPU: what the sorts give for tags that are no permutation, or a re-sort for an input out of tag
+order, does not depend on what the workspace held: slots that no bead was placed in keep the bead
+that stood there, and a bead left out is nobody's partner."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from gpu_util import host  # noqa: E402
+from paper_1310_2041_amd import engine, hpf  # noqa: E402
+from synth import workloads as wl  # noqa: E402
+
+FILLS = [0, 5, 1 << 24, -1]                       # in range (0, 5) and outside
+
+
+def _state(N=3000):
+    s = wl.small_system(N // 30, 10, 24.0, 24, seed=12, n_solvent=N - 10 * (N // 30))
+    st = engine.HpfState.from_system(s, sort_brick=8)
+    st.bonds2.fill_(-7)
+    return st
+
+
+@pytest.mark.parametrize("N", [600, 70000])       # one workgroup's columns, several
+@pytest.mark.parametrize("left_out", [1, 9])
+def test_full_sort_with_beads_left_out(N, left_out):
+    ref = None
+    rng = np.random.default_rng(N)
+    lost = rng.permutation(N // 30 * 10)[:left_out]          # chain beads, which have partners
+    for fill in FILLS:
+        st = _state(N)
+        st.tag[torch.from_numpy(lost).cuda()] = N + 3
+        R0, bonds0 = host(st.R), host(st.bonds)
+        st.work.view(torch.int32)[: st.work.numel() // 4].fill_(fill)
+        hpf.hpf_get_device_status(clear=True)
+        st.sort()
+        assert hpf.hpf_get_device_status(clear=True) & hpf.HPF_FLAG_SORT_ORDER
+        out = [host(x) for x in (st.R, st.tag, st.bonds, st.cell_start)]
+        assert out[3][-1] == N - left_out
+        assert np.array_equal(out[0][N - left_out:], R0[N - left_out:])
+        tags = out[1][: N - left_out]
+        for p in range(0, N - left_out, 1 + N // 500):       # partners by input index
+            for d in range(bonds0.shape[0]):
+                j = bonds0[d, tags[p]]
+                want = -1 if j < 0 or j in lost else int(np.flatnonzero(tags == j)[0])
+                assert out[2][d, p] == want, (p, d)
+        if ref is not None:
+            assert all(np.array_equal(x, y) for x, y in zip(out, ref))
+        ref = out
+
+
+@pytest.mark.parametrize("fill", FILLS)
+def test_resort_of_an_input_out_of_order(fill):
+    """The last two beads of a brick change places, and a bead whose tag is between theirs comes
+    in: the mover and both stayers take two slots, the third stays free."""
+    st = _state()
+    st.sort()
+    cs, tag = host(st.cell_start), host(st.tag)
+    for k in range(27):
+        a, b = int(cs[k]), int(cs[k + 1])
+        if b - a < 3:
+            continue
+        t0, t1 = tag[b - 2], tag[b - 1]
+        between = [i for i in np.flatnonzero((tag > t0) & (tag < t1)) if not a <= i < b]
+        if between:
+            break
+    assert between
+    for x in (st.R, st.Vel, st.T, st.tag):
+        x[[b - 2, b - 1]] = x[[b - 1, b - 2]]
+    st.R[int(between[0])] = st.R[b - 1]                      # into the brick
+    before = host(st.R)
+    st.work.view(torch.int32)[: st.work.numel() // 4].fill_(fill)
+    st.resort = True
+    hpf.hpf_get_device_status(clear=True)
+    st.sort()
+    assert hpf.hpf_get_device_status(clear=True) & hpf.HPF_FLAG_SORT_ORDER
+    free = int(host(st.cell_start)[k + 1]) - 1
+    assert np.array_equal(host(st.R)[free], before[free])
+    assert np.isin(host(st.bonds), np.arange(-1, st.N)).all()

@@ -844,7 +844,7 @@ __global__ __launch_bounds__(kPlaceThreads) void k_resort_place(const int32_t* _
     __shared__ unsigned long long smv[kMoverCap];
     __shared__ uint32_t below[kMoverCap];          // stayers below each mover
     const uint32_t k = (uint32_t)xcd_block(blockIdx.x, gridDim.x);
-    const int64_t nmv = min((int64_t)cnt_move[k], N - moff[k]), ns = cnt_stay[k];
+    const int64_t nmv = max((int64_t)0, min((int64_t)cnt_move[k], N - moff[k])), ns = cnt_stay[k];
     const int64_t base = start[k];
     unsigned long long* mv = movers + moff[k];
     const int32_t* st = order + min((int64_t)cs_old[k], N);
@@ -854,7 +854,9 @@ __global__ __launch_bounds__(kPlaceThreads) void k_resort_place(const int32_t* _
     while (p2above <= nmv)
         p2above <<= 1;
     auto put = [&](int64_t dst, int32_t i) {
-        if (dst < N) {                   // always, unless the key starts handed in were broken
+        // always, unless the key starts handed in were broken: where their ranges overlap, slots lie
+        // beyond N and movers' entries are left as the workspace had them
+        if (dst < N && i >= 0 && i < N) {
             perm[dst] = i;
             inv[i] = (int32_t)dst;
         }

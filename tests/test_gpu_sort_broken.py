@@ -80,3 +80,29 @@ def test_resort_of_an_input_out_of_order(fill):
     free = int(host(st.cell_start)[k + 1]) - 1
     assert np.array_equal(host(st.R)[free], before[free])
     assert np.isin(host(st.bonds), np.arange(-1, st.N)).all()
+
+
+@pytest.mark.parametrize("fill", [0, -1, 0x7eadbeef])
+@pytest.mark.parametrize("starts", ["overlapping", "descending", "beyond"])
+def test_resort_with_broken_key_starts_stays_in_range(starts, fill):
+    """Key starts that no sort produced: every output row is an input row, and every partner is a
+    bead or -1."""
+    st = _state()
+    st.sort()
+    st.R.copy_(st.R[torch.randperm(st.N, device="cuda", generator=torch.Generator("cuda").manual_seed(1))])
+    n = st.cell_start.numel()
+    if starts == "overlapping":
+        cs = np.where(np.arange(n) % 2, st.N, 0)
+    elif starts == "descending":
+        cs = np.linspace(st.N, 0, n)
+    else:
+        cs = np.where(np.arange(n) % 3, 2 ** 31 - 1 - np.arange(n), st.N // 2)
+    st.cell_start.copy_(torch.from_numpy(cs.astype(np.int32)))
+    R0 = host(st.R)
+    st.work.view(torch.int32)[: st.work.numel() // 4].fill_(fill)
+    st.resort = True
+    hpf.hpf_get_device_status(clear=True)
+    st.sort()
+    hpf.hpf_get_device_status(clear=True)
+    assert np.isin(host(st.R)[:, 0], R0[:, 0]).all()
+    assert np.isin(host(st.bonds), np.arange(-1, st.N)).all()

@@ -198,8 +198,11 @@ def _check(fn: str, status: int):
 
 def _stream(stream):
     if stream is None:
-        # the current stream's handle without building a torch.cuda.Stream (4 us a call)
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            # the current stream's handle without building a torch.cuda.Stream (4 us a call)
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:           # torch's own, not in its public interface
+            return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)

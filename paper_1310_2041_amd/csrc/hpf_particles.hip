@@ -1141,10 +1141,31 @@ __global__ __launch_bounds__(kAdvPipeThreads) void k_advance(const float3* __res
 // and on the stored deposit boxes.
 constexpr int kASThreadsDefault = 512;
 constexpr int kASThreadsWide = 768;
-// The thermostat's form needs more than 128 VGPRs, so a CU holds 3 waves per SIMD of it: three
-// workgroups of 256 threads, but only one of 512 (3.3M beads in 2028 bricks: 137 against 189 us;
-// 384 threads, whose second workgroup did not fit either, 219).
+// The thermostat's pipelined form needs more than 128 VGPRs, so a CU holds 3 waves per SIMD of
+// it: three workgroups of 256 threads, but only one of 512 (3.3M beads in 2028 bricks: 137 against
+// 189 us; 384 threads, whose second workgroup did not fit either, 219). With a CU for each brick
+// the one workgroup has the more threads the better: 512 (100,000 beads in 125 bricks: 22 us
+// against 30).
 constexpr int kASThreadsThermo = 256;
+
+// Whether the bricks' workgroups, per_cu of them on a CU at a time, come in many turns or in turns
+// that are nearly full.
+static bool turns_full(int64_t bricks, int64_t per_cu)
+{
+    const int64_t turns = (bricks + per_cu * kCus - 1) / (per_cu * kCus);
+    return turns > 2 || 5 * turns * per_cu * kCus <= 6 * bricks;
+}
+
+// The plain loop with the thermostat fits 128 VGPRs: a CU takes four workgroups of 256 threads at a
+// time or two of 512. 256 pay where their turns are full (four bond rows, 256 against 512 threads:
+// 70 and 48 us with 512 bricks, 87 and 69 with 729, 66 and 76 with 1000, 104 and 97 with 1331, 113
+// and 124 with 1728, 142 and 149 with 2197, 310 and 333 with 4096).
+static bool thermo_plain_narrow(int64_t bricks) { return turns_full(bricks, 4); }
+
+// Three bond rows with the thermostat: piped with a CU for each brick (512 threads) or full turns of
+// 256 threads, else in the plain loop (piped against plain: 24 and 26 us with 216 bricks, 47 and 44
+// with 512, 55 and 64 with 729).
+static bool thermo_pipe_wide_rows(int64_t bricks) { return bricks <= kCus || turns_full(bricks, 3); }
 
 template <bool kR0Zero, int kASThreads, bool kPipe, bool kThermo, bool kNT, int kD>
 // The second bound is waves per SIMD. The form without the thermostat (512 threads) keeps two
@@ -1470,7 +1491,7 @@ using LaunchFn = hpf_status_t (*)(const float3*, float3*, float3*, const uint8_t
 
 // (A null function stands for a form that the rule for `pipe` below never asks for.)
 template <bool kPipe, bool kNT, int kD>
-static LaunchFn scatter_launch_fn(bool wide, bool thermo, bool r0z)
+static LaunchFn scatter_launch_fn(bool wide, bool thermo, bool r0z, int64_t bricks)
 {
     if (thermo && wide)
         return r0z ? launch_advance_scatter_t<true, kASThreadsWide, kPipe, true, kNT, kD>
@@ -1481,19 +1502,22 @@ static LaunchFn scatter_launch_fn(bool wide, bool thermo, bool r0z)
     if constexpr (kNT && kD > kPreBonds) {
         return nullptr;
     } else {
-        if (thermo)
+        if (thermo && (kPipe ? bricks > kCus : thermo_plain_narrow(bricks)))
             return r0z ? launch_advance_scatter_t<true, kASThreadsThermo, kPipe, true, kNT, kD>
                        : launch_advance_scatter_t<false, kASThreadsThermo, kPipe, true, kNT, kD>;
+        if (thermo)
+            return r0z ? launch_advance_scatter_t<true, kASThreadsDefault, kPipe, true, kNT, kD>
+                       : launch_advance_scatter_t<false, kASThreadsDefault, kPipe, true, kNT, kD>;
         return r0z ? launch_advance_scatter_t<true, kASThreadsDefault, kPipe, false, kNT, kD>
                    : launch_advance_scatter_t<false, kASThreadsDefault, kPipe, false, kNT, kD>;
     }
 }
 
 template <int kD>
-static LaunchFn scatter_pipe_fn(bool nt, bool wide, bool thermo, bool r0z)
+static LaunchFn scatter_pipe_fn(bool nt, bool wide, bool thermo, bool r0z, int64_t bricks)
 {
-    return nt ? scatter_launch_fn<true, true, kD>(wide, thermo, r0z)
-              : scatter_launch_fn<true, false, kD>(wide, thermo, r0z);
+    return nt ? scatter_launch_fn<true, true, kD>(wide, thermo, r0z, bricks)
+              : scatter_launch_fn<true, false, kD>(wide, thermo, r0z, bricks);
 }
 
 hpf_status_t launch_advance_scatter(const float* R, float* R_next, float* Vel, const uint8_t* T, int64_t N,
@@ -1521,11 +1545,13 @@ hpf_status_t launch_advance_scatter(const float* R, float* R_next, float* Vel, c
     // 36 in the plain loop; 8M in 16-cell bricks: the step 343 us against 519; 2.5M in 8-cell
     // bricks, streaming: 120 against 117).
     const bool pipe = (int64_t)K * tk.m.nm * 12 <= kBufMeshBytes &&
-                      (D <= kPreBonds || (D <= kPreBondsWide && (wide || !streams)));
+                      (D <= kPreBonds ||
+                       (D <= kPreBondsWide && (wide || (!streams && (!thermo || thermo_pipe_wide_rows(tk.ntiles))))));
     const bool nt = pipe && streams;
-    const LaunchFn launch = !pipe            ? scatter_launch_fn<false, false, kPreBonds>(wide, thermo, r0z)
-                            : D <= kPreBonds ? scatter_pipe_fn<kPreBonds>(nt, wide, thermo, r0z)
-                                             : scatter_pipe_fn<kPreBondsWide>(nt, wide, thermo, r0z);
+    const int64_t bricks = tk.ntiles;
+    const LaunchFn launch = !pipe            ? scatter_launch_fn<false, false, kPreBonds>(wide, thermo, r0z, bricks)
+                            : D <= kPreBonds ? scatter_pipe_fn<kPreBonds>(nt, wide, thermo, r0z, bricks)
+                                             : scatter_pipe_fn<kPreBondsWide>(nt, wide, thermo, r0z, bricks);
     if (!launch)
         return HPF_EINVAL;
     return launch(Rp, Rn, Vp, T, N, tk, K, Gp, bonds, D, k, r0, box, inv_mass, dt, cell_start, partials, counts, Fo,

@@ -34,9 +34,21 @@ def _system(n, B, halo, D, M=(25, 23, 27)):
                                            (8, 1, 2, 0.0, 5003), (8, 1, 2, 0.5, 4999), (8, 1, 3, 0.5, 5003),
                                            (8, 2, 3, 0.0, 777), (8, 1, 4, 0.5, 1501)])
 def test_depositing_pass_energies(masses, thermo, B, halo, D, r0, n):
+    _check_energies(_system(n, B, halo, D), masses, thermo, B, halo, r0, n)
+
+
+@pytest.mark.parametrize("bricks,D,r0", [(256, 2, 0.0), (320, 2, 0.5), (320, 3, 0.0), (704, 3, 0.5), (832, 4, 0.5),
+                                         (896, 4, 0.0), (1088, 4, 0.5), (1088, 3, 0.0), (1088, 1, 0.0)])
+def test_depositing_pass_energies_with_the_thermostat_by_bricks(bricks, D, r0):
+    """Both sides of the numbers of bricks at which its workgroup changes."""
+    st = _system(20000, 8, 1, D, M=(64, 64, bricks // 8))
+    assert hpf.sort_key_count(st.mesh, 8) == bricks
+    _check_energies(st, bricks % 256 == 0, True, 8, 1, r0, bricks)
+
+
+def _check_energies(st, masses, thermo, B, halo, r0, n):
     """All beads can be binned, so that every sum is finite. The two passes group the same FP64 terms
     differently: each sum is within 1e-12 of the sum of its terms' sizes."""
-    st = _system(n, B, halo, D)
     if thermo:
         st.set_thermostat(10.0, seed=5)
     torch.manual_seed(n)

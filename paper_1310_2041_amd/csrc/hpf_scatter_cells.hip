@@ -143,9 +143,13 @@ __device__ __forceinline__ void box_deposit(unsigned long long* box, int P, int 
 // or of LDS. Otherwise 512 threads measure best. The three passes, with 256 threads of four
 // beads / 512 of two / 1024 of two: 20,000 beads in 27 bricks 15.1 / 12.4 / 11.7 us; 3M beads in
 // 216 bricks of 16 cells 72.1 / 50.6 / 42.5, in 1,728 of 8 cells 39.6 / 38.8 / 50.6; 1M in 512
-// bricks 22.5 / 19.3 / 21.1.
+// bricks 22.5 / 19.3 / 21.1. Where LDS and bricks make at least kScManyPerCu workgroups a CU, 256
+// threads of two fill it too, and wait less for each other (with 512: 10,648 bricks of 3 cells, 95
+// beads each, 55 us against 75; 8,000 of 5 cells, 250 beads, 65 against 78; 1,728 of 8 cells, halo 1,
+// K = 2, 95 beads 27 against 30, 1200 beads 34.5 against 37).
 constexpr int kScBatch = 2;
 constexpr int kScBrickThreads = 512;
+constexpr int kScManyPerCu = 6;
 constexpr int kScLoneThreads = 1024;
 constexpr int64_t kCus = 256;
 constexpr size_t kLdsPerCu = 160 * 1024;
@@ -710,8 +714,10 @@ hpf_status_t launch_scatter_cells(const float* R, const uint8_t* T, int64_t N, c
         return HPF_OK;
     };
     const bool lone = tk.ntiles <= kCus || 2 * smem > kLdsPerCu;
-    const hpf_status_t st = lone ? go(k_scatter_bricks<kScLoneThreads>, kScLoneThreads)
-                                 : go(k_scatter_bricks<kScBrickThreads>, kScBrickThreads);
+    const bool many = tk.ntiles >= kScManyPerCu * kCus && kScManyPerCu * smem <= kLdsPerCu;
+    const hpf_status_t st = lone   ? go(k_scatter_bricks<kScLoneThreads>, kScLoneThreads)
+                            : many ? go(k_scatter_bricks<kTcThreads>, kTcThreads)
+                                   : go(k_scatter_bricks<kScBrickThreads>, kScBrickThreads);
     if (st != HPF_OK)
         return st;
     hipLaunchKernelGGL(k_scatter_sum<false>, dim3((unsigned)tk.ntiles + kFindBlocks), sum_block(tk.ntiles), 0, s,

@@ -40,7 +40,8 @@ def _moved(R, tag, gone, M, seed):
     return torch.where((tag < gone)[:, None], to, R)
 
 
-CASES = [("one_brick", (64, 64, 64), {77: 300000}, 300000, 9000),
+CASES = [("many_small_bricks", (96, 96, 88), {i: 3000 for i in (7, 800, 1583)}, 7000, 30000),
+         ("one_brick", (64, 64, 64), {77: 300000}, 300000, 9000),
          ("at_the_limit", (64, 72, 64), {5: LONG + 1, 60: LONG, 61: LONG - 1}, 3 * LONG, 2000),
          ("few_bricks", (40, 33, 40), {3: 20000, 9: 2500}, 22500, 100),
          ("more_than_named", (64, 64, 64), {i: 2100 for i in range(100, 150)}, 50 * 2100, 50000),

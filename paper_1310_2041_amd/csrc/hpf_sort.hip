@@ -23,6 +23,7 @@
 // order. Finally one pass gathers the bead arrays and the renumbered bond table
 // into the output buffers.
 #include <algorithm>
+#include <type_traits>
 
 #include "hpf_common.hpp"
 
@@ -534,12 +535,20 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_angles(const int32_t* __r
 // barriers, every bead's key written and read again and the stayers' tags searched in global
 // memory: 350, 290, 581, and 1060 for the rows, bonds and inverse.) A single round of bricks
 // (1M beads in 512) takes 95 us, as the full sort does.
+// Small bricks take workgroups of 128 threads in the key pass, one row a thread, and a wavefront
+// each in the placement, where a workgroup of 512 threads spends its time on barriers and on
+// rows past the brick's end: 36,000 bricks of 6 beads 500 us, now 150, of 120 beads 815 and
+// 330. Both passes loop, so that a large brick among small ones (a droplet) is only slower: 1M
+// beads of a 24^3-cell droplet in 256^3 cells 490 us against 375 with 512 threads.
 constexpr int kResortThreads = 512;
 constexpr int kResortWaves = kResortThreads / kWave;
-constexpr int kResortPer = 8;
-constexpr int kPlaceThreads = 512;
+constexpr int kSmallThreads = 128;       // key pass of small bricks
+constexpr int kResortPer = 8;            // rows a thread of the key pass reads at once
 constexpr int kPlacePer = 4;             // stayers a thread reads at once
-constexpr int kMoverCap = 2048;          // movers of one key sorted in LDS (16 KiB)
+constexpr int kMoverCap = kPlacePer * kResortThreads;   // movers of one key sorted in LDS (16 KiB)
+constexpr uint32_t kWaveBeads = 1024;    // stayers of a key that one wavefront places
+template <int n>
+using Rows = std::integral_constant<int, n>;
 constexpr uint32_t kMoveKeys = 128;      // keys an old range's movers are counted under in LDS
 constexpr int kMoveProbes = 16;
 
@@ -548,43 +557,52 @@ __device__ __forceinline__ int32_t tag_of(const int32_t* __restrict__ tag, int64
     return tag ? tag[i] : (int32_t)i;
 }
 
-template <class Keyer>
-__global__ __launch_bounds__(kResortThreads) void k_resort_keys(Keyer keyer, const int32_t* __restrict__ tag,
-                                                                const uint32_t* __restrict__ cs_old, int64_t N,
-                                                                int32_t* __restrict__ order,
-                                                                uint32_t* __restrict__ mkey,
-                                                                uint32_t* __restrict__ mslot,
-                                                                uint32_t* __restrict__ mrank,
-                                                                uint32_t* __restrict__ cnt_stay,
-                                                                uint32_t* __restrict__ cnt_move)
+template <int kThreads, class Keyer>
+__global__ __launch_bounds__(kThreads) void k_resort_keys(Keyer keyer, const int32_t* __restrict__ tag,
+                                                          const uint32_t* __restrict__ cs_old, int64_t N,
+                                                          int32_t* __restrict__ order,
+                                                          uint32_t* __restrict__ mkey,
+                                                          uint32_t* __restrict__ mslot,
+                                                          uint32_t* __restrict__ mrank,
+                                                          uint32_t* __restrict__ cnt_stay,
+                                                          uint32_t* __restrict__ cnt_move)
 {
+    constexpr int kWaves = kThreads / kWave;
+    static_assert(kResortPer * kWaves <= kWave && kThreads >= (int)kMoveKeys, "one wave scans pre; a thread a table entry");
     __shared__ uint32_t hkey[kMoveKeys], hcnt[kMoveKeys];
-    __shared__ uint32_t pre[kResortPer * kResortWaves + 1];
+    __shared__ uint32_t pre[kResortPer * kWaves + 1];
     const uint32_t k = (uint32_t)xcd_block(blockIdx.x, gridDim.x);
     const int64_t a = min((int64_t)cs_old[k], N), b = min((int64_t)cs_old[k + 1], N);
+    if (a >= b) {
+        if (threadIdx.x == 0)
+            cnt_stay[k] = 0u;
+        return;
+    }
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    for (uint32_t h = threadIdx.x; h < kMoveKeys; h += kResortThreads) {
-        hkey[h] = kNoKey;
-        hcnt[h] = 0u;
+    if (threadIdx.x < kMoveKeys) {
+        hkey[threadIdx.x] = kNoKey;
+        hcnt[threadIdx.x] = 0u;
     }
     int64_t run = 0;                     // stayers so far
     bool bad = false;
-    for (int64_t base = a; base < b; base += kResortPer * kResortThreads) {
+    // kPer rows of a tile from base on
+    auto tile = [&](auto per, int64_t base) {
+        constexpr int kPer = decltype(per)::value;
         // all rows first: a key's branches between them would have each wait for its own
-        float3 r[kResortPer];
-        int32_t tg[kResortPer], tb[kResortPer];
+        float3 r[kPer];
+        int32_t tg[kPer], tb[kPer];
 #pragma unroll
-        for (int u = 0; u < kResortPer; ++u) {
-            const int64_t i = min(base + u * kResortThreads + threadIdx.x, b - 1);
+        for (int u = 0; u < kPer; ++u) {
+            const int64_t i = min(base + u * kThreads + threadIdx.x, b - 1);
             r[u] = keyer.R[i];
             tg[u] = tag_of(tag, i);
             tb[u] = i > a ? tag_of(tag, i - 1) : -1;
         }
-        uint32_t key[kResortPer];
-        uint64_t stay[kResortPer];
+        uint32_t key[kPer];
+        uint64_t stay[kPer];
 #pragma unroll
-        for (int u = 0; u < kResortPer; ++u) {
-            const int64_t i = base + u * kResortThreads + threadIdx.x;
+        for (int u = 0; u < kPer; ++u) {
+            const int64_t i = base + u * kThreads + threadIdx.x;
             key[u] = kNoKey;
             if (i < b) {
                 key[u] = keyer((int32_t)i, r[u]);
@@ -593,27 +611,27 @@ __global__ __launch_bounds__(kResortThreads) void k_resort_keys(Keyer keyer, con
         }
         __syncthreads();                 // pre is read out; the table is cleared
 #pragma unroll
-        for (int u = 0; u < kResortPer; ++u) {
+        for (int u = 0; u < kPer; ++u) {
             stay[u] = __ballot(key[u] == k);
             if (lane == 0)
-                pre[u * kResortWaves + wave] = (uint32_t)__builtin_popcountll(stay[u]);
+                pre[u * kWaves + wave] = (uint32_t)__builtin_popcountll(stay[u]);
         }
         __syncthreads();
         if (wave == 0) {
-            const uint32_t v = lane < kResortPer * kResortWaves ? pre[lane] : 0u;
+            const uint32_t v = lane < kPer * kWaves ? pre[lane] : 0u;
             const uint32_t inc = wave_incl_scan(v);
-            if (lane < kResortPer * kResortWaves)
+            if (lane < kPer * kWaves)
                 pre[lane] = inc - v;
-            if (lane == kResortPer * kResortWaves - 1)
+            if (lane == kPer * kWaves - 1)
                 pre[lane + 1] = inc;
         }
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kResortPer; ++u) {
-            const int64_t i = base + u * kResortThreads + threadIdx.x;
+        for (int u = 0; u < kPer; ++u) {
+            const int64_t i = base + u * kThreads + threadIdx.x;
             if (i >= b)
                 continue;
-            const int64_t before = run + pre[u * kResortWaves + wave] +
+            const int64_t before = run + pre[u * kWaves + wave] +
                                    (uint32_t)__builtin_popcountll(stay[u] & ((1ull << lane) - 1));
             if (key[u] == k) {
                 order[a + before] = (int32_t)i;
@@ -623,11 +641,28 @@ __global__ __launch_bounds__(kResortThreads) void k_resort_keys(Keyer keyer, con
             order[pos] = (int32_t)i;
             mkey[pos] = key[u];
         }
-        run += pre[kResortPer * kResortWaves];
+        run += pre[kPer * kWaves];
+    };
+    for (int64_t base = a; base < b;) {
+        if (b - base > 2 * kThreads) {
+            tile(Rows<kResortPer>(), base);
+            base += kResortPer * kThreads;
+        } else {
+            tile(Rows<1>(), base);
+            base += kThreads;
+        }
     }
+    if (bad) {
+        raise_flag(HPF_FLAG_SORT_ORDER);
+        cnt_move[gridDim.x] = 1u;        // for k_resort_movers
+    }
+    if (threadIdx.x == 0)
+        cnt_stay[k] = (uint32_t)run;
+    if (a + run == b)                    // uniform
+        return;
     __syncthreads();
     // the movers, now side by side, are counted per key
-    for (int64_t pos = a + run + threadIdx.x; pos < b; pos += kResortThreads) {
+    for (int64_t pos = a + run + threadIdx.x; pos < b; pos += kThreads) {
         const uint32_t key = mkey[pos];
         uint32_t h = (key * 2654435761u) >> 25, slot = kMoveKeys, rank = 0;
         for (int q = 0; q < kMoveProbes; ++q, h = (h + 1) % kMoveKeys) {
@@ -648,17 +683,11 @@ __global__ __launch_bounds__(kResortThreads) void k_resort_keys(Keyer keyer, con
     if (threadIdx.x < kMoveKeys && hcnt[threadIdx.x])
         hcnt[threadIdx.x] = atomicAdd(cnt_move + hkey[threadIdx.x], hcnt[threadIdx.x]);
     __syncthreads();
-    for (int64_t pos = a + run + threadIdx.x; pos < b; pos += kResortThreads)
+    for (int64_t pos = a + run + threadIdx.x; pos < b; pos += kThreads)
         if (mslot[pos] < kMoveKeys)
             mrank[pos] += hcnt[mslot[pos]];
-    if (threadIdx.x == 0)
-        cnt_stay[k] = (uint32_t)run;
-    if (bad) {
-        raise_flag(HPF_FLAG_SORT_ORDER);
-        cnt_move[gridDim.x] = 1u;        // for k_resort_movers
-    }
 }
-static_assert(kMoveKeys == 1u << (32 - 25) && kResortPer * kResortWaves <= kWave, "hash bits; one wave scans pre");
+static_assert(kMoveKeys == 1u << (32 - 25), "hash bits");
 
 // One block: new key starts (stayers + movers per key, exclusive scan; the last entry the
 // total) and the movers' slot offsets (exclusive scan of the mover counts).
@@ -763,17 +792,18 @@ __device__ __forceinline__ int64_t movers_below(unsigned long long key, int64_t 
     return lo;
 }
 
-// Number of entries of v[0, n) (ascending) below each of the keys e[0, kPlacePer): one binary
+// Number of entries of v[0, n) (ascending) below each of the keys e[0, kPer): one binary
 // search each, their steps side by side. p2 is a power of two above n.
+template <int kPer>
 __device__ __forceinline__ void lds_below(const unsigned long long* v, int n, int p2,
-                                          const unsigned long long (&e)[kPlacePer], int (&pos)[kPlacePer])
+                                          const unsigned long long (&e)[kPer], int (&pos)[kPer])
 {
 #pragma unroll
-    for (int u = 0; u < kPlacePer; ++u)
+    for (int u = 0; u < kPer; ++u)
         pos[u] = 0;
     for (int s = p2 >> 1; s > 0; s >>= 1) {
 #pragma unroll
-        for (int u = 0; u < kPlacePer; ++u) {
+        for (int u = 0; u < kPer; ++u) {
             const int q = pos[u] + s;
             if (q <= n && v[q - 1] < e[u])
                 pos[u] = q;
@@ -802,8 +832,7 @@ __device__ __forceinline__ unsigned long long wave_sort(unsigned long long v)
 // over all of them took a barrier for each of its 55 steps at 600 values.)
 __device__ __forceinline__ void sort_movers(int n, unsigned long long* v)
 {
-    constexpr int kWaves = kPlaceThreads / kWave, kPer = kMoverCap / kPlaceThreads;
-    static_assert(kPer == kPlacePer, "lds_below takes a thread's values together");
+    constexpr int kWaves = kResortWaves, kPer = kPlacePer;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int runs = (n + kWave - 1) / kWave;
     unsigned long long e[kPer];
@@ -836,30 +865,24 @@ __device__ __forceinline__ void sort_movers(int n, unsigned long long* v)
 }
 
 // Per new key: movers sorted by tag (in LDS when they fit, else in place in their
-// slots), then stayers and movers merged by tag into the key's output range.
-__global__ __launch_bounds__(kPlaceThreads) void k_resort_place(const int32_t* __restrict__ tag,
-                                                                const uint32_t* __restrict__ cs_old, int64_t N,
-                                                                const int32_t* __restrict__ order,
-                                                                const uint32_t* __restrict__ cnt_stay,
-                                                                const uint32_t* __restrict__ cnt_move,
-                                                                const uint32_t* __restrict__ moff,
-                                                                const uint32_t* __restrict__ start,
-                                                                unsigned long long* __restrict__ movers,
-                                                                int32_t* __restrict__ perm,
-                                                                int32_t* __restrict__ inv)
+// slots), then stayers and movers merged by tag into the key's output range. kGroup: a
+// wavefront per key, kResortWaves keys a workgroup, which then takes those that are too large
+// for one together; else a workgroup per key.
+template <bool kGroup>
+__global__ __launch_bounds__(kResortThreads) void k_resort_place(const int32_t* __restrict__ tag,
+                                                                 const uint32_t* __restrict__ cs_old, int64_t N,
+                                                                 const int32_t* __restrict__ order,
+                                                                 const uint32_t* __restrict__ cnt_stay,
+                                                                 const uint32_t* __restrict__ cnt_move,
+                                                                 const uint32_t* __restrict__ moff,
+                                                                 const uint32_t* __restrict__ start, uint32_t nkeys,
+                                                                 unsigned long long* __restrict__ movers,
+                                                                 int32_t* __restrict__ perm,
+                                                                 int32_t* __restrict__ inv)
 {
     __shared__ unsigned long long smv[kMoverCap];
     __shared__ uint32_t below[kMoverCap];          // stayers below each mover
-    const uint32_t k = (uint32_t)xcd_block(blockIdx.x, gridDim.x);
-    const int64_t nmv = max((int64_t)0, min((int64_t)cnt_move[k], N - moff[k])), ns = cnt_stay[k];
-    const int64_t base = start[k];
-    unsigned long long* mv = movers + moff[k];
-    const int32_t* st = order + min((int64_t)cs_old[k], N);
-    int64_t p2 = 1, p2above = 1;
-    while (p2 < nmv)
-        p2 <<= 1;
-    while (p2above <= nmv)
-        p2above <<= 1;
+    const int lane = threadIdx.x & (kWave - 1);
     auto put = [&](int64_t dst, int32_t i) {
         // always, unless the key starts handed in were broken: where their ranges overlap, slots lie
         // beyond N and movers' entries are left as the workspace had them
@@ -868,75 +891,138 @@ __global__ __launch_bounds__(kPlaceThreads) void k_resort_place(const int32_t* _
             inv[i] = (int32_t)dst;
         }
     };
-    const bool in_lds = nmv <= kMoverCap;
-    auto lds = [&](int64_t q) { return smv[q]; };
-    auto glob = [&](int64_t q) { return mv[q]; };
-    if (in_lds) {
-        for (int64_t q = threadIdx.x; q < (nmv + kWave - 1) / kWave * kWave; q += kPlaceThreads) {
-            smv[q] = q < nmv ? mv[q] : ~0ull;
-            below[q] = (uint32_t)ns;
-        }
-        __syncthreads();
-        sort_movers((int)nmv, smv);
-    } else {
-        sort_padded(nmv, p2, glob, [&](int64_t q, unsigned long long v) { mv[q] = v; });
-    }
-    // stayers: rank among stayers + movers with a smaller tag; the movers between a stayer
-    // and the one before it have that stayer's rank of stayers below them
-    for (int64_t q0 = 0; q0 < ns; q0 += kPlacePer * kPlaceThreads) {
-        int32_t idx[kPlacePer], tg[kPlacePer];
+    auto n_movers = [&](uint32_t k) { return max((int64_t)0, min((int64_t)cnt_move[k], N - moff[k])); };
+    // up to a wavefront's lanes of movers, by one wavefront
+    auto by_wave = [&](uint32_t k) {
+        const int64_t nmv = n_movers(k), ns = cnt_stay[k], base = start[k];
+        const int32_t* st = order + min((int64_t)cs_old[k], N);
+        volatile uint32_t* mine = below + threadIdx.x / kWave * kWave;   // one wavefront's, in order
+        unsigned long long e = lane < nmv ? movers[moff[k] + lane] : ~0ull;
+        if (nmv > 1)
+            e = wave_sort(e);
+        mine[lane] = (uint32_t)ns;
+        int last = 0;                    // movers below the stayer before these
+        for (int64_t q0 = 0; q0 < ns; q0 += kWave) {
+            const int64_t q = q0 + lane;
+            const int32_t idx = q < ns ? st[q] : 0;
+            int c = 0;
+            if (nmv) {
+                const unsigned long long t = (unsigned long long)(uint32_t)tag_of(tag, idx) << 32;
 #pragma unroll
-        for (int u = 0; u < kPlacePer; ++u) {
-            const int64_t q = q0 + u * kPlaceThreads + threadIdx.x;
-            idx[u] = q < ns ? st[q] : 0;
-        }
-#pragma unroll
-        for (int u = 0; u < kPlacePer; ++u)
-            tg[u] = tag_of(tag, idx[u]);
-        unsigned long long e[kPlacePer];
-        int c[kPlacePer];
-#pragma unroll
-        for (int u = 0; u < kPlacePer; ++u) {
-            e[u] = (unsigned long long)(uint32_t)tg[u] << 32;
-            c[u] = in_lds ? 0 : (int)movers_below(e[u], nmv, glob);
-        }
-        if (in_lds)
-            lds_below(smv, (int)nmv, (int)p2above, e, c);
-#pragma unroll
-        for (int u = 0; u < kPlacePer; ++u) {
-            const int64_t q = q0 + u * kPlaceThreads + threadIdx.x;
+                for (int step = kWave / 2; step > 0; step >>= 1)
+                    c += __shfl(e, c + step - 1, kWave) < t ? step : 0;
+                c += __shfl(e, c, kWave) < t;
+            }
             if (q < ns)
-                put(base + q + c[u], idx[u]);
-            if (!in_lds)
-                continue;
-            int prev = __shfl_up(c[u], 1, kWave);
-            if ((threadIdx.x & (kWave - 1)) == 0)
-                prev = q > 0 && q < ns
-                           ? (int)movers_below((unsigned long long)(uint32_t)tag_of(tag, st[q - 1]) << 32, nmv, lds)
-                           : 0;
+                put(base + q + c, idx);
+            const int up = __shfl_up(c, 1, kWave);
             if (q < ns)
-                for (int j = prev; j < c[u]; ++j)
-                    below[j] = (uint32_t)q;
+                for (int j = lane ? up : last; j < c; ++j)
+                    mine[j] = (uint32_t)q;
+            last = __shfl(c, kWave - 1, kWave);
         }
-    }
-    __syncthreads();
-    for (int64_t q = threadIdx.x; q < nmv; q += kPlaceThreads) {
-        const unsigned long long e = in_lds ? smv[q] : mv[q];
-        int64_t lo = 0;
+        if (lane < nmv)
+            put(base + lane + mine[lane], (int32_t)(uint32_t)e);
+    };
+    auto by_block = [&](uint32_t k) {
+        const int64_t nmv = n_movers(k), ns = cnt_stay[k];
+        const int64_t base = start[k];
+        unsigned long long* mv = movers + moff[k];
+        const int32_t* st = order + min((int64_t)cs_old[k], N);
+        int64_t p2 = 1, p2above = 1;
+        while (p2 < nmv)
+            p2 <<= 1;
+        while (p2above <= nmv)
+            p2above <<= 1;
+        const bool in_lds = nmv <= kMoverCap;
+        auto lds = [&](int64_t q) { return smv[q]; };
+        auto glob = [&](int64_t q) { return mv[q]; };
         if (in_lds) {
-            lo = below[q];
+            for (int64_t q = threadIdx.x; q < (nmv + kWave - 1) / kWave * kWave; q += kResortThreads) {
+                smv[q] = q < nmv ? mv[q] : ~0ull;
+                below[q] = (uint32_t)ns;
+            }
+            __syncthreads();
+            sort_movers((int)nmv, smv);
         } else {
-            const int32_t t = (int32_t)(e >> 32);
-            int64_t hi = ns;
-            while (lo < hi) {
-                const int64_t mid = (lo + hi) >> 1;
-                if (tag_of(tag, st[mid]) < t)
-                    lo = mid + 1;
-                else
-                    hi = mid;
+            sort_padded(nmv, p2, glob, [&](int64_t q, unsigned long long v) { mv[q] = v; });
+        }
+        // stayers: rank among stayers + movers with a smaller tag; the movers between a stayer
+        // and the one before it have that stayer's rank of stayers below them
+        for (int64_t q0 = 0; q0 < ns; q0 += kPlacePer * kResortThreads) {
+            int32_t idx[kPlacePer], tg[kPlacePer];
+#pragma unroll
+            for (int u = 0; u < kPlacePer; ++u) {
+                const int64_t q = q0 + u * kResortThreads + threadIdx.x;
+                idx[u] = q < ns ? st[q] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kPlacePer; ++u)
+                tg[u] = tag_of(tag, idx[u]);
+            unsigned long long e[kPlacePer];
+            int c[kPlacePer];
+#pragma unroll
+            for (int u = 0; u < kPlacePer; ++u) {
+                e[u] = (unsigned long long)(uint32_t)tg[u] << 32;
+                c[u] = in_lds ? 0 : (int)movers_below(e[u], nmv, glob);
+            }
+            if (in_lds)
+                lds_below(smv, (int)nmv, (int)p2above, e, c);
+#pragma unroll
+            for (int u = 0; u < kPlacePer; ++u) {
+                const int64_t q = q0 + u * kResortThreads + threadIdx.x;
+                if (q < ns)
+                    put(base + q + c[u], idx[u]);
+                if (!in_lds)
+                    continue;
+                int prev = __shfl_up(c[u], 1, kWave);
+                if (lane == 0)
+                    prev = q > 0 && q < ns
+                               ? (int)movers_below((unsigned long long)(uint32_t)tag_of(tag, st[q - 1]) << 32, nmv, lds)
+                               : 0;
+                if (q < ns)
+                    for (int j = prev; j < c[u]; ++j)
+                        below[j] = (uint32_t)q;
             }
         }
-        put(base + q + lo, (int32_t)(uint32_t)e);
+        __syncthreads();
+        for (int64_t q = threadIdx.x; q < nmv; q += kResortThreads) {
+            const unsigned long long e = in_lds ? smv[q] : mv[q];
+            int64_t lo = 0;
+            if (in_lds) {
+                lo = below[q];
+            } else {
+                const int32_t t = (int32_t)(e >> 32);
+                int64_t hi = ns;
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi) >> 1;
+                    if (tag_of(tag, st[mid]) < t)
+                        lo = mid + 1;
+                    else
+                        hi = mid;
+                }
+            }
+            put(base + q + lo, (int32_t)(uint32_t)e);
+        }
+    };
+    const uint32_t b = (uint32_t)xcd_block(blockIdx.x, gridDim.x);
+    if constexpr (!kGroup) {
+        by_block(b);
+    } else {
+        __shared__ bool large[kResortWaves];
+        const int wave = threadIdx.x / kWave;
+        const uint32_t k = b + wave * gridDim.x;           // far from each other: large keys tend not to be
+        const bool too_large = k < nkeys && (cnt_move[k] > kWave || cnt_stay[k] > kWaveBeads);
+        if (k < nkeys && !too_large)
+            by_wave(k);
+        if (lane == 0)
+            large[wave] = too_large;
+        __syncthreads();
+        for (int w = 0; w < kResortWaves; ++w)
+            if (large[w]) {
+                by_block(b + w * gridDim.x);
+                __syncthreads();
+            }
     }
 }
 
@@ -1120,6 +1206,12 @@ hpf_status_t launch_sort(const SortK& sk, const SortPlan& pl, int64_t N, const f
                     start, work, s);
 }
 
+// Whether the re-sort takes the passes for small bricks. The line lies where they stop being the
+// faster ones (with / without, a tenth of a cell moved and half a cell: 4,096 bricks of 400 beads
+// 74 / 110 and 127 / 126 us, of 600 91 / 131 and 163 / 152; 1,000 bricks of 120 beads 28 / 31 and
+// 28 / 33, of 400 40 / 36 and 41 / 38).
+static bool small_bricks(int64_t N, uint32_t nkeys) { return N <= (nkeys >= 2048 ? 400 : 128) * (int64_t)nkeys; }
+
 // The re-sort (steps 1-4 above), then the gather and the bond renumbering of run_sort. The
 // movers' table slots and ranks stand in perm and inv until the placement writes those.
 template <class Keyer>
@@ -1144,13 +1236,16 @@ hpf_status_t run_resort(const SortPlan& pl, Keyer keyer, int64_t N, const float*
     }
     hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)std::min<int64_t>(grid_for(nk), 4096)), dim3(kSortThreads), 0, s,
                        cmove, (int64_t)nk + 1, 0u);
-    hipLaunchKernelGGL(k_resort_keys<Keyer>, dim3(nk), dim3(kResortThreads), 0, s, keyer, tag_in, cs_old, N, order,
-                       mkey, reinterpret_cast<uint32_t*>(perm), reinterpret_cast<uint32_t*>(inv), cstay, cmove);
+    const bool small = small_bricks(N, nk);
+    hipLaunchKernelGGL((small ? k_resort_keys<kSmallThreads, Keyer> : k_resort_keys<kResortThreads, Keyer>), dim3(nk),
+                       dim3(small ? kSmallThreads : kResortThreads), 0, s, keyer, tag_in, cs_old, N, order, mkey, reinterpret_cast<uint32_t*>(perm),
+                       reinterpret_cast<uint32_t*>(inv), cstay, cmove);
     hipLaunchKernelGGL(k_resort_scan, dim3(1), dim3(kScanThreads), 0, s, cstay, cmove, nk, cs_new, moff);
     hipLaunchKernelGGL(k_resort_movers, dim3(nk), dim3(kSortThreads), 0, s, tag_in, cs_old, N, cstay, cmove,
                        order, mkey, moff, movers, perm, inv);
-    hipLaunchKernelGGL(k_resort_place, dim3(nk), dim3(kPlaceThreads), 0, s, tag_in, cs_old, N, order, cstay, cmove,
-                       moff, cs_new, movers, perm, inv);
+    hipLaunchKernelGGL((small ? k_resort_place<true> : k_resort_place<false>),
+                       dim3(small ? (nk + kResortWaves - 1) / kResortWaves : nk), dim3(kResortThreads), 0, s, tag_in, cs_old, N, order, cstay, cmove,
+                       moff, cs_new, nk, movers, perm, inv);
     launch_permute(N, perm, inv, R_in, V_in, T_in, tag_in, bonds_in, D, R_out, V_out, T_out, tag_out, bonds_out, s);
     return hipGetLastError() == hipSuccess ? HPF_OK : HPF_EHIP;
 }

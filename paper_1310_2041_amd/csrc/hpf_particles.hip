@@ -807,7 +807,8 @@ __global__ __launch_bounds__(kPThreads, 4) void k_force_kick(const float3* __res
 // the positions again: 1.2M beads, five species, 74^3 points: 11 + 2.7 + 27 + 8 us apart.
 constexpr int kVSThreads = 512;
 
-__global__ __launch_bounds__(kVSThreads) void k_verlet_scatter(float3* __restrict__ R, float3* __restrict__ Vel,
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_verlet_scatter(float3* __restrict__ R, float3* __restrict__ Vel,
                                                                const float3* __restrict__ F,
                                                                const uint8_t* __restrict__ T,
                                                                const float* __restrict__ inv_mass, int64_t N,
@@ -846,16 +847,16 @@ __global__ __launch_bounds__(kVSThreads) void k_verlet_scatter(float3* __restric
     if (i < last)
         fetch(i);
     if (!tail)
-        for (int q = threadIdx.x; q < nbox; q += kVSThreads)
+        for (int q = threadIdx.x; q < nbox; q += kThreads)
             dbox[q] = 0ull;
     __syncthreads();
-    for (; i < last; i += kVSThreads) {
+    for (; i < last; i += kThreads) {
         float3 rn = r, vn = v;
         const float3 fn = f;
         const int tn = t;
         const float imn = im;
-        if (i + kVSThreads < last)
-            fetch(i + kVSThreads);
+        if (i + kThreads < last)
+            fetch(i + kThreads);
         kick(vn, fn, imn, hdt);
         drift(rn, vn, dt, box);
         nonfinite |= !(finite3(rn) && finite3(vn));
@@ -876,7 +877,7 @@ __global__ __launch_bounds__(kVSThreads) void k_verlet_scatter(float3* __restric
         return;
     __syncthreads();
     unsigned long long* out = partials + item * (int64_t)nbox;
-    for (int q = threadIdx.x; q < nbox; q += kVSThreads)
+    for (int q = threadIdx.x; q < nbox; q += kThreads)
         out[q] = dbox[q];
 }
 
@@ -1403,10 +1404,14 @@ hpf_status_t launch_verlet_scatter(float* R, float* Vel, const float* F, const u
                                    unsigned long long* counts, hipStream_t s)
 {
     const size_t smem = scatter_cells_smem(K, tk.P);
-    if (smem > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(k_verlet_scatter),
+    // as in the cell scatter, 256 threads fill a CU where bricks and boxes make many workgroups of it
+    // (a step of 10,648 bricks of 3 cells and 30 beads 90 -> 74 us; with 1,500 beads 105 -> 108)
+    const bool many = many_bricks(tk, smem) && N < 1024 * tk.ntiles;
+    const auto kernel = many ? k_verlet_scatter<kTcThreads> : k_verlet_scatter<kVSThreads>;
+    if (smem > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
         return HPF_EINVAL;
-    hipLaunchKernelGGL(k_verlet_scatter, dim3((unsigned)(tk.ntiles + 1)), dim3(kVSThreads), smem, s,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(tk.ntiles + 1)), dim3(many ? kTcThreads : kVSThreads), smem, s,
                        reinterpret_cast<float3*>(R), reinterpret_cast<float3*>(Vel),
                        reinterpret_cast<const float3*>(F), T, inv_mass, N, dt, box, tk, K, cell_start, partials,
                        counts);

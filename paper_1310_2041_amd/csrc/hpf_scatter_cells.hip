@@ -691,6 +691,12 @@ size_t scatter_cells_smem(int K, int P)
     return sizeof(unsigned long long) * (size_t)K * P * P * P;
 }
 
+// Whether LDS (smem bytes a workgroup) and bricks make kScManyPerCu workgroups a CU.
+static bool many_bricks(const TileK& tk, size_t smem)
+{
+    return tk.ntiles >= kScManyPerCu * kCus && kScManyPerCu * smem <= kLdsPerCu;
+}
+
 size_t scatter_cells_partials(int64_t ntiles, int K, int P)
 {
     return sizeof(unsigned long long) * (size_t)ntiles * K * P * P * P;
@@ -714,7 +720,7 @@ hpf_status_t launch_scatter_cells(const float* R, const uint8_t* T, int64_t N, c
         return HPF_OK;
     };
     const bool lone = tk.ntiles <= kCus || 2 * smem > kLdsPerCu;
-    const bool many = tk.ntiles >= kScManyPerCu * kCus && kScManyPerCu * smem <= kLdsPerCu;
+    const bool many = many_bricks(tk, smem);
     const hpf_status_t st = lone   ? go(k_scatter_bricks<kScLoneThreads>, kScLoneThreads)
                             : many ? go(k_scatter_bricks<kTcThreads>, kTcThreads)
                                    : go(k_scatter_bricks<kScBrickThreads>, kScBrickThreads);

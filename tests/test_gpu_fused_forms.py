@@ -74,6 +74,7 @@ def _check_energies(st, masses, thermo, B, halo, r0, n):
 @pytest.mark.parametrize("masses", [False, True])
 @pytest.mark.parametrize("B,halo,M,fill", [(8, 1, (24, 24, 25), (0, 1, 511, 512, 513, 1024, 1025)),
                                            (8, 2, (24, 33, 24), (3000, 0, 1)), (16, 2, (48, 33, 40), (5000, 511, 0, 1)),
+                                           (8, 1, (96, 96, 88), (700, 0, 255, 256, 257, 513)),
                                            (8, 1, (24, 24, 24), ())])
 def test_verlet_scatter_over_masses_and_brick_fills(masses, B, halo, M, fill):
     """fill[b] beads in brick b, none anywhere else."""

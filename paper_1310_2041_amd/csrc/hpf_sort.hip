@@ -1208,9 +1208,9 @@ hpf_status_t launch_sort(const SortK& sk, const SortPlan& pl, int64_t N, const f
 
 // Whether the re-sort takes the passes for small bricks. The line lies where they stop being the
 // faster ones (with / without, a tenth of a cell moved and half a cell: 4,096 bricks of 400 beads
-// 74 / 110 and 127 / 126 us, of 600 91 / 131 and 163 / 152; 1,000 bricks of 120 beads 28 / 31 and
-// 28 / 33, of 400 40 / 36 and 41 / 38).
-static bool small_bricks(int64_t N, uint32_t nkeys) { return N <= (nkeys >= 2048 ? 400 : 128) * (int64_t)nkeys; }
+// 74 / 110 and 127 / 126 us, of 600 91 / 131 and 163 / 152). A few hundred bricks fill the chip
+// only a workgroup each: 27 of 111 beads, every bead moving, 85 and 30 us.
+static bool small_bricks(int64_t N, uint32_t nkeys) { return nkeys >= 2048 && N <= 400 * (int64_t)nkeys; }
 
 // The re-sort (steps 1-4 above), then the gather and the bond renumbering of run_sort. The
 // movers' table slots and ranks stand in perm and inv until the placement writes those.

@@ -92,7 +92,7 @@ __device__ __forceinline__ void item_range(const RepK* __restrict__ reps, const 
     last = range[1];
 }
 
-// (with strays, kFindBlocks workgroups before those of the bricks, as in k_scatter_sum)
+// (without kAdd, kFindBlocks workgroups before those of the bricks, as in k_scatter_sum)
 template <bool kAdd>
 __global__ __launch_bounds__(kSumThreads) void k_batch_scatter_sum(const RepK* __restrict__ reps,
                                                            const ItemK* __restrict__ items, int B, int h,
@@ -102,8 +102,8 @@ __global__ __launch_bounds__(kSumThreads) void k_batch_scatter_sum(const RepK* _
                                                            const unsigned long long* __restrict__ partials,
                                                            unsigned long long* __restrict__ counts)
 {
-    const int skip = strays ? kFindBlocks : 0;
-    if ((int)blockIdx.x < skip) {
+    constexpr int skip = kAdd ? 0 : kFindBlocks;
+    if (!kAdd && (int)blockIdx.x < skip) {
         if (blockIdx.x == 0)
             find_long_lists(strays, Ntot, gridDim.x - skip, [&](int64_t b, uint32_t& first, uint32_t& last) {
                 item_range(reps, items, cell_start, b, first, last);

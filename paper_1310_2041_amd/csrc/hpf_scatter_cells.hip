@@ -542,8 +542,9 @@ __device__ __forceinline__ void find_long_lists(uint32_t* __restrict__ strays, i
         out[0] = min(found, kLongLists);
 }
 
-// With strays, the launch has kFindBlocks workgroups before those of the bricks (a whole turn of
-// the XCDs, so that a brick's stays on its own); the first finds the long lists.
+// Without kAdd (a scatter with strays) the launch has kFindBlocks workgroups before those of the
+// bricks (a whole turn of the XCDs, so that a brick's stays on its own); the first finds the long
+// lists. With it, N, cell_start and strays are not read.
 constexpr int kFindBlocks = 8;
 
 template <bool kAdd>
@@ -553,8 +554,8 @@ __global__ __launch_bounds__(kSumThreads) void k_scatter_sum(const unsigned long
                                                      uint32_t* __restrict__ strays,
                                                      unsigned long long* __restrict__ counts)
 {
-    const int skip = strays ? kFindBlocks : 0;
-    if ((int)blockIdx.x < skip) {
+    constexpr int skip = kAdd ? 0 : kFindBlocks;
+    if (!kAdd && (int)blockIdx.x < skip) {
         if (blockIdx.x == 0)
             find_long_lists(strays, N, tk.ntiles, [&](int64_t b, uint32_t& first, uint32_t& last) {
                 first = cell_start[b];

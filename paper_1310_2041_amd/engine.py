@@ -422,7 +422,7 @@ class HpfState:
 
     def advance(self, report=False, stream=None, deposit=True):
         """Fused forces + Verlet pass, x_n -> x_n+1 (with the density deposit of x_n+1 when
-        cell-sorted). Counts must be zero on entry (the potential pass
+        cell-sorted), which starts from cleared counts (the potential pass
         leaves them so). Without `deposit` (the next step keeps the field) the plain pass runs
         instead of the depositing one; the beads move the same either way."""
         bonds = self.bonds if self.bonds.shape[0] else None
@@ -432,6 +432,9 @@ class HpfState:
         th = self.thermostat()
         self.density_pending = False
         if deposit and self.uses_scatter_advance():
+            if not self.counts_clear:          # replayed steps leave a read-out's counts alone
+                with _on(stream):
+                    self.counts.zero_()
             self.counts_clear = False
             hpf.hpf_advance_scatter(self.R, self.R2, self.Vel, self.T, self.mesh, self.K, self.G, bonds,
                                     self.k_bond, self.r0, self.box, self.dt, self.cell_start, self.B,

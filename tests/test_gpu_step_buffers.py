@@ -75,6 +75,24 @@ def test_step_leaves_no_counts_behind(left_by):
     assert a.energies()["W"] == b.energies()["W"]
 
 
+def test_deposit_after_replayed_steps_and_a_read_out():
+    a, b = _states()
+    for st in (a, b):
+        st.step()                                  # the strays' buffer is there before the capture
+    torch.cuda.synchronize()
+    g = engine.Graph(lambda: [a.step() for _ in range(2)])
+    a.scatter()
+    g.launch(torch.cuda.current_stream())
+    b.step()
+    b.step()
+    for st in (a, b):
+        st.prime()
+        st.advance()                               # deposits, from the last gradient
+        st.step_fused(report=True)
+    _assert_same(a, b)
+    assert a.energies()["W"] == b.energies()["W"]
+
+
 def test_step_goes_on_without_memory_for_its_strays(monkeypatch):
     a, b = _states()
     tried = []

@@ -269,7 +269,7 @@ def run_composition(steps=40, sort_every=20):
             out["absent_point_species_fraction"] = float(
                 1.0 - sum(((pr >> k) & 1).mean() for k in range(s.K)) / s.K)
         del st
-    out["note"] = ("six-call steps with angles (the fused passes take bonds only), graph-replayed; "
+    out["note"] = ("HpfState.step with angles (step_fused takes bonds only), graph-replayed; "
                    "gradient_us: the gradient pass alone")
     return out
 

@@ -207,7 +207,7 @@ hpf_status_t hpf_density_scatter_cells(const float* R, const uint8_t* T, int64_t
  * HPF_STATIC_SCRATCH_BYTES (for example 1M beads on a 64^3 mesh with K = 2,
  * B = 8, halo = 2 needs 22 MB; 10M beads on 128^3 need 184 MB and are refused).
  * Every call on one GPU uses that GPU's one array and leaves its contents
- * behind (each launch clears what must start at zero): calls that overlap in
+ * behind (each launch reads only what it has written): calls that overlap in
  * time on one GPU, from any streams or threads, race and must not be made.
  * ------------------------------------------------------------------------- */
 hpf_status_t hpf_density_scatter_cells_static(const float* R, const uint8_t* T, int64_t N,

@@ -225,8 +225,8 @@ hpf_status_t hpf_density_scatter_cells_static(const float* R, const uint8_t* T, 
     const hpf_status_t st = static_scratch(&w);
     if (st != HPF_OK)
         return st;
-    // the stray counter at the head of the list is cleared by a kernel of the launch,
-    // and every brick overwrites its whole partial box
+    // every launch writes what it reads of the array: each brick its whole partial box, the length
+    // of its list of strays, and the number of long lists
     return launch_scatter_cells(R, T, N, tk, K, cell_start, counts, reinterpret_cast<uint32_t*>(w),
                                 reinterpret_cast<unsigned long long*>(w + sb), as_stream(stream));
 }

@@ -975,8 +975,8 @@ struct BeadLoads {
     bool ok;
 };
 
-// Cell of the bead, the corner loads of its lane pair (corners_pair; a bead that cannot be binned
-// loads the corners of cell 0 and gets no field force) and its partner loads (an index
+// Cell of the bead, its corner loads (with kPair those of its lane pair; a bead that cannot be
+// binned loads the corners of cell 0 and gets no field force) and its partner loads (an index
 // outside [0, N) loads the bead itself; the bond is then skipped or flagged).
 template <bool kPair, bool kThermo, bool kNT, int kD>
 __device__ __forceinline__ void bead_issue(BeadLoads<kD>& L, BeadIn<kD>& p, int64_t i, const MeshK& m, int K,
@@ -1136,14 +1136,14 @@ __global__ __launch_bounds__(kAdvPipeThreads) void k_advance(const float3* __res
 // Workgroup size: 512 threads (two workgroups of 8 waves per CU at 4 waves
 // per SIMD); with the software-pipelined loop this measured faster than 256
 // threads at every mesh size tried, and a small mesh still fills the chip.
-// kPipe selects the software-pipelined bead loop (bond tables of at most
-// kPreBonds rows, gradient meshes of at most kBufMeshBytes); the plain loop serves
+// kPipe selects the software-pipelined bead loop (bond tables of at most kD
+// rows, gradient meshes of at most kBufMeshBytes); the plain loop serves
 // the others. kNT puts the nontemporal hint on the pipelined loop's streamed data
 // and on the stored deposit boxes.
 constexpr int kASThreadsDefault = 512;
 constexpr int kASThreadsWide = 768;
 // The thermostat's pipelined form needs more than 128 VGPRs, so a CU holds 3 waves per SIMD of
-// it: three workgroups of 256 threads, but only one of 512 (3.3M beads in 2028 bricks: 137 against
+// it: three workgroups of 256 threads, but only one of 512 (3.3M beads in 2028 bricks: 120 against
 // 189 us; 384 threads, whose second workgroup did not fit either, 219). With a CU for each brick
 // the one workgroup has the more threads the better: 512 (100,000 beads in 125 bricks: 22 us
 // against 30).
@@ -1218,7 +1218,7 @@ k_advance_scatter(
             const int64_t first = cell_start[item];
             const int64_t last = min((int64_t)cell_start[item + 1], N);
             if (kPipe) {
-                // Bond table of at most kPreBonds rows. The next bead's own loads go out
+                // Bond table of at most kD rows. The next bead's own loads go out
                 // after this bead's corner and partner loads (the scheduling barriers keep
                 // that order) and stay in flight through its arithmetic; a thread's last
                 // bead fetches a valid bead again.

@@ -14,8 +14,8 @@
 //           (per axis the own brick and at most one neighbour) and stores the
 //           count;
 //   fixup   beads that moved more than h cells out of their brick since the
-//           sort, and beads the sort could not bin, are added with global u64
-//           atomics.
+//           sort (listed by pass 1, long lists found by pass 2), and beads the
+//           sort could not bin, are added with global u64 atomics.
 //
 // Every bead is deposited exactly once, integer addition is exact and order
 // free, so the counts equal those of hpf_density_scatter bit for bit.

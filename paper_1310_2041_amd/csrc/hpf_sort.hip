@@ -530,10 +530,10 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_angles(const int32_t* __r
 // The result equals the stable counting sort's exactly: (key, tag) order.
 // Step 1 reads 16 B a bead and writes 4; only movers cost more. A workgroup reads 4096 beads
 // between barriers, all rows before the first key, and counts its movers in an LDS table of
-// the few keys they go to, with one global atomic per key. 42M beads in 13,824 bricks: keys
-// 287 us, movers 63, placement 475 with the inverse, rows 920. (With 256 beads between
-// barriers, every bead's key written and read again and the stayers' tags searched in global
-// memory: 350, 290, 581, and 1060 for the rows, bonds and inverse.) A single round of bricks
+// the few keys they go to, with one global atomic per key. 42M beads in 13,824 bricks, 10 steps
+// after their sort: keys 277 us, movers 46, placement 415 with the inverse, rows 827. (With 256
+// beads between barriers, every bead's key written and read again and the stayers' tags searched
+// in global memory: 350, 290, 581, and 1060 for the rows, bonds and inverse.) A single round of bricks
 // (1M beads in 512) takes 95 us, as the full sort does.
 // Small bricks take workgroups of 128 threads in the key pass, one row a thread, and a wavefront
 // each in the placement, where a workgroup of 512 threads spends its time on barriers and on

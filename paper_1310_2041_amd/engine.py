@@ -86,8 +86,7 @@ class HpfState:
         # Force interpolation (Algorithm 1 Kernels 3-4): "centred" = centred differences at the
         # mesh points gathered with the deposit's weights (hpf_field_gradient +
         # hpf_force_gather, and the fused passes); "staggered" = the paper-literal backward /
-        # forward differences at the nearest mesh point (hpf_force_gather_staggered; the
-        # six-call step only).
+        # forward differences at the nearest mesh point (step() only).
         if stencil not in ("centred", "staggered"):
             raise ValueError("stencil must be 'centred' or 'staggered'")
         self.stencil = stencil
@@ -133,8 +132,8 @@ class HpfState:
         self.bonds = up(bonds, torch.int32) if bonds is not None and len(bonds) else \
             torch.zeros((0, self.N), dtype=torch.int32, device=dev)
         self.F = torch.zeros((self.N, 3), dtype=torch.float32, device=dev)
-        # angles (Bonded forces section): per-bead table [3A, N] and per-type parameters; the
-        # six-call step evaluates them (the fused passes take bonds only)
+        # angles (Bonded forces section): per-bead table [3A, N] and per-type parameters; step()
+        # evaluates them (the fused passes of step_fused() take bonds only)
         self.angles = up(angles, torch.int32) if angles is not None and len(angles) else None
         self.angles2 = torch.empty_like(self.angles) if self.angles is not None else None
         self.angle_params = (tuple(angle_k), tuple(angle_theta0), tuple(angle_form))
